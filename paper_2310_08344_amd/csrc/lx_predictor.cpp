@@ -20,6 +20,7 @@ struct lx_predictor {
     float* scratch = nullptr;
     size_t scratch_rows = 0;
     int* d_idx = nullptr;
+    int* h_idx = nullptr;        // the same list in pinned host memory
     size_t idx_cap = 0;
     double* h_loss = nullptr;    // pinned
     float* d_x = nullptr;        // lx_phi_leja_learned: features [n][8]
@@ -65,9 +66,11 @@ lx_status grow_idx(lx_predictor* p, size_t n) {
     if (n <= p->idx_cap) return LX_OK;
     (void)hipStreamSynchronize(p->ctx->stream);
     (void)hipFree(p->d_idx);
-    p->d_idx = nullptr;
+    (void)hipHostFree(p->h_idx);
+    p->d_idx = p->h_idx = nullptr;
     p->idx_cap = 0;
-    if (hipMalloc(&p->d_idx, sizeof(int) * n) != hipSuccess)
+    if (hipMalloc(&p->d_idx, sizeof(int) * n) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&p->h_idx), sizeof(int) * n, hipHostMallocDefault) != hipSuccess)
         return lx_internal_fail(p->ctx, LX_ENOMEM, "minibatch index list of %zu entries", n);
     p->idx_cap = n;
     return LX_OK;
@@ -124,6 +127,7 @@ void lx_predictor_destroy(lx_predictor* p) {
     (void)hipFree(p->d_loss);
     (void)hipFree(p->scratch);
     (void)hipFree(p->d_idx);
+    (void)hipHostFree(p->h_idx);
     (void)hipHostFree(p->h_loss);
     (void)hipFree(p->d_x);
     (void)hipFree(p->d_y);
@@ -229,18 +233,28 @@ lx_status lx_predictor_train(lx_predictor* p, const float* d_x, const float* d_y
     lx_status s = grow_scratch(p, static_cast<size_t>(batch));
     if (s == LX_OK) s = grow_idx(p, total);
     if (s != LX_OK) return s;
-    std::vector<int> idx(total);
     if (order != nullptr) {
-        for (size_t i = 0; i < total; ++i) {
+        for (size_t i = 0; i < total; ++i)
             if (order[i] < 0 || order[i] >= n) return lx_internal_fail(ctx, LX_EINVAL, "order[%zu] out of range", i);
-            idx[i] = order[i];
-        }
-    } else {
-        // epochs of a Fisher-Yates shuffle driven by splitmix64
-        std::vector<int> perm(static_cast<size_t>(n));
-        uint64_t st = seed;
-        size_t pos = static_cast<size_t>(n);
-        for (size_t i = 0; i < total; ++i) {
+    }
+    // The minibatches' indices go to the device kIdxSteps steps at a time and
+    // the next ones are drawn while the GPU trains on these: drawing all of
+    // them first kept it idle for 1.3 ms of a call of 200 steps of 512 (of
+    // 6.4 ms).  Each copy has its own part of the pinned list.
+    constexpr int kIdxSteps = 8;
+    int* idx = p->h_idx;
+    // epochs of a Fisher-Yates shuffle driven by splitmix64
+    std::vector<int> perm(order == nullptr ? static_cast<size_t>(n) : 0);
+    uint64_t st = seed;
+    size_t pos = static_cast<size_t>(n);
+    for (int k0 = 0; k0 < steps; k0 += kIdxSteps) {
+        const int ks = std::min(kIdxSteps, steps - k0);
+        const size_t i0 = static_cast<size_t>(k0) * batch, cnt = static_cast<size_t>(ks) * batch;
+        for (size_t i = i0; i < i0 + cnt; ++i) {
+            if (order != nullptr) {
+                idx[i] = order[i];
+                continue;
+            }
             if (pos == static_cast<size_t>(n)) {
                 for (int k = 0; k < n; ++k) perm[static_cast<size_t>(k)] = k;
                 for (int k = n - 1; k > 0; --k) {
@@ -251,18 +265,18 @@ lx_status lx_predictor_train(lx_predictor* p, const float* d_x, const float* d_y
             }
             idx[i] = perm[pos++];
         }
-    }
-    LXP_HIP(ctx, hipMemcpyAsync(p->d_idx, idx.data(), sizeof(int) * total, hipMemcpyHostToDevice, ctx->stream));
-    for (int k = 0; k < steps; ++k) {
-        LXP_HIP(ctx, lx::launch_mlp_fwd_bwd(p->theta, d_x, d_y, p->d_idx + static_cast<size_t>(k) * batch, batch, p->sc,
-                                            p->scratch, ctx->stream));
-        LXP_HIP(ctx, lx::launch_mlp_grad(p->scratch, batch, p->grad, k + 1 == steps ? p->d_loss : nullptr, ctx->stream));
-        p->t += 1;
-        LXP_HIP(ctx, lx::launch_mlp_adam(p->theta, p->grad, p->theta + lx::kMlpParams, p->theta + 2 * lx::kMlpParams,
-                                         p->t, lr, ctx->stream));
+        LXP_HIP(ctx, hipMemcpyAsync(p->d_idx + i0, idx + i0, sizeof(int) * cnt, hipMemcpyHostToDevice, ctx->stream));
+        for (int k = k0; k < k0 + ks; ++k) {
+            LXP_HIP(ctx, lx::launch_mlp_fwd_bwd(p->theta, d_x, d_y, p->d_idx + static_cast<size_t>(k) * batch, batch,
+                                                p->sc, p->scratch, ctx->stream));
+            p->t += 1;
+            LXP_HIP(ctx, lx::launch_mlp_grad_adam(p->scratch, batch, k + 1 == steps ? p->d_loss : nullptr, p->theta,
+                                                  p->theta + lx::kMlpParams, p->theta + 2 * lx::kMlpParams, p->t, lr,
+                                                  ctx->stream));
+        }
     }
     LXP_HIP(ctx, hipMemcpyAsync(p->h_loss, p->d_loss, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    LXP_HIP(ctx, hipStreamSynchronize(ctx->stream));   // idx (host vector) must outlive the copy
+    LXP_HIP(ctx, hipStreamSynchronize(ctx->stream));   // the index list is reused by the next call
     if (final_loss) *final_loss = *p->h_loss;
     return LX_OK;
 }

@@ -2,13 +2,14 @@
 // 8 -> 64 -> 64 -> 2 with ReLU, float32 weights and bfloat16 hidden
 // activations, trained with Adam on the mean squared error.
 //
-// Training step on a minibatch of B samples:
-//   mlp_fwd_bwd_kernel  one thread per sample: standardise, forward, loss,
-//                       backward to the per-sample deltas (float32); writes
-//                       the sample's inputs, activations and deltas
+// Training step on a minibatch of B samples, two launches:
+//   mlp_fwd_bwd_kernel  one wavefront per sample, a lane per hidden unit:
+//                       standardise, forward, loss, backward to the
+//                       per-sample deltas (float32); writes the sample's
+//                       inputs, activations and deltas
 //   mlp_grad_kernel     one thread per parameter: sums its gradient over the
-//                       minibatch in sample order (float64 accumulation)
-//   mlp_adam_kernel     one thread per parameter
+//                       minibatch in sample order (float64 accumulation) and
+//                       takes the parameter's Adam step
 // The network is tiny (4866 parameters, ~4.7k multiply-adds per sample):
 // the kernels are latency-bound, and the fixed summation order makes every
 // step deterministic.
@@ -71,112 +72,223 @@ __device__ __forceinline__ void forward_one(const Net& n, const float (&x)[kMlpI
     }
 }
 
-__global__ __launch_bounds__(kT) void mlp_fwd_bwd_kernel(const float* __restrict__ theta,
-                                                         const float* __restrict__ X, const float* __restrict__ Y,
-                                                         const int* __restrict__ idx, int B, MlpScaling sc,
-                                                         float* __restrict__ scratch) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B) return;
+constexpr int kFbWaves = 4;              // samples (wavefronts) per workgroup at a time
+constexpr int kW2Pitch = kMlpH + 1;      // LDS row pitch: rows and columns of W2 both without bank conflicts
+
+// One wavefront per sample, lane i its hidden unit i.  W2 sits in LDS: lane
+// i reads row i in the forward pass and column i in the backward pass, and
+// the other layer's values are broadcast from LDS.  Every sum runs over its
+// terms in index order from the bias (forward) or 0 (backward), one FMA
+// each, as one thread per sample would take them, so the values do not
+// depend on how the minibatch is split.  What bounds it is the chain of
+// 64 + 64 + 64 dependent FMAs and the staging of W2 from L2: 8.7 us at B = 512
+// where one thread per sample (two workgroups in all) took 70.
+__global__ __launch_bounds__(64 * kFbWaves) void mlp_fwd_bwd_kernel(const float* __restrict__ theta,
+                                                                    const float* __restrict__ X,
+                                                                    const float* __restrict__ Y,
+                                                                    const int* __restrict__ idx, int B, MlpScaling sc,
+                                                                    float* __restrict__ scratch) {
+    __shared__ float w2[kMlpH * kW2Pitch];
+    __shared__ __attribute__((aligned(16))) float act[kFbWaves][3][kMlpH];   // a1, a2, dz2 of each wavefront's sample
     const Net n = net_of(theta);
-    const int r = idx ? idx[s] : s;
-    float x[kMlpIn], t[kMlpOut];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int e = tid; e < kMlpH * kMlpH; e += 64 * kFbWaves) w2[(e >> 6) * kW2Pitch + (e & 63)] = n.W2[e];
+    float w1[kMlpIn];
 #pragma unroll
-    for (int j = 0; j < kMlpIn; ++j) x[j] = (X[static_cast<long>(r) * kMlpIn + j] - sc.mean_x[j]) / sc.std_x[j];
+    for (int j = 0; j < kMlpIn; ++j) w1[j] = n.W1[lane * kMlpIn + j];
+    const float b1 = n.b1[lane], b2 = n.b2[lane];
+    float w3[kMlpOut];
 #pragma unroll
-    for (int o = 0; o < kMlpOut; ++o) t[o] = (Y[static_cast<long>(r) * kMlpOut + o] - sc.mean_y[o]) / sc.std_y[o];
-    float a1[kMlpH], a2[kMlpH], y[kMlpOut];
-    forward_one(n, x, a1, a2, y);
-    float* __restrict__ row = scratch + static_cast<long>(s) * kMlpRow;
-    float dY[kMlpOut];
-    float loss = 0.0f;
-    const float scale = 2.0f / static_cast<float>(B * kMlpOut);
+    for (int o = 0; o < kMlpOut; ++o) w3[o] = n.W3[o * kMlpH + lane];
+    __syncthreads();
+    // the loop bound is the same for all wavefronts of a workgroup (they meet
+    // at the barriers); one past the end computes the last sample again and
+    // stores nothing
+    for (int s0 = static_cast<int>(blockIdx.x) * kFbWaves; s0 < B; s0 += static_cast<int>(gridDim.x) * kFbWaves) {
+        const bool live = s0 + wave < B;
+        const int s = live ? s0 + wave : B - 1;
+        const int r = idx ? idx[s] : s;
+        float x[kMlpIn], t[kMlpOut];
 #pragma unroll
-    for (int o = 0; o < kMlpOut; ++o) {
-        const float d = y[o] - t[o];
-        loss = fmaf(d, d, loss);
-        dY[o] = scale * d;
-    }
-    // dz2 = (W3^T dY) * [a2 > 0]   (a2 > 0 exactly when z2 > 0)
-    float dz2[kMlpH];
-    for (int j = 0; j < kMlpH; ++j) {
+        for (int j = 0; j < kMlpIn; ++j) x[j] = (X[static_cast<long>(r) * kMlpIn + j] - sc.mean_x[j]) / sc.std_x[j];
+#pragma unroll
+        for (int o = 0; o < kMlpOut; ++o) t[o] = (Y[static_cast<long>(r) * kMlpOut + o] - sc.mean_y[o]) / sc.std_y[o];
+        float z = b1;
+#pragma unroll
+        for (int j = 0; j < kMlpIn; ++j) z = fmaf(w1[j], x[j], z);
+        const float a1 = to_bf16(fmaxf(z, 0.0f));
+        act[wave][0][lane] = a1;
+        __syncthreads();
+        z = b2;
+#pragma unroll
+        for (int j = 0; j < kMlpH; ++j) z = fmaf(w2[lane * kW2Pitch + j], act[wave][0][j], z);
+        const float a2 = to_bf16(fmaxf(z, 0.0f));
+        act[wave][1][lane] = a2;
+        __syncthreads();
+        float dY[kMlpOut], loss = 0.0f;
+        const float scale = 2.0f / static_cast<float>(B * kMlpOut);
+        {
+            // lanes with the same parity form the same output
+            const int o = lane & 1;
+            float y = n.b3[o];
+#pragma unroll
+            for (int j = 0; j < kMlpH; ++j) y = fmaf(n.W3[o * kMlpH + j], act[wave][1][j], y);
+#pragma unroll
+            for (int k = 0; k < kMlpOut; ++k) {
+                const float d = __shfl(y, k, 64) - t[k];
+                loss = fmaf(d, d, loss);
+                dY[k] = scale * d;
+            }
+        }
+        // dz2 = (W3^T dY) * [a2 > 0]   (a2 > 0 exactly when z2 > 0)
         float g = 0.0f;
 #pragma unroll
-        for (int o = 0; o < kMlpOut; ++o) g = fmaf(n.W3[o * kMlpH + j], dY[o], g);
-        dz2[j] = a2[j] > 0.0f ? g : 0.0f;
-    }
-    // dz1 = (W2^T dz2) * [a1 > 0]
-    for (int j = 0; j < kMlpH; ++j) {
-        float g = 0.0f;
-        for (int i = 0; i < kMlpH; ++i) g = fmaf(n.W2[i * kMlpH + j], dz2[i], g);
-        row[kOffDz1 + j] = a1[j] > 0.0f ? g : 0.0f;
-    }
+        for (int o = 0; o < kMlpOut; ++o) g = fmaf(w3[o], dY[o], g);
+        const float dz2 = a2 > 0.0f ? g : 0.0f;
+        act[wave][2][lane] = dz2;
+        __syncthreads();
+        // dz1 = (W2^T dz2) * [a1 > 0]
+        g = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kMlpIn; ++j) row[kOffX + j] = x[j];
-    for (int j = 0; j < kMlpH; ++j) {
-        row[kOffA1 + j] = a1[j];
-        row[kOffA2 + j] = a2[j];
-        row[kOffDz2 + j] = dz2[j];
-    }
+        for (int i = 0; i < kMlpH; ++i) g = fmaf(w2[i * kW2Pitch + lane], act[wave][2][i], g);
+        if (live) {
+            float* __restrict__ row = scratch + static_cast<long>(s) * kMlpRow;
+            row[kOffA1 + lane] = a1;
+            row[kOffA2 + lane] = a2;
+            row[kOffDz1 + lane] = a1 > 0.0f ? g : 0.0f;
+            row[kOffDz2 + lane] = dz2;
+            if (lane == 0) {
 #pragma unroll
-    for (int o = 0; o < kMlpOut; ++o) row[kOffDy + o] = dY[o];
-    row[kOffLoss] = loss;
+                for (int j = 0; j < kMlpIn; ++j) row[kOffX + j] = x[j];
+#pragma unroll
+                for (int o = 0; o < kMlpOut; ++o) row[kOffDy + o] = dY[o];
+                row[kOffLoss] = loss;
+            }
+        }
+    }
 }
 
-// gradient of parameter p summed over the minibatch in sample order
-__global__ __launch_bounds__(kT) void mlp_grad_kernel(const float* __restrict__ scratch, int B,
-                                                      float* __restrict__ grad, double* __restrict__ loss_out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0 && loss_out != nullptr) {
-        double L = 0.0;
-        for (int s = 0; s < B; ++s) L += scratch[static_cast<long>(s) * kMlpRow + kOffLoss];
-        *loss_out = L / (static_cast<double>(B) * kMlpOut);
+constexpr int kGradChunk = 128;   // samples staged at a time
+constexpr int kGradThreads = 256;
+constexpr int kGradWin = 64;      // floats of a sample's row in each of the two staged windows
+
+// Gradient of every parameter summed over the minibatch in sample order, then
+// (kAdam) its Adam step t.  Workgroup g holds the parameters 64 g .. 64 g +
+// 63, all of one layer's weights or biases: gradient = sum over the samples
+// of row[off_a] * row[off_b].  A parameter's sum is a chain of B dependent
+// FP64 FMAs (2 us at B = 512), which the first wavefront runs; what bounds
+// the kernel beside it is the latency of the factors, so all four wavefronts
+// stage the two windows of 64 floats that hold them through LDS, one chunk
+// of samples ahead, with every load of a chunk in flight at once.  Per
+// launch at B = 512: 245 us with one pair of loads in flight per sum, 22
+// with 32 pairs, 13.6 from LDS (the Adam step had 5.5 us of its own besides).
+template <bool kAdam>
+__global__ __launch_bounds__(kGradThreads) void mlp_grad_kernel(const float* __restrict__ scratch, int B,
+                                                                float* __restrict__ grad,
+                                                                double* __restrict__ loss_out,
+                                                                float* __restrict__ theta, float* __restrict__ m,
+                                                                float* __restrict__ v, int t, float lr, float beta1,
+                                                                float beta2, float eps) {
+    const int tid = threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {
+        // the loss has a workgroup of its own, after the parameters'
+        if (tid == 0 && loss_out != nullptr) {
+            double L = 0.0;
+            for (int s = 0; s < B; ++s) L += scratch[static_cast<long>(s) * kMlpRow + kOffLoss];
+            *loss_out = L / (static_cast<double>(B) * kMlpOut);
+        }
+        return;
     }
-    if (p >= kMlpParams) return;
-    int off_a, off_b;   // gradient = sum_s row[off_a] * row[off_b] (off_b < 0: bias)
-    if (p < kPW1 + kMlpH * kMlpIn) {
-        const int q = p - kPW1;
-        off_a = kOffDz1 + q / kMlpIn;
-        off_b = kOffX + q % kMlpIn;
-    } else if (p < kPB1 + kMlpH) {
+    const int p = static_cast<int>(blockIdx.x) * 64 + (tid & 63);
+    int off_a, off_b, win_b;   // the windows are the same for the whole workgroup
+    bool bias = false;
+    if (p < kPB1) {
+        off_a = kOffDz1 + (p - kPW1) / kMlpIn;
+        off_b = kOffX + (p - kPW1) % kMlpIn;
+        win_b = kOffX;
+    } else if (p < kPW2) {
         off_a = kOffDz1 + (p - kPB1);
-        off_b = -1;
-    } else if (p < kPW2 + kMlpH * kMlpH) {
-        const int q = p - kPW2;
-        off_a = kOffDz2 + q / kMlpH;
-        off_b = kOffA1 + q % kMlpH;
-    } else if (p < kPB2 + kMlpH) {
+        bias = true;
+        win_b = kOffX;
+    } else if (p < kPB2) {
+        off_a = kOffDz2 + (p - kPW2) / kMlpH;
+        off_b = kOffA1 + (p - kPW2) % kMlpH;
+        win_b = kOffA1;
+    } else if (p < kPW3) {
         off_a = kOffDz2 + (p - kPB2);
-        off_b = -1;
-    } else if (p < kPW3 + kMlpOut * kMlpH) {
-        const int q = p - kPW3;
-        off_a = kOffDy + q / kMlpH;
-        off_b = kOffA2 + q % kMlpH;
+        bias = true;
+        win_b = kOffX;
+    } else if (p < kPB3) {
+        off_a = kOffDy + (p - kPW3) / kMlpH;
+        off_b = kOffA2 + (p - kPW3) % kMlpH;
+        win_b = kOffA2;
     } else {
-        off_a = kOffDy + (p - kPB3);
-        off_b = -1;
+        off_a = kOffDy + (p < kMlpParams ? p - kPB3 : 0);
+        bias = true;
+        win_b = kOffX;
     }
+    const int win_a = p < kPW2 ? kOffDz1 : (p < kPW3 ? kOffDz2 : kMlpRow - kGradWin);
+    const int ia = off_a - win_a, ib = bias ? 0 : off_b - win_b;
+    static_assert(kPB1 % 64 == 0 && kPW2 % 64 == 0 && kPB2 % 64 == 0 && kPW3 % 64 == 0 && kPB3 % 64 == 0,
+                  "a workgroup's parameters share their windows");
+    static_assert(kMlpRow % 4 == 0 && kOffA1 % 4 == 0 && kOffA2 % 4 == 0 && kOffDz1 % 4 == 0 && kOffDz2 % 4 == 0 &&
+                      kOffDy >= kMlpRow - kGradWin && kOffX + kGradWin <= kMlpRow,
+                  "16-byte windows inside a row");
+    __shared__ __attribute__((aligned(16))) float lds[2][2][kGradChunk][kGradWin];
+    constexpr int kVec = kGradWin / 4;                              // float4 of a window
+    constexpr int kLoads = kGradChunk * kVec / kGradThreads;        // per thread, window and chunk
+    float4 ra[kLoads], rb[kLoads];
+    auto load = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int e = i * kGradThreads + tid, s = s0 + e / kVec, c = (e % kVec) * 4;
+            ra[i] = rb[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};         // samples past the last one add 0
+            if (s < B) {
+                const float* row = scratch + static_cast<long>(s) * kMlpRow;
+                ra[i] = *reinterpret_cast<const float4*>(row + win_a + c);
+                rb[i] = *reinterpret_cast<const float4*>(row + win_b + c);
+            }
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int e = i * kGradThreads + tid;
+            *reinterpret_cast<float4*>(&lds[buf][0][e / kVec][(e % kVec) * 4]) = ra[i];
+            *reinterpret_cast<float4*>(&lds[buf][1][e / kVec][(e % kVec) * 4]) = rb[i];
+        }
+    };
     double acc = 0.0;
-    for (int s = 0; s < B; ++s) {
-        const float* row = scratch + static_cast<long>(s) * kMlpRow;
-        const double a = row[off_a];
-        acc += off_b >= 0 ? a * static_cast<double>(row[off_b]) : a;
+    load(0);
+    store(0);
+    __syncthreads();
+    int buf = 0;
+    for (int s0 = 0; s0 < B; s0 += kGradChunk, buf ^= 1) {
+        const bool more = s0 + kGradChunk < B;
+        if (more) load(s0 + kGradChunk);
+        if (tid < 64) {
+#pragma unroll 16
+            for (int s = 0; s < kGradChunk; ++s) {
+                const float fb = lds[buf][1][s][ib];
+                acc = fma(static_cast<double>(lds[buf][0][s][ia]), bias ? 1.0 : static_cast<double>(fb), acc);
+            }
+        }
+        if (more) store(buf ^ 1);
+        __syncthreads();
     }
-    grad[p] = static_cast<float>(acc);
-}
-
-__global__ __launch_bounds__(kT) void mlp_adam_kernel(float* __restrict__ theta, const float* __restrict__ grad,
-                                                      float* __restrict__ m, float* __restrict__ v, int t, float lr,
-                                                      float beta1, float beta2, float eps) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kMlpParams) return;
-    const float g = grad[p];
-    const float mm = beta1 * m[p] + (1.0f - beta1) * g;
-    const float vv = beta2 * v[p] + (1.0f - beta2) * g * g;
-    m[p] = mm;
-    v[p] = vv;
-    const float mhat = mm / (1.0f - powf(beta1, static_cast<float>(t)));
-    const float vhat = vv / (1.0f - powf(beta2, static_cast<float>(t)));
-    theta[p] -= lr * mhat / (sqrtf(vhat) + eps);
+    if (tid >= 64 || p >= kMlpParams) return;
+    const float g = static_cast<float>(acc);
+    if constexpr (kAdam) {
+        const float mm = beta1 * m[p] + (1.0f - beta1) * g;
+        const float vv = beta2 * v[p] + (1.0f - beta2) * g * g;
+        m[p] = mm;
+        v[p] = vv;
+        const float mhat = mm / (1.0f - powf(beta1, static_cast<float>(t)));
+        const float vhat = vv / (1.0f - powf(beta2, static_cast<float>(t)));
+        theta[p] -= lr * mhat / (sqrtf(vhat) + eps);
+    } else {
+        grad[p] = g;
+    }
 }
 
 __global__ __launch_bounds__(kT) void mlp_infer_kernel(const float* __restrict__ theta, const float* __restrict__ X,
@@ -241,18 +353,24 @@ __global__ __launch_bounds__(kT) void features_kernel(const FeatureInst* __restr
 
 hipError_t launch_mlp_fwd_bwd(const float* theta, const float* X, const float* Y, const int* idx, int B,
                               const MlpScaling& sc, float* scratch, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3((B + kT - 1) / kT), dim3(kT), 0, s, theta, X, Y, idx, B, sc, scratch);
+    // at most four workgroups per CU; larger minibatches loop
+    const int nb = B < 4096 ? (B + kFbWaves - 1) / kFbWaves : 1024;
+    hipLaunchKernelGGL(mlp_fwd_bwd_kernel, dim3(nb), dim3(64 * kFbWaves), 0, s, theta, X, Y, idx, B, sc, scratch);
     return hipGetLastError();
 }
+
+constexpr int kGradBlocks = (kMlpParams + 63) / 64 + 1;   // the last one forms the loss
 
 hipError_t launch_mlp_grad(const float* scratch, int B, float* grad, double* loss, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3((kMlpParams + kT - 1) / kT), dim3(kT), 0, s, scratch, B, grad, loss);
+    hipLaunchKernelGGL(mlp_grad_kernel<false>, dim3(kGradBlocks), dim3(kGradThreads), 0, s, scratch, B, grad, loss, nullptr,
+                       nullptr, nullptr, 0, 0.0f, 0.0f, 0.0f, 0.0f);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_adam(float* theta, const float* grad, float* m, float* v, int t, float lr, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_adam_kernel, dim3((kMlpParams + kT - 1) / kT), dim3(kT), 0, s, theta, grad, m, v, t, lr,
-                       0.9f, 0.999f, 1e-8f);
+hipError_t launch_mlp_grad_adam(const float* scratch, int B, double* loss, float* theta, float* m, float* v, int t,
+                                float lr, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_grad_kernel<true>, dim3(kGradBlocks), dim3(kGradThreads), 0, s, scratch, B, nullptr, loss, theta, m,
+                       v, t, lr, 0.9f, 0.999f, 1e-8f);
     return hipGetLastError();
 }
 

@@ -41,7 +41,9 @@ struct FeatureInst {
 hipError_t launch_mlp_fwd_bwd(const float* theta, const float* X, const float* Y, const int* idx, int B,
                               const MlpScaling& sc, float* scratch, hipStream_t s);
 hipError_t launch_mlp_grad(const float* scratch, int B, float* grad, double* loss, hipStream_t s);
-hipError_t launch_mlp_adam(float* theta, const float* grad, float* m, float* v, int t, float lr, hipStream_t s);
+// the same gradient, applied at once as Adam step t (beta 0.9/0.999, eps 1e-8) to theta, m and v
+hipError_t launch_mlp_grad_adam(const float* scratch, int B, double* loss, float* theta, float* m, float* v, int t,
+                                float lr, hipStream_t s);
 hipError_t launch_mlp_infer(const float* theta, const float* X, int n, const MlpScaling& sc, float* Y,
                             hipStream_t s);
 hipError_t launch_features(const FeatureInst* fi, int n, float* X, hipStream_t s);
