@@ -28,9 +28,10 @@
  *   Listing 10: allocate once per object, free in the destructor).
  *   All device work is enqueued on the stream given to lx_create; every call
  *   that returns host values waits for that stream once, at its end, except
- *   that a Leja loop returns as soon as it has read its final state: the few
- *   launches it enqueued past the end then still run on the stream (they
- *   read the loop state and return; every output is final on return).
+ *   that a Leja loop and lx_spectrum return as soon as they have read their
+ *   final state: the launch that wrote it and the few a loop enqueued past
+ *   its end then still run on the stream (the latter read the loop state and
+ *   return; every output is final on return).
  *   A context is not thread-safe: one host thread at a time per context.
  *   Every call returns an lx_status; on an error other than LX_ENOTCONV the
  *   outputs are unspecified and lx_last_error() holds a message.

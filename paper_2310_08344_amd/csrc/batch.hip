@@ -12,7 +12,6 @@
 // well, so a whole batch runs without a host round trip per instance.
 #include <hip/hip_runtime.h>
 
-#include "dd_math.h"
 #include "lx_device.h"
 #include "stencil_coeffs.h"
 #include "sweep_device.h"
@@ -21,9 +20,6 @@ namespace lx {
 namespace {
 
 using namespace dev;
-
-constexpr int kCoefThreads = 64;
-constexpr int kMaxCoef = 1008;   // coefficients per instance: up to max_iters + 1 + the window depth
 
 struct Who {
     int i;   // instance
@@ -152,44 +148,6 @@ __global__ __launch_bounds__(kBlockThreads) void batch_power_final_kernel(BatchI
     }
 }
 
-// Newton coefficients d_0..d_{ld-1} of phi_l(h (c + gamma xi)) for one
-// instance per workgroup of one wavefront: values at the Leja points in
-// double-double, then the divided-difference table column by column
-//     d_k <- (d_k - d_{k-1}) / (xi_k - xi_{k-j}),  k = ld-1 .. j,
-// in chunks of 64 from the top, every chunk reading before it writes.
-__global__ __launch_bounds__(kCoefThreads) void batch_coeffs_kernel(const BatchInst* insts,
-                                                                    const double* __restrict__ xi,
-                                                                    double* __restrict__ coef, const int ld) {
-    __shared__ double hi[kMaxCoef], lo[kMaxCoef];
-    const BatchInst& I = insts[blockIdx.x];
-    const int lane = threadIdx.x;
-    const int M = ld;
-    for (int j = lane; j < M; j += kCoefThreads) {
-        const dd f = dd_phi_at(I.l, 1.0, 1.0, I.h, I.c, I.gamma, xi[j]);
-        hi[j] = f.hi;
-        lo[j] = f.lo;
-    }
-    __syncthreads();
-    for (int jj = 1; jj < M; ++jj) {
-        for (int top = M - 1; top >= jj; top -= kCoefThreads) {
-            const int k = top - lane;
-            const bool act = k >= jj;
-            dd nv{0.0, 0.0};
-            if (act) {
-                const dd a{hi[k], lo[k]}, b{hi[k - 1], lo[k - 1]};
-                nv = dd_div(dd_sub(a, b), two_sum(xi[k], -xi[k - jj]));
-            }
-            __syncthreads();
-            if (act) {
-                hi[k] = nv.hi;
-                lo[k] = nv.lo;
-            }
-            __syncthreads();
-        }
-    }
-    for (int j = lane; j < M; j += kCoefThreads) coef[static_cast<long>(blockIdx.x) * ld + j] = hi[j] + lo[j];
-}
-
 __device__ __forceinline__ void sweep_coeffs(const BatchInst& I, SweepArgs& a) {
     if (I.kind == kOpDiffAdv) {
         a.aE = I.st[0];
@@ -310,13 +268,6 @@ hipError_t launch_batch_power_final(BatchInst* insts, int n_inst, const double* 
                                     double safety, hipStream_t s) {
     hipLaunchKernelGGL(batch_power_final_kernel, dim3(n_inst), dim3(kBlockThreads), 0, s, insts, partials, k_last,
                        safety);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_coeffs(const BatchInst* insts, int n_inst, const double* xi, double* coef, int ld,
-                               hipStream_t s) {
-    if (ld < 2 || ld > kMaxCoef) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(batch_coeffs_kernel, dim3(n_inst), dim3(kCoefThreads), 0, s, insts, xi, coef, ld);
     return hipGetLastError();
 }
 

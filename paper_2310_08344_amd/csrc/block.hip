@@ -636,7 +636,7 @@ __global__ __launch_bounds__(kBlockThreads) void power_block_final(PowerArgs a, 
             if (j == nlev - 1) last = tot[j];
             if (j == nlev - 2) prev = tot[j];
         }
-        a.ctl->rho = sqrt(last / prev);
+        publish_rho(a.rho, sqrt(last / prev));
     }
 }
 

@@ -38,6 +38,7 @@ __global__ __launch_bounds__(kBlockThreads) void leja_sweep(SweepArgs a, const i
     constexpr int NV = 1 + K;
     __shared__ SweepState s_cur;
     const int tid = flat_tid();
+    if (blockIdx.x == 0 && tid == 0) report_progress(a.progress, m);
     if (m == 0) {
         if (tid == 0) s_cur = ctl->slot[0];
     } else {
@@ -137,10 +138,10 @@ __global__ __launch_bounds__(kBlockThreads) void power_norm_kernel(const double*
 
 // rho = ||w_iters|| from the last sweep's partial sums
 __global__ __launch_bounds__(kBlockThreads) void power_final_kernel(int nb, const double* __restrict__ P,
-                                                                    LoopCtl* ctl) {
+                                                                    RhoRecord* rho) {
     double tot[1];
     sum_partials<1>(P, nb, tot);
-    if (threadIdx.x == 0) ctl->rho = sqrt(tot[0]);
+    if (threadIdx.x == 0) publish_rho(rho, sqrt(tot[0]));
 }
 
 // splitmix64 (Steele, Lea and Flood, OOPSLA 2014): state_i = seed + (i+1) *
@@ -381,8 +382,8 @@ hipError_t launch_power_norm(const double* x, long n, int nb, double* partials, 
     return hipGetLastError();
 }
 
-hipError_t launch_power_final(int nb, const double* partials, LoopCtl* ctl, hipStream_t s) {
-    hipLaunchKernelGGL(power_final_kernel, dim3(1), dim3(kBlockThreads), 0, s, nb, partials, ctl);
+hipError_t launch_power_final(int nb, const double* partials, RhoRecord* rho, hipStream_t s) {
+    hipLaunchKernelGGL(power_final_kernel, dim3(1), dim3(kBlockThreads), 0, s, nb, partials, rho);
     return hipGetLastError();
 }
 

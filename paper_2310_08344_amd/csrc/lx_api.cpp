@@ -1,9 +1,8 @@
 // C ABI of the Leja phi-action library (declarations and contracts in lx.h).
 //
-// Host side of the device-resident Leja loop: argument checks, the planner
-// (Leja points; divided differences produced a chunk ahead of the sweeps
-// that read them, while the GPU works), the initial loop state, then sweeps
-// enqueued in chunks.  The sweeps decide by themselves when to stop (a
+// Host side of the device-resident Leja loop: argument checks, the Leja
+// points, then sweeps enqueued in chunks, each chunk after the launch that
+// forms the Newton coefficients it reads.  The sweeps decide by themselves when to stop (a
 // converged loop turns later sweeps into no-ops); the host only looks at the
 // state once per chunk, one chunk behind, to stop enqueuing: the launch that
 // ends the loop writes the final state into pinned host memory, so looking
@@ -37,8 +36,7 @@ using lx::Tile;
 
 namespace {
 
-constexpr int kFirstChunk = 16;   // sweeps enqueued before the first look at the state
-constexpr int kChunk = 8;         // sweeps per later chunk
+constexpr int kCoefStep = 16;   // least Newton coefficients formed by one launch
 
 lx_status fail(lx_ctx* ctx, lx_status s, const char* fmt, ...) {
     if (ctx != nullptr) {
@@ -139,6 +137,44 @@ lx_status ensure_xi(lx_ctx* ctx, int M) {
     LX_HIP(ctx, hipMemcpyAsync(ctx->xi, ctx->h_xi, sizeof(double) * M, hipMemcpyHostToDevice, ctx->stream));
     LX_HIP(ctx, hipStreamSynchronize(ctx->stream));   // h_xi is reused by the next extension
     ctx->xi_uploaded = M;
+    return LX_OK;
+}
+
+// Waits until ready() (a read of pinned memory that a kernel on the stream
+// writes).  Every kQueryMs it asks whether the stream still runs (the query
+// puts a marker on it, which costs 6 us between two launches): *idle is set
+// if everything on it has finished without ready().
+constexpr double kQueryMs = 20.0;
+
+template <typename Ready>
+lx_status wait_for(lx_ctx* ctx, Ready ready, bool* idle) {
+    auto t0 = std::chrono::steady_clock::now();
+    for (unsigned n = 1;; ++n) {
+        if (ready()) return LX_OK;
+        if ((n & 255u) != 0) continue;
+        const auto t1 = std::chrono::steady_clock::now();
+        if (std::chrono::duration<double, std::milli>(t1 - t0).count() < kQueryMs) continue;
+        t0 = t1;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipSuccess) {
+            *idle = !ready();
+            return LX_OK;
+        }
+        if (e != hipErrorNotReady) return fail(ctx, LX_EDEVICE, "the stream failed: %s", hipGetErrorString(e));
+        // "not ready" is no error of the launches that follow
+        if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+    }
+}
+
+// The result of the power iteration whose final launch is enqueued.
+lx_status wait_rho(lx_ctx* ctx, double* rho) {
+    volatile lx::RhoRecord* r = ctx->h_rho;
+    bool idle = false;
+    const lx_status s = wait_for(ctx, [&] { return r->done != 0; }, &idle);
+    if (s != LX_OK) return s;
+    if (idle) return fail(ctx, LX_EDEVICE, "the power iteration did not record its result");
+    std::atomic_thread_fence(std::memory_order_acquire);
+    *rho = r->rho;
     return LX_OK;
 }
 
@@ -404,55 +440,36 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     const auto t0 = std::chrono::steady_clock::now();
     lx_status s = ensure_xi(ctx, NC);
     if (s != LX_OK) return s;
-    for (int k = 0; k < K; ++k)
-        ctx->series[k].reset(q.l[k], q.alpha[k], q.sigma[k], q.h, q.c, q.gamma, ctx->h_xi);
-    int have = 0;          // coefficients d_0..d_{have-1} computed and enqueued for upload
-    double plan_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+    const double plan_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     // the launch that ends the loop writes its final state here (pinned)
     volatile SweepState* pub = ctx->h_poll;
     pub->done = 0;
-    // stop_on_done: a look ahead, abandoned (nothing uploaded, *ended set)
-    // once the loop has published its final state; the series then no longer
-    // match `have`, and the caller ends the loop
-    auto ensure_coeffs = [&](int upto, bool* ended = nullptr) -> lx_status {
+    *ctx->h_progress = 0;
+    // the coefficients' first launch also writes the loop's initial state
+    lx::CoefArgs ca{};
+    ca.K = K;
+    for (int k = 0; k < K; ++k) ca.s[k] = lx::CoefSeries{q.alpha[k], q.sigma[k], q.h, q.c, q.gamma, q.l[k]};
+    ca.rtol = q.o.rtol;
+    ca.atol = q.o.atol;
+    ca.fp32_switch = fp32 ? q.o.fp32_switch : -1.0;
+    ca.max_iters = q.o.max_iters;
+    ca.out32 = (fp32 && q.o.fp32_switch == 0.0) ? 1 : 0;
+    int have = 0, rows = 0;   // coefficients d_0..d_{have-1} enqueued, from tables of `rows` rows
+    auto ensure_coeffs = [&](int upto) -> lx_status {
         upto = std::min(upto, NC);
         if (upto <= have) return LX_OK;
-        const auto ta = std::chrono::steady_clock::now();
-        for (int j = have; j < upto; ++j) {
-            if (ended != nullptr && pub->done) {
-                *ended = true;
-                plan_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - ta).count();
-                return LX_OK;
-            }
-            for (int k = 0; k < K; ++k) ctx->h_coef[static_cast<size_t>(k) * NC + j] = ctx->series[k].next();
+        // at least kCoefStep more: a launch costs more than a few columns
+        upto = std::min(std::max(upto, have + kCoefStep), NC);
+        const bool first = have == 0;
+        if (upto > rows) {   // tables with more rows start over (the same values again)
+            rows = lx::coef_rows(upto, NC);
+            have = 0;
         }
-        // one copy for all outputs (each copy is a launch on the stream): the
-        // span from d_have of output 0 to d_{upto-1} of output K-1 also
-        // carries the coefficients already on the device (the same values)
-        // and slots past upto that no launch reads before a later copy
-        // brings their final values
-        const size_t off = static_cast<size_t>(have);
-        const size_t len = static_cast<size_t>(K - 1) * NC + upto - have;
-        LX_HIP(ctx, hipMemcpyAsync(ctx->coef + off, ctx->h_coef + off, sizeof(double) * len, hipMemcpyHostToDevice,
-                                   ctx->stream));
+        LX_HIP(ctx, lx::launch_coeffs(ca, ctx->xi, ctx->coef_state, ctx->coef, NC, rows, have, upto,
+                                      first ? ctx->ctl : nullptr, ctx->stream));
         have = upto;
-        plan_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - ta).count();
         return LX_OK;
     };
-
-    LoopCtl& init = *ctx->h_ctl;
-    std::memset(&init, 0, sizeof(init));
-    init.rtol = q.o.rtol;
-    init.atol = q.o.atol;
-    init.fp32_switch = fp32 ? q.o.fp32_switch : -1.0;
-    init.max_iters = q.o.max_iters;
-    SweepState& s0 = init.slot[0];
-    s0.out32 = (fp32 && q.o.fp32_switch == 0.0) ? 1 : 0;
-    for (int k = 0; k < K; ++k) {
-        s0.active[k] = 1;
-        s0.iters[k] = q.o.max_iters;
-    }
-    LX_HIP(ctx, hipMemcpyAsync(ctx->ctl, &init, sizeof(LoopCtl), hipMemcpyHostToDevice, ctx->stream));
 
     if (fp32 && op.kind == LX_OP_BURGERS2D) LX_HIP(ctx, lx::launch_to_fp32(q.u, ctx->u32, N, ctx->stream));
 
@@ -494,6 +511,7 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     a.xi = ctx->xi;
     a.ctl = ctx->ctl;
     a.pub = ctx->h_poll;
+    a.progress = ctx->h_progress;
     const int opcode = opcode_of(op.kind);
     const size_t need_partials = 2 * static_cast<size_t>(a.nb) * (1 + K) * (blk ? D : (pair ? 2 : 1));
     if (q.scratch != nullptr) {
@@ -526,54 +544,34 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
         LX_HIP(ctx, hipEventRecord(ctx->tev[0], ctx->stream));
     }
     auto coeffs_for = [&](int launches) { return per * launches + 1; };   // d_0 .. d_{per*launches}
-    int launched = 0, chunk_id = 0, last_slot = -1;
-    // launches per chunk: about kFirstChunk and kChunk iterations, but at
-    // least three and two launches, so that the queue never runs dry while
-    // the host looks at the state of the chunk before.  A window is long
-    // enough on its own to hide the host's work on the next chunk's
-    // coefficients, so windows start with one launch: the GPU waits only for
-    // d_0..d_D, not for the first three windows' coefficients (the first
-    // look still comes after three launches).
-    const int first_chunk = blk ? 1 : std::max(3, kFirstChunk / per), next_chunk = std::max(2, kChunk / per);
-    int chunk = first_chunk;
-    bool seen_done = false;   // a look at the state found the final one
-    while (launched <= last) {
-        const int n = std::min(chunk, last + 1 - launched);
-        s = ensure_coeffs(coeffs_for(launched + n));
-        if (s != LX_OK) return s;
-        for (int i = 0; i < n; ++i) {
-            const int L = launched + i;
+    // A launch goes out once the launch `ahead` before it has started (it
+    // says so in pinned memory), so that the queue never runs dry and at
+    // most `ahead` launches run past the end of the loop.
+    const int ahead = blk ? 3 : 4;
+    volatile int* progress = ctx->h_progress;
+    int launched = 0;
+    bool idle = false;
+    while (!pub->done && !idle) {
+        const bool more = launched <= last;
+        if (more && launched < *progress + ahead) {
+            const int L = launched;
+            s = ensure_coeffs(coeffs_for(L + 1));
+            if (s != LX_OK) return s;
             if (t.stream) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
             else if (blk) LX_HIP(ctx, lx::launch_leja_block(opcode, K, t.th, D, a, L, ctx->stream));
             else if (pair) LX_HIP(ctx, lx::launch_leja_pair(opcode, K, t.th, a, L, ctx->stream));
             else LX_HIP(ctx, lx::launch_leja_sweep(opcode, K, fp32, t, a, L, ctx->stream));
             if (timing && L < last) LX_HIP(ctx, hipEventRecord(ctx->tev[L + 1], ctx->stream));
+            ++launched;
+            continue;
         }
-        launched += n;
-        const int slot = chunk_id & 1;
-        LX_HIP(ctx, hipEventRecord(ctx->poll_ev[slot], ctx->stream));
-        last_slot = slot;
-        if (chunk_id >= 1) {
-            // the next chunk's coefficients are prepared while the GPU works,
-            // unless the final state appears meanwhile (the host then returns
-            // at once instead of finishing them first)
-            s = ensure_coeffs(coeffs_for(std::min(launched + next_chunk, last)), &seen_done);
-            if (s != LX_OK) return s;
-            // the chunk before has run: has a launch published the final state?
-            if (!seen_done && !pub->done) LX_HIP(ctx, hipEventSynchronize(ctx->poll_ev[slot ^ 1]));
-            if (seen_done || pub->done) {
-                seen_done = true;
-                break;
-            }
-        }
-        ++chunk_id;
-        chunk = next_chunk;
+        s = wait_for(ctx, [&] { return pub->done != 0 || (more && launched < *progress + ahead); }, &idle);
+        if (s != LX_OK) return s;
     }
     // Once the final state is published, every launch that writes an output
     // has finished (they precede the publishing launch on the stream); the
     // launches still queued only read the loop state and return, so the call
     // does not wait for them.
-    if (!seen_done) LX_HIP(ctx, hipEventSynchronize(ctx->poll_ev[last_slot]));
     // the device writes `done` after the rest of the state (both at system
     // scope): what follows a read of done = 1 sees the whole state
     std::atomic_thread_fence(std::memory_order_acquire);
@@ -885,7 +883,7 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
     lx_status s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb) * (1 + DP));
     if (s != LX_OK) return s;
     a.partials = ctx->partials;
-    a.ctl = ctx->ctl;
+    a.rho = ctx->h_rho;
     const int nblk = (iters + per - 1) / per;
     if (ctx->timing) {
         s = ensure_timing_events(ctx, static_cast<size_t>(nblk) + 1);
@@ -895,6 +893,7 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
     // (when it makes a full DP levels); a NaN estimate from it means that
     // ||x0|| lay outside the range where that is safe, and the iteration
     // runs again with x0 scaled first
+    double rho = 0.0;
     auto run = [&](const bool raw) -> lx_status {
         if (!raw) LX_HIP(ctx, lx::launch_power_norm(x0, N, a.nb, ctx->partials, ctx->stream));
         if (ctx->timing) LX_HIP(ctx, hipEventRecord(ctx->tev[0], ctx->stream));
@@ -906,19 +905,17 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
             if (ctx->timing) LX_HIP(ctx, hipEventRecord(ctx->tev[b + 1], ctx->stream));
             prev = nlev;
         }
+        ctx->h_rho->done = 0;
         LX_HIP(ctx, lx::launch_power_stream_final(a, nblk - 1, nlev, raw, ctx->stream));
-        LX_HIP(ctx, hipMemcpyAsync(ctx->h_ctl, ctx->ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, ctx->stream));
-        LX_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        return LX_OK;
+        return wait_rho(ctx, &rho);
     };
     const bool raw = per == DP && iters >= DP;
     s = run(raw);
     if (s != LX_OK) return s;
-    if (raw && !std::isfinite(ctx->h_ctl->rho)) {
+    if (raw && !std::isfinite(rho)) {
         s = run(false);
         if (s != LX_OK) return s;
     }
-    const double rho = ctx->h_ctl->rho;
     lx_stats& S = ctx->stats;
     S.n_apply = iters;
     S.n_launch = nblk;
@@ -927,6 +924,7 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
     S.rho_hat = rho;
     S.bytes = 16.0 * static_cast<double>(N) * nblk;
     if (ctx->timing) {
+        LX_HIP(ctx, hipEventSynchronize(ctx->tev[nblk]));
         S.loop_ms = elapsed(ctx->tev[0], ctx->tev[nblk]);
         S.sweep_ms = S.loop_ms;
         S.first_sweep_ms = elapsed(ctx->tev[0], ctx->tev[1]);
@@ -1000,9 +998,12 @@ void lx_destroy(lx_ctx* ctx) {
     (void)hipFree(ctx->partials);
     (void)hipFree(ctx->ctl);
     (void)hipFree(ctx->coef);
+    (void)hipFree(ctx->coef_state);
     (void)hipFree(ctx->xi);
     (void)hipHostFree(ctx->h_ctl);
     (void)hipHostFree(ctx->h_poll);
+    (void)hipHostFree(ctx->h_progress);
+    (void)hipHostFree(ctx->h_rho);
     (void)hipHostFree(ctx->h_coef);
     (void)hipHostFree(ctx->h_xi);
     for (hipEvent_t e : ctx->poll_ev)
@@ -1034,11 +1035,13 @@ lx_status lx_create(lx_ctx** out, size_t n_max, int k_max, void* stream) {
     if (hipMalloc(&ctx->partials, sizeof(double) * ctx->partials_len) != hipSuccess) return bail(LX_ENOMEM);
     if (hipMalloc(&ctx->ctl, sizeof(LoopCtl)) != hipSuccess) return bail(LX_ENOMEM);
     if (hipMalloc(&ctx->coef, sizeof(double) * k_max * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
+    if (hipMalloc(&ctx->coef_state, sizeof(double) * k_max * 2 * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
     if (hipMalloc(&ctx->xi, sizeof(double) * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
     if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_ctl), sizeof(LoopCtl), hipHostMallocDefault) != hipSuccess)
         return bail(LX_ENOMEM);
-    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_poll), 2 * sizeof(SweepState), hipHostMallocDefault) !=
-        hipSuccess)
+    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_poll), sizeof(SweepState), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&ctx->h_progress), sizeof(int), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&ctx->h_rho), sizeof(lx::RhoRecord), hipHostMallocDefault) != hipSuccess)
         return bail(LX_ENOMEM);
     if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_coef), sizeof(double) * k_max * lx::kMaxPoints,
                       hipHostMallocDefault) != hipSuccess)
@@ -1049,7 +1052,9 @@ lx_status lx_create(lx_ctx** out, size_t n_max, int k_max, void* stream) {
     for (auto& e : ctx->poll_ev)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail(LX_EDEVICE);
     std::memset(ctx->h_ctl, 0, sizeof(LoopCtl));
-    std::memset(ctx->h_poll, 0, 2 * sizeof(SweepState));
+    std::memset(ctx->h_poll, 0, sizeof(SweepState));
+    std::memset(ctx->h_rho, 0, sizeof(lx::RhoRecord));
+    *ctx->h_progress = 0;
     if (hipMemcpyAsync(ctx->ctl, ctx->h_ctl, sizeof(LoopCtl), hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
         return bail(LX_EDEVICE);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(LX_EDEVICE);
@@ -1136,7 +1141,7 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb) * (1 + PD));
         if (s != LX_OK) return s;
         a.partials = ctx->partials;
-        a.ctl = ctx->ctl;
+        a.rho = ctx->h_rho;
         const int nblk = (iters + PD - 1) / PD;
         LX_HIP(ctx, lx::launch_power_norm(x0, N, a.nb, ctx->partials, ctx->stream));
         if (ctx->timing) {
@@ -1151,10 +1156,11 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
             LX_HIP(ctx, lx::launch_power_block(pcode, a, in, ctx->ybuf[b & 1], b, nlev, ctx->stream));
             if (ctx->timing) LX_HIP(ctx, hipEventRecord(ctx->tev[b + 1], ctx->stream));
         }
+        ctx->h_rho->done = 0;
         LX_HIP(ctx, lx::launch_power_block_final(a, nblk - 1, nlev, ctx->stream));
-        LX_HIP(ctx, hipMemcpyAsync(ctx->h_ctl, ctx->ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, ctx->stream));
-        LX_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        const double rho = ctx->h_ctl->rho;
+        double rho = 0.0;
+        s = wait_rho(ctx, &rho);
+        if (s != LX_OK) return s;
         lx_stats& S = ctx->stats;
         S.n_apply = iters;
         S.n_launch = nblk;
@@ -1162,6 +1168,7 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         S.rho_hat = rho;
         S.bytes = (op->kind == LX_OP_BURGERS2D ? 24.0 : 16.0) * static_cast<double>(N) * nblk;   // + u per launch
         if (ctx->timing) {
+            LX_HIP(ctx, hipEventSynchronize(ctx->tev[nblk]));
             S.loop_ms = elapsed(ctx->tev[0], ctx->tev[nblk]);
             S.sweep_ms = S.loop_ms;
             S.first_sweep_ms = elapsed(ctx->tev[0], ctx->tev[1]);
@@ -1206,7 +1213,6 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
     s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb));
     if (s != LX_OK) return s;
     a.partials = ctx->partials;
-    a.ctl = ctx->ctl;
     const int opcode = opcode_of(op->kind);
     // |x0|^2 partials into slot 1, read by sweep 0
     LX_HIP(ctx, lx::launch_power_norm(x0, N, a.nb, ctx->partials, ctx->stream));
@@ -1221,11 +1227,12 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         LX_HIP(ctx, lx::launch_power_sweep(opcode, t, a, k, ctx->stream));
         if (ctx->timing) LX_HIP(ctx, hipEventRecord(ctx->tev[k + 1], ctx->stream));
     }
-    LX_HIP(ctx, lx::launch_power_final(a.nb, ctx->partials + static_cast<size_t>((iters - 1) & 1) * a.nb, ctx->ctl,
+    ctx->h_rho->done = 0;
+    LX_HIP(ctx, lx::launch_power_final(a.nb, ctx->partials + static_cast<size_t>((iters - 1) & 1) * a.nb, ctx->h_rho,
                                        ctx->stream));
-    LX_HIP(ctx, hipMemcpyAsync(ctx->h_ctl, ctx->ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, ctx->stream));
-    LX_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    const double rho = ctx->h_ctl->rho;
+    double rho = 0.0;
+    s = wait_rho(ctx, &rho);
+    if (s != LX_OK) return s;
     lx_stats& S = ctx->stats;
     S.n_apply = iters;
     S.n_launch = iters;
@@ -1233,6 +1240,7 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
     S.rho_hat = rho;
     S.bytes = (16.0 + (op->kind == LX_OP_BURGERS2D ? 8.0 : 0.0)) * static_cast<double>(N) * iters;
     if (ctx->timing) {
+        LX_HIP(ctx, hipEventSynchronize(ctx->tev[iters]));
         S.loop_ms = elapsed(ctx->tev[0], ctx->tev[iters]);
         S.sweep_ms = S.loop_ms;
         S.first_sweep_ms = elapsed(ctx->tev[0], ctx->tev[1]);

@@ -110,6 +110,7 @@ void lx_internal_free_batch(lx_ctx* ctx) {
     (void)hipFree(b.d_ctl);
     (void)hipFree(b.d_block_inst);
     (void)hipFree(b.d_coef);
+    (void)hipFree(b.d_coef_state);
     (void)hipFree(b.d_partials);
     (void)hipFree(b.d_basis);
     (void)hipFree(b.d_done);
@@ -261,7 +262,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     lx_batch_ws& W = ctx->batch;
     lx_status s = LX_OK;
     const size_t nn = static_cast<size_t>(n), nblk = static_cast<size_t>(total_blocks);
-    const void* addr_before[] = {W.d_inst, W.d_ctl, W.d_block_inst, W.d_coef, W.d_partials, W.d_basis, W.d_done};
+    const void* addr_before[] = {W.d_inst, W.d_ctl, W.d_block_inst, W.d_coef, W.d_coef_state, W.d_partials, W.d_basis, W.d_done};
     if ((s = grow_device(ctx, reinterpret_cast<BatchInst**>(&W.d_inst), &W.cap_d_inst, nn)) != LX_OK ||
         (s = grow_device(ctx, reinterpret_cast<LoopCtl**>(&W.d_ctl), &W.cap_d_ctl, nn)) != LX_OK ||
         (s = grow_pinned(ctx, reinterpret_cast<BatchInst**>(&W.h_inst), &W.cap_h_inst, nn)) != LX_OK ||
@@ -269,6 +270,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         (s = grow_device(ctx, &W.d_block_inst, &W.cap_d_blk, nblk)) != LX_OK ||
         (s = grow_pinned(ctx, &W.h_block_inst, &W.cap_h_blk, nblk)) != LX_OK ||
         (s = grow_device(ctx, &W.d_coef, &W.cap_coef, nn * ld)) != LX_OK ||
+        (s = grow_device(ctx, &W.d_coef_state, &W.cap_coef_state, nn * 2 * ld)) != LX_OK ||
         (s = grow_device(ctx, &W.d_partials, &W.cap_partials, static_cast<size_t>(part_total))) != LX_OK ||
         (s = grow_device(ctx, &W.d_basis, &W.cap_basis, basis_total)) != LX_OK ||
         (s = grow_device(ctx, &W.d_done, &W.cap_done, 1)) != LX_OK ||
@@ -279,7 +281,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     {
         // a captured pipeline holds the workspace addresses: drop every one
         // once a workspace has moved
-        const void* addr_after[] = {W.d_inst, W.d_ctl, W.d_block_inst, W.d_coef, W.d_partials, W.d_basis, W.d_done};
+        const void* addr_after[] = {W.d_inst, W.d_ctl, W.d_block_inst, W.d_coef, W.d_coef_state, W.d_partials, W.d_basis, W.d_done};
         if (!std::equal(std::begin(addr_before), std::end(addr_before), std::begin(addr_after))) drop_graphs(W);
     }
 
@@ -325,8 +327,8 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     }
     const int last = blk ? (max_budget + BD - 1) / BD + 2 : (pair ? (max_budget + 1) / 2 + 1 : max_budget);
     const int per = blk ? BD : (pair ? 2 : 1);
-    // the device pipeline: spectral bounds (Listing 7), Newton coefficients,
-    // then window (or one- or two-iteration) launches first .. first+count-1
+    // the device pipeline: spectral bounds (Listing 7), then the Newton
+    // coefficients and the window (or one- or two-iteration) launches
     auto enqueue_head = [&](hipStream_t q) -> hipError_t {
         hipError_t e = hipSuccess;
         if (power_iters > 0) {
@@ -337,11 +339,24 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             if (e == hipSuccess)
                 e = lx::launch_batch_power_final(d_inst, n, W.d_partials, power_iters - 1, safety, q);
         }
-        if (e == hipSuccess) e = lx::launch_batch_coeffs(d_inst, n, ctx->xi, W.d_coef, ld, q);
         return e;
     };
-    auto enqueue_loop = [&](hipStream_t q, int first, int count) -> hipError_t {
+    // launches first .. first+count-1, after the launch that forms the Newton
+    // coefficients they read and cf does not yet hold
+    struct Coefs {
+        int have = 0, rows = 0;
+    };
+    auto enqueue_loop = [&](hipStream_t q, int first, int count, Coefs& cf) -> hipError_t {
         hipError_t e = hipSuccess;
+        const int upto = std::min(per * (first + count) + 1, ld);
+        if (upto > cf.have) {
+            if (upto > cf.rows) {   // tables with more rows start over (the same values again)
+                cf.rows = lx::coef_rows(upto, ld);
+                cf.have = 0;
+            }
+            e = lx::launch_batch_coeffs(d_inst, n, ctx->xi, W.d_coef_state, W.d_coef, ld, cf.rows, cf.have, upto, q);
+            cf.have = upto;
+        }
         for (int L = first; L < first + count && e == hipSuccess; ++L) {
             if (blk) {
                 e = lx::launch_batch_block(d_inst, d_ctl, W.d_block_inst, total_blocks, any_burgers, th, W.d_partials,
@@ -365,7 +380,8 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         key.push_back(sb);
         for (const void* a : {static_cast<const void*>(d_inst), static_cast<const void*>(d_ctl),
                               static_cast<const void*>(W.d_block_inst), static_cast<const void*>(W.d_partials),
-                              static_cast<const void*>(W.d_coef), static_cast<const void*>(W.d_done),
+                              static_cast<const void*>(W.d_coef), static_cast<const void*>(W.d_coef_state),
+                              static_cast<const void*>(W.d_done),
                               static_cast<const void*>(ctx->xi)})
             key.push_back(static_cast<long long>(reinterpret_cast<uintptr_t>(a)));
     }
@@ -378,6 +394,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
 
     int launched = 0, chunk_id = 0, last_slot = 0;
     bool finished = false;
+    Coefs cf;
     const bool replayed = graph != nullptr;
     if (graph != nullptr) {
         // one captured pipeline, then one look at the finished count; a batch
@@ -385,6 +402,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         graph->last_use = W.calls;
         LXB_HIP(ctx, hipGraphLaunch(graph->exec, st));
         launched = graph->launches;
+        cf = Coefs{graph->coef_have, graph->coef_rows};
         LXB_HIP(ctx, hipMemcpyAsync(&W.h_done[0], W.d_done, sizeof(unsigned), hipMemcpyDeviceToHost, st));
         LXB_HIP(ctx, hipEventRecord(ctx->poll_ev[0], st));
         LXB_HIP(ctx, hipEventSynchronize(ctx->poll_ev[0]));
@@ -403,7 +421,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     int chunk = graph != nullptr ? next_chunk : first_chunk;
     while (!finished && launched <= last) {
         const int cnt = std::min(chunk, last + 1 - launched);
-        LXB_HIP(ctx, enqueue_loop(st, launched, cnt));
+        LXB_HIP(ctx, enqueue_loop(st, launched, cnt, cf));
         launched += cnt;
         const int slot = chunk_id & 1;
         LXB_HIP(ctx, hipMemcpyAsync(&W.h_done[slot], W.d_done, sizeof(unsigned), hipMemcpyDeviceToHost, st));
@@ -494,7 +512,8 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             if (W.cap_stream != nullptr &&
                 hipStreamBeginCapture(W.cap_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
                 hipError_t e = enqueue_head(W.cap_stream);
-                if (e == hipSuccess) e = enqueue_loop(W.cap_stream, 0, needed);
+                Coefs gc;
+                if (e == hipSuccess) e = enqueue_loop(W.cap_stream, 0, needed, gc);
                 const hipError_t e2 = hipStreamEndCapture(W.cap_stream, &g);
                 hipGraphExec_t ex = nullptr;
                 if (e == hipSuccess && e2 == hipSuccess && g != nullptr &&
@@ -507,7 +526,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
                         (void)hipGraphExecDestroy(lru->exec);
                         W.graphs.erase(lru);
                     }
-                    W.graphs.push_back(lx_batch_graph{key, ex, needed, W.calls});
+                    W.graphs.push_back(lx_batch_graph{key, ex, needed, gc.have, gc.rows, W.calls});
                 }
                 if (g != nullptr) (void)hipGraphDestroy(g);
                 (void)hipGetLastError();

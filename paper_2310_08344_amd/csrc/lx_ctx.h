@@ -20,6 +20,7 @@ struct lx_batch_graph {
     std::vector<long long> key;
     hipGraphExec_t exec = nullptr;
     int launches = 0;
+    int coef_have = 0, coef_rows = 0;   // coefficients it forms, and the rows of their tables
     unsigned long long last_use = 0;
 };
 
@@ -29,6 +30,7 @@ struct lx_batch_ws {
     void* d_ctl = nullptr;       // lx::LoopCtl[n]
     int* d_block_inst = nullptr; // instance of each workgroup
     double* d_coef = nullptr;    // n * ld Newton coefficients
+    double* d_coef_state = nullptr;  // their divided-difference tables' rows
     double* d_partials = nullptr;
     double* d_basis = nullptr;   // two basis vectors per instance
     unsigned* d_done = nullptr;  // instances that have finished
@@ -38,7 +40,7 @@ struct lx_batch_ws {
     unsigned* h_done = nullptr;  // [2] polled counters
     void* d_feat = nullptr;      // feature descriptors (lx_instance_features)
     void* h_feat = nullptr;
-    size_t cap_d_inst = 0, cap_d_ctl = 0, cap_d_blk = 0, cap_coef = 0, cap_partials = 0, cap_basis = 0,
+    size_t cap_d_inst = 0, cap_d_ctl = 0, cap_d_blk = 0, cap_coef = 0, cap_coef_state = 0, cap_partials = 0, cap_basis = 0,
            cap_done = 0, cap_h_inst = 0, cap_h_ctl = 0, cap_h_blk = 0, cap_h_done = 0, cap_feat = 0;
     std::vector<lx_batch_graph> graphs;    // at most kBatchGraphs, least recently used replaced
     hipStream_t cap_stream = nullptr;      // private stream the graphs are captured on
@@ -65,16 +67,19 @@ struct lx_ctx {
     size_t partials_len = 0;
     lx::LoopCtl* ctl = nullptr;
     double* coef = nullptr;                 // k_max * kMaxPoints
+    double* coef_state = nullptr;           // k_max divided-difference tables' rows (2 * ld each)
     double* xi = nullptr;                   // kMaxPoints
     int xi_uploaded = 0;
     // pinned host staging
     lx::LoopCtl* h_ctl = nullptr;           // initial loop control (pinned)
-    lx::SweepState* h_poll = nullptr;       // [2]: polled final-state slots (pinned)
+    // what running kernels write to the host (pinned)
+    lx::SweepState* h_poll = nullptr;       // a Leja loop's final state
+    int* h_progress = nullptr;              // the launches of a Leja loop that have started
+    lx::RhoRecord* h_rho = nullptr;         // a power iteration's result
     double* h_coef = nullptr;
     double* h_xi = nullptr;
     hipEvent_t poll_ev[2] = {nullptr, nullptr};
     std::vector<hipEvent_t> tev;            // timing events
-    lx::NewtonSeries series[LX_K_MAX];      // per-output divided differences
     // launch shapes: forced by lx_set_tile, else tuned per (kind, nx, ny, K, prec)
     lx::Tile forced{0, 0, 0, 0, 0};         // tx == 0: not forced
     int depth_forced = 0;                   // lx_set_depth: 0 automatic, 1 or 2 iterations per launch

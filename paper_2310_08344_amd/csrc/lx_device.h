@@ -40,8 +40,15 @@ struct LoopCtl {
     SweepState slot[3];
     double rtol, atol;
     double fp32_switch;      // < 0: never switch to FP32 sweeps
-    double rho;              // power iteration result
     int max_iters;
+    int pad;
+};
+
+// The result of a power iteration, in pinned host memory: the kernel that
+// ends it writes rho, then (after a system-scope fence) done.
+struct RhoRecord {
+    double rho;
+    int done;
     int pad;
 };
 
@@ -102,6 +109,7 @@ struct SweepArgs {
     double* partials;        // [2][nb][1+K]
     LoopCtl* ctl;
     SweepState* pub;         // host-visible copy of the final state (pinned host memory), or NULL
+    int* progress;           // pinned: launch L stores L + 1 as it starts working; or NULL
 };
 
 struct PowerArgs {
@@ -116,7 +124,7 @@ struct PowerArgs {
     const double* u;
     const double* add;             // rhs_sweep: the source S (else NULL)
     double* partials;              // [2][nb]
-    LoopCtl* ctl;
+    RhoRecord* rho;                // the final launch's result (pinned host memory)
 };
 
 // kOpDiffAdv3: diffusion with third-order upwind advection, a radius-2 cross
@@ -165,17 +173,17 @@ hipError_t launch_leja_pair(int op, int K, int th, const SweepArgs& a, int L, hi
 // needs a.u), the five-point diffusion-advection operator also at 6.
 hipError_t launch_leja_block(int op, int K, int th, int depth, const SweepArgs& a, int L, hipStream_t s);
 // Power iteration: norm of the start vector into partials[1], then sweeps
-// k = 0..iters-1, then the final norm into ctl->rho.
+// k = 0..iters-1, then the final norm into *rho.
 hipError_t launch_power_norm(const double* x, long n, int nb, double* partials, hipStream_t s);
 hipError_t launch_power_sweep(int op, const Tile& t, const PowerArgs& a, int k, hipStream_t s);
-hipError_t launch_power_final(int nb, const double* partials, LoopCtl* ctl, hipStream_t s);
+hipError_t launch_power_final(int nb, const double* partials, RhoRecord* rho, hipStream_t s);
 // Power iteration with kPowerBlockDepth sweeps per launch (block.hip; every
 // operator (Burgers needs a.u), nx even, 128-column tiles of
 // power_block_rows(op) rows with a.tiles_x/a.tiles_y in that layout): launch b makes nlev (1..depth)
 // levels from `in`; the start vector's norm partials at partials[nb + i]
 // (launch_power_norm), its own at partials[2 nb + (b & 1) nb depth + ...];
 // partials needs 2 nb (1 + depth) doubles.  Then the final ratio into
-// ctl->rho.
+// *a.rho.
 constexpr int kPowerBlockDepth = 4;
 // op: kOpDiffAdv (tiles of 128 x 16), kOpDiffAdv3 or kOpBurgersJ (128 x 8)
 int power_block_rows(int op);
@@ -248,8 +256,35 @@ hipError_t launch_batch_power_sweep(const BatchInst* insts, const int* block_ins
                                     int k, hipStream_t s);
 hipError_t launch_batch_power_final(BatchInst* insts, int n_inst, const double* partials, int k_last,
                                     double safety, hipStream_t s);
-hipError_t launch_batch_coeffs(const BatchInst* insts, int n_inst, const double* xi, double* coef, int ld,
-                               hipStream_t s);
+// Newton coefficients (coeffs.hip): the columns [j0, j1) of the divided-
+// difference tables, j1 <= rows <= kMaxCoefRows, rows points in all; coef[k ld
+// + j] = d_j for j0 <= j < j1.  j0 = 0 starts the tables; a later launch goes
+// on from the same `state` (2 ld doubles per series) with the same
+// rows.
+constexpr int kMaxCoefRows = 1024;
+struct CoefSeries {
+    double alpha, sigma, h, c, gamma;
+    int l;
+};
+struct CoefArgs {
+    CoefSeries s[kKMax];
+    int K;
+    // the loop's initial state, written to *ctl by the launch that is given one
+    double rtol, atol, fp32_switch;
+    int max_iters, out32;
+};
+hipError_t launch_coeffs(const CoefArgs& a, const double* xi, double* state, double* coef, int ld, int rows, int j0,
+                         int j1, LoopCtl* ctl, hipStream_t s);
+// The same for every instance of a batch (one output each).
+hipError_t launch_batch_coeffs(const BatchInst* insts, int n_inst, const double* xi, double* state, double* coef,
+                               int ld, int rows, int j0, int j1, hipStream_t s);
+// Rows a table is started with so that d_0 .. d_{upto-1} exist: 128, then
+// 256, then as many as there are (ld), so that the common loop does not carry
+// rows it never reads.
+constexpr int coef_rows(int upto, int ld) {
+    const int r = upto <= 128 ? 128 : (upto <= 256 ? 256 : kMaxCoefRows);
+    return r < ld ? r : ld;
+}
 // Batched two-iteration launch L (pair.hip; one output per instance, every
 // instance with nx even and 16-byte aligned vectors); th in {8, 16};
 // burgers: the batch holds a Burgers instance (sizes the LDS for its u tile).

@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(kBlockThreads) void power_stream_final(PowerArgs a,
             if (j == nlev - 2) prev = tot[j];
         }
         const bool safe = x2[0] >= 1e-200 && x2[0] <= 1e20;
-        a.ctl->rho = safe ? sqrt(last / prev) : __builtin_nan("");
+        publish_rho(a.rho, safe ? sqrt(last / prev) : __builtin_nan(""));
     }
 }
 

@@ -180,6 +180,20 @@ __device__ __forceinline__ void publish_final(LoopCtl* ctl, SweepState* pub, con
     }
 }
 
+// Launch L of a loop has started: every launch before it is complete.  The
+// host reads this to keep a few launches queued without an event between
+// them (an event's marker costs the stream 6 us).
+__device__ __forceinline__ void report_progress(int* progress, const int L) {
+    if (progress != nullptr) __hip_atomic_store(progress, L + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The end of a power iteration: its result, then the flag the host waits for.
+__device__ __forceinline__ void publish_rho(RhoRecord* r, const double rho) {
+    __hip_atomic_store(&r->rho, rho, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __hip_atomic_store(&r->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ bool loop_ended(const LoopCtl* ctl) {
     __shared__ int s_end;
     if (flat_tid() == 0) s_end = ctl->slot[2].done;
