@@ -344,9 +344,12 @@ typedef struct {
  * instances advance together, each with its own stop decision and budget
  * (Sec. 2.2), and finished instances cost nothing more.  Launch shape: the
  * one lx_tune_batched or lx_set_batch_shape chose for the batch's class,
- * else windows of four when every side allows them (8-row tiles with a
- * Burgers instance, 16 otherwise; 16384 points per workgroup), else two
- * iterations per launch, else one.  The device pipeline (power iteration,
+ * else register marching when every nx is even, every side at least 10 and
+ * every vector 16-byte aligned (windows of six; Burgers instances four, or
+ * six when the batch holds more than 2^23 points; lx_stats.depth is the
+ * Burgers depth when there are any), else windows of four on LDS tiles when
+ * every side allows them (8-row tiles with a Burgers instance, 16 otherwise;
+ * 16384 points per workgroup), else two iterations per launch, else one.  The device pipeline (power iteration,
  * coefficients, windows) of a layout is captured in a hipGraph after its
  * first call and replayed by later calls with the same layout (the same
  * instance count, sizes, shape and workspaces), with as many window
@@ -370,7 +373,8 @@ lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* inst, int p
  * itself (every instance's d_out is written) 1 + repeats times under each
  * candidate: windows of four, two and one iterations per launch x tile rows
  * 8, 16 (windows with a Burgers instance: 8) x 4096, 8192, 16384, 32768
- * points per workgroup; keeps the shape with the lowest median wall time
+ * points per workgroup, and the default rule (reported with 0 points per
+ * workgroup); keeps the shape with the lowest median wall time
  * for the batch's class (whether any instance is a Burgers Jacobian, and
  * the set of distinct grid sides) in the context, appended to the file
  * LX_TUNE_CACHE names when set.  report: host text, or NULL: one line per

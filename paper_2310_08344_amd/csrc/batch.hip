@@ -55,9 +55,10 @@ __global__ __launch_bounds__(kBlockThreads) void batch_fill_x0_kernel(BatchInst*
 
 __global__ __launch_bounds__(kBlockThreads) void batch_power_norm_kernel(const BatchInst* insts,
                                                                          const int* block_inst,
-                                                                         double* partials) {
+                                                                         double* partials, const int given_only) {
     const Who w = who(insts, block_inst);
     const BatchInst& I = insts[w.i];
+    if (given_only && I.kind == kOpDiffAdv && !I.has_x0) return;
     const double* __restrict__ x = gptr(I.has_x0 ? I.x0 : I.y[1]);
     const long n = static_cast<long>(I.nx) * I.ny;
     double acc = 0.0;
@@ -88,9 +89,11 @@ __device__ __forceinline__ void power_coeffs(const BatchInst& I, PowerArgs& a) {
 
 __global__ __launch_bounds__(kBlockThreads) void batch_power_sweep_kernel(const BatchInst* insts,
                                                                           const int* block_inst,
-                                                                          double* partials, const int k) {
+                                                                          double* partials, const int k,
+                                                                          const int burgers_only) {
     const Who w = who(insts, block_inst);
     const BatchInst& I = insts[w.i];
+    if (burgers_only && I.kind == kOpDiffAdv) return;
     double* __restrict__ P = partials + I.part_off;
     double tot[1];
     sum_partials<1>(P + static_cast<long>((k - 1) & 1) * I.nb, I.nb, tot);
@@ -134,8 +137,10 @@ __global__ __launch_bounds__(kBlockThreads) void batch_power_sweep_kernel(const 
 // gamma = -lambda/4 (Listing 7); one workgroup per instance
 __global__ __launch_bounds__(kBlockThreads) void batch_power_final_kernel(BatchInst* insts,
                                                                           const double* partials,
-                                                                          const int k_last, const double safety) {
+                                                                          const int k_last, const double safety,
+                                                                          const int burgers_only) {
     BatchInst& I = insts[blockIdx.x];
+    if (burgers_only && I.kind == kOpDiffAdv) return;
     double tot[1];
     sum_partials<1>(partials + I.part_off + static_cast<long>(k_last & 1) * I.nb, I.nb, tot);
     if (flat_tid() == 0) {
@@ -251,23 +256,23 @@ hipError_t launch_batch_fill_x0(BatchInst* insts, const int* block_inst, int nbl
 }
 
 hipError_t launch_batch_power_norm(const BatchInst* insts, const int* block_inst, int nblocks, double* partials,
-                                   hipStream_t s) {
+                                   bool given_only, hipStream_t s) {
     hipLaunchKernelGGL(batch_power_norm_kernel, dim3(nblocks), dim3(kBatchTx, kBatchTy), 0, s, insts, block_inst,
-                       partials);
+                       partials, given_only ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_power_sweep(const BatchInst* insts, const int* block_inst, int nblocks, double* partials,
-                                    int k, hipStream_t s) {
+                                    int k, bool burgers_only, hipStream_t s) {
     hipLaunchKernelGGL(batch_power_sweep_kernel, dim3(nblocks), dim3(kBatchTx, kBatchTy), 0, s, insts, block_inst,
-                       partials, k);
+                       partials, k, burgers_only ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_power_final(BatchInst* insts, int n_inst, const double* partials, int k_last,
-                                    double safety, hipStream_t s) {
+                                    double safety, bool burgers_only, hipStream_t s) {
     hipLaunchKernelGGL(batch_power_final_kernel, dim3(n_inst), dim3(kBlockThreads), 0, s, insts, partials, k_last,
-                       safety);
+                       safety, burgers_only ? 1 : 0);
     return hipGetLastError();
 }
 

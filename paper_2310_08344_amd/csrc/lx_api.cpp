@@ -281,6 +281,10 @@ void load_tune_cache(lx_ctx* ctx) {
             (b.depth == 1 || b.depth == 2 || b.depth == lx::kBatchBlockDepth) && (b.th == 8 || b.th == 16) &&
             b.ppw > 0 && b.ppw <= (1 << 22))
             ctx->batch.tuned[cls] = b;
+        else if (*q == ']' && cls.size() >= 3 && cls.size() % 2 == 1 &&
+                 std::sscanf(q, "], \"depth\": %d, \"th\": %d, \"ppw\": %d", &b.depth, &b.th, &b.ppw) == 3 &&
+                 b.depth == 0 && b.th == 0 && b.ppw == 0)
+            ctx->batch.tuned[cls] = lx::BatchShape{};   // the default rule was the fastest
     }
     std::fclose(f);
 }

@@ -15,7 +15,9 @@
 #include <cstdlib>
 #include <cstring>
 #include <iterator>
+#include <map>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "lx.h"
@@ -72,6 +74,77 @@ lx_status grow_pinned(lx_ctx* ctx, T** p, size_t* cap, size_t need) {
         return lx_internal_fail(ctx, LX_ENOMEM, "pinned batch staging of %zu bytes", need * sizeof(T));
     *cap = need;
     return LX_OK;
+}
+
+// Register marching: a batch whose vectors exceed the Infinity Cache runs the
+// Burgers windows at depth six (points of all instances).
+constexpr long kMarchDeepPoints = 1L << 23;
+
+// Strips, bands and workgroups of the register-marching launches of one grid
+// size: an item is a strip by a band, a workgroup marches four.
+struct MarchShape {
+    int nx, ny, depth;
+    int count;               // instances of this size
+    int strips, bands, nb;
+};
+
+int march_bands(int strips, int nb, int ny) { return std::max(1, std::min(4 * nb / strips, ny)); }
+
+int march_rows(const MarchShape& m) { return (m.ny + m.bands - 1) / m.bands; }
+
+// Of the workgroup counts that give bands of 2/3 hb to 3/2 hb rows (one band,
+// if no count does), the one whose wavefronts form the fewest rows in all:
+// every band forms 2 depth rows more than it outputs, and a workgroup's last
+// wavefronts may have no item.
+void march_shape(MarchShape& m, int hb) {
+    m.strips = lx::stream_strips(m.nx, m.depth);
+    const int nb0 = (m.strips + 3) / 4;
+    int nb_best = nb0;
+    long best = -1;
+    for (int nb = nb0; nb <= kMaxWorkgroupsPerInstance; ++nb) {
+        m.bands = march_bands(m.strips, nb, m.ny);
+        const int rows = march_rows(m);
+        if (2 * rows > 3 * hb) continue;
+        if (3 * rows < 2 * hb) break;
+        const long cost = static_cast<long>(nb) * (rows + 2 * m.depth);
+        if (best < 0 || cost < best) {
+            best = cost;
+            nb_best = nb;
+        }
+    }
+    m.nb = nb_best;
+    m.bands = march_bands(m.strips, m.nb, m.ny);
+}
+
+// The shapes of a batch's sizes.  A batch that fits one resident round of
+// workgroups (two per CU) takes as long as its tallest band; a larger one as
+// long as its rows spread over the round, and about half a tallest band more
+// while the last workgroups run out.  The band height with the least of that
+// is taken (rows formed per wavefront stand for time).  Measured, us per call:
+// 16 instances of 128^2, 372 with bands of 8 rows (one round), 655 of 48; 256
+// of 64^2 to 512^2, 1680 with 57 (two rounds), 1995 with 114 (one,
+// of uneven bands), 1850 with 32; 1024 of 256^2, 4650 with 64, 5490 with 128.
+void march_shapes(std::vector<MarchShape>& sizes) {
+    constexpr int kResident = 512;
+    std::vector<MarchShape> best;
+    double best_t = 0.0;
+    for (int hb : {8, 12, 16, 24, 32, 48, 64, 96}) {
+        long wgs = 0;
+        double work = 0.0, tallest = 0.0;
+        for (MarchShape& m : sizes) {
+            march_shape(m, hb);
+            const double rows = march_rows(m) + 2 * m.depth;
+            wgs += static_cast<long>(m.nb) * m.count;
+            work += rows * m.nb * m.count;
+            tallest = std::max(tallest, rows);
+        }
+        const double t = wgs <= kResident ? tallest : work / kResident + 0.5 * tallest;
+        if (best.empty() || t < best_t) {
+            best_t = t;
+            best = sizes;
+        }
+    }
+    sizes = best;
 }
 
 // The class of a batch for the tuned launch shapes: whether any instance
@@ -167,26 +240,56 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     const int want_depth = ctx->depth_forced != 0 ? ctx->depth_forced : ts.depth;
     bool pair = want_depth != 1;
     bool blk = want_depth != 1 && want_depth != 2;
-    bool any_burgers = false;
+    // register marching unless a depth, a tile shape, points per workgroup or
+    // LDS tiles are asked for
+    bool march = want_depth == 0 && ts.th == 0 && ts.ppw == 0 && ctx->pair_th == 0 && ctx->win_kind != 1;
+    bool any_burgers = false, any_diffadv = false;
+    long points = 0;
     for (int i = 0; i < n; ++i) {
         const lx_instance& q = inst[i];
         any_burgers = any_burgers || q.op.kind == LX_OP_BURGERS2D;
+        any_diffadv = any_diffadv || q.op.kind == LX_OP_DIFFADV2D;
+        const long N = static_cast<long>(q.op.nx) * q.op.ny;
+        points += N;
+        march = march && q.op.nx >= lx::kPowerStreamDepth && q.op.ny >= lx::kPowerStreamDepth && N <= (1L << 27);
         pair = pair && q.op.nx % 2 == 0 && aligned16(q.d_v) && aligned16(q.d_out) &&
                (q.d_u == nullptr || aligned16(q.d_u)) && (q.d_x0 == nullptr || aligned16(q.d_x0));
         blk = blk && q.op.nx >= BD && q.op.ny >= BD;
     }
     blk = blk && pair;
+    march = march && pair;
     if (blk) pair = false;
+    // Windows of six; the Burgers Jacobian's take four while the batch's
+    // vectors stay in the Infinity Cache (a 2048^2 grid: 10.7 us per iteration
+    // with four, 11.7 with six; 4096^2: 36.4 and 27.2)
+    const int da = march ? 6 : 0, db = march && any_burgers ? (points > kMarchDeepPoints ? 6 : 4) : 0;
+    const int depth_max = march ? std::max(da, db) : (blk ? BD : (pair ? 2 : 1));
+    const int depth_min = march ? (any_burgers ? db : da) : depth_max;
+    std::vector<MarchShape> shapes;
+    std::map<std::tuple<int, int, int>, size_t> shape_of;   // place in shapes by nx, ny, depth
+    auto shape_key = [&](const lx_operator& op) {
+        return std::make_tuple(op.nx, op.ny, op.kind == LX_OP_BURGERS2D ? db : da);
+    };
+    if (march) {
+        for (int i = 0; i < n; ++i) {
+            const auto key = shape_key(inst[i].op);
+            const auto at = shape_of.emplace(key, shapes.size());
+            if (at.second) shapes.push_back(MarchShape{std::get<0>(key), std::get<1>(key), std::get<2>(key), 0, 0, 0, 0});
+            ++shapes[at.first->second].count;
+        }
+        march_shapes(shapes);
+    }
     // tile rows: 16 (40 KB of LDS, 4 workgroups per CU) unless the Burgers
     // state needs room too, then 8 (36 KB)
     int th = (ctx->pair_th == 8 || ctx->pair_th == 16) ? ctx->pair_th
              : (ts.th == 8 || ts.th == 16)               ? ts.th
                                                           : (any_burgers ? 8 : 16);
-    if (blk && any_burgers) th = 8;   // the Burgers window layout takes 8-row tiles in a batch
+    if (blk && !march && any_burgers) th = 8;   // the Burgers window layout takes 8-row tiles in a batch
     const long ppw = ts.ppw > 0 ? ts.ppw : kPointsPerWorkgroup;
     std::vector<BatchInst> hi(static_cast<size_t>(n));
     std::vector<int> budget(static_cast<size_t>(n));
     int total_blocks = 0, max_budget = 1;
+    int power_per = lx::kPowerStreamDepth;   // sweeps per marching power launch
     long part_total = 0;
     size_t basis_total = 0;
     for (int i = 0; i < n; ++i) {
@@ -216,7 +319,17 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         b.vec = (al && b.nx % 2 == 0) ? 2 : 1;
         b.l = q.l;
         long tile_points;
-        if (pair || blk) {
+        if (march) {
+            const MarchShape& m = shapes[shape_of[shape_key(q.op)]];
+            b.tiles_x = m.strips;
+            b.tiles_y = m.bands;
+            b.nb = m.nb;
+            if (b.kind == lx::kOpDiffAdv) {
+                b.ptiles_x = lx::stream_strips(b.nx, lx::kPowerStreamDepth);
+                b.ptiles_y = march_bands(b.ptiles_x, b.nb, b.ny);
+            }
+            tile_points = 0;
+        } else if (pair || blk) {
             b.tiles_x = (b.nx + 127) / 128;
             b.tiles_y = (b.ny + th - 1) / th;
             tile_points = 128L * th;
@@ -225,15 +338,22 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             b.tiles_y = (b.ny + lx::kBatchTy - 1) / lx::kBatchTy;
             tile_points = static_cast<long>(lx::kBatchTx) * b.vec * lx::kBatchTy;
         }
-        b.ptiles_x = (b.nx + lx::kBatchTx * b.vec - 1) / (lx::kBatchTx * b.vec);
-        b.ptiles_y = (b.ny + lx::kBatchTy * lx::kBatchPowerRows - 1) / (lx::kBatchTy * lx::kBatchPowerRows);
-        const int T = b.tiles_x * b.tiles_y;
-        const int tpw = static_cast<int>(std::max(1L, ppw / tile_points));
-        b.nb = std::min(std::max((T + tpw - 1) / tpw, 1), kMaxWorkgroupsPerInstance);
+        if (!march || b.kind != lx::kOpDiffAdv) {
+            b.ptiles_x = (b.nx + lx::kBatchTx * b.vec - 1) / (lx::kBatchTx * b.vec);
+            b.ptiles_y = (b.ny + lx::kBatchTy * lx::kBatchPowerRows - 1) / (lx::kBatchTy * lx::kBatchPowerRows);
+        }
+        if (!march) {
+            const int T = b.tiles_x * b.tiles_y;
+            const int tpw = static_cast<int>(std::max(1L, ppw / tile_points));
+            b.nb = std::min(std::max((T + tpw - 1) / tpw, 1), kMaxWorkgroupsPerInstance);
+        }
         b.wg_begin = total_blocks;
         total_blocks += b.nb;
         b.part_off = part_total;
-        part_total += (blk ? 4L * BD : (pair ? 8L : 4L)) * b.nb;   // [2][nb][NV] partial sums
+        // [2][nb][NV] partial sums; marching also the power iteration's
+        const long nv = march ? std::max(4L * depth_max, 2L * (1 + lx::kPowerStreamDepth))
+                              : (blk ? 4L * BD : (pair ? 8L : 4L));
+        part_total += nv * b.nb;
         b.has_x0 = q.d_x0 != nullptr;
         b.dx = q.op.dx;
         b.dy = q.op.dy;
@@ -246,17 +366,24 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         b.gamma = q.gamma;
         const int sk = b.kind == lx::kOpDiffAdv ? 0 : 1;
         lx::stencil_coeffs(sk, b.dx, b.dy, b.D, b.vx, b.vy, b.nu, 0.0, 1.0, b.pw);
+        if (march && sk == 0) {
+            // the levels of an unnormalised power launch grow at most like the
+            // Gershgorin bound: their squares stay below 1e300 (x0 as in lx_spectrum)
+            const double g = std::fabs(b.pw[0]) + std::fabs(b.pw[1]) + std::fabs(b.pw[2]) + std::fabs(b.pw[3]) +
+                             std::fabs(b.pw[4]);
+            if (g > 10.0) power_per = std::max(1, std::min(power_per, static_cast<int>(140.0 / std::log10(g))));
+        }
         if (power_iters == 0) lx::stencil_coeffs(sk, b.dx, b.dy, b.D, b.vx, b.vy, b.nu, b.c, b.gamma, b.st);
         b.u = q.op.kind == LX_OP_BURGERS2D ? q.d_u : nullptr;
         b.v = q.d_v;
         b.out = q.d_out;
         b.x0 = q.d_x0;
-        basis_total += (blk ? 3 : 2) * static_cast<size_t>(b.nx) * b.ny;   // windows: a second output buffer
+        basis_total += (blk || march ? 3 : 2) * static_cast<size_t>(b.nx) * b.ny;   // windows: a second output buffer
         budget[static_cast<size_t>(i)] = q.budget > 0 ? q.budget : opt.max_iters;
         max_budget = std::max(max_budget, budget[static_cast<size_t>(i)]);
     }
     if (total_blocks > (1 << 30)) return lx_internal_fail(ctx, LX_EINVAL, "batch too large");
-    const int ld = max_budget + (blk ? BD + 1 : (pair ? 2 : 1));   // Newton coefficients per instance
+    const int ld = max_budget + (depth_max >= 3 ? depth_max + 1 : depth_max);   // Newton coefficients per instance
 
     // ---- workspaces ----
     lx_batch_ws& W = ctx->batch;
@@ -296,7 +423,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         b.y[1] = W.d_basis + boff + N;
         boff += 2 * N;
         b.out2 = nullptr;
-        if (blk) {
+        if (blk || march) {
             b.out2 = W.d_basis + boff;
             boff += N;
         }
@@ -325,19 +452,39 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         s = lx_internal_ensure_timing_events(ctx, 4);
         if (s != LX_OK) return s;
     }
-    const int last = blk ? (max_budget + BD - 1) / BD + 2 : (pair ? (max_budget + 1) / 2 + 1 : max_budget);
-    const int per = blk ? BD : (pair ? 2 : 1);
+    const int last = depth_max >= 3 ? (max_budget + depth_min - 1) / depth_min + 2
+                                    : (pair ? (max_budget + 1) / 2 + 1 : max_budget);
+    const int per = depth_max;
+    const bool windows = blk || march;
     // the device pipeline: spectral bounds (Listing 7), then the Newton
     // coefficients and the window (or one- or two-iteration) launches
     auto enqueue_head = [&](hipStream_t q) -> hipError_t {
         hipError_t e = hipSuccess;
         if (power_iters > 0) {
             e = lx::launch_batch_fill_x0(d_inst, W.d_block_inst, total_blocks, q);
-            if (e == hipSuccess) e = lx::launch_batch_power_norm(d_inst, W.d_block_inst, total_blocks, W.d_partials, q);
-            for (int k = 0; k < power_iters && e == hipSuccess; ++k)
-                e = lx::launch_batch_power_sweep(d_inst, W.d_block_inst, total_blocks, W.d_partials, k, q);
+            // one marching launch of one sweep needs the start vector's norm
+            const bool scale_own = power_iters == 1;
             if (e == hipSuccess)
-                e = lx::launch_batch_power_final(d_inst, n, W.d_partials, power_iters - 1, safety, q);
+                e = lx::launch_batch_power_norm(d_inst, W.d_block_inst, total_blocks, W.d_partials,
+                                                march && !scale_own, q);
+            if (march && any_diffadv) {
+                const int nblk = (power_iters + power_per - 1) / power_per;
+                int prev = power_per;
+                for (int b = 0; b < nblk && e == hipSuccess; ++b) {
+                    const int nlev = b == nblk - 1 ? power_iters - power_per * (nblk - 1) : power_per;
+                    e = lx::launch_batch_power_stream(d_inst, W.d_block_inst, total_blocks, W.d_partials, b, nlev, prev,
+                                                      scale_own, q);
+                    prev = nlev;
+                }
+                if (e == hipSuccess)
+                    e = lx::launch_batch_power_stream_final(d_inst, n, W.d_partials, nblk - 1, prev, safety, q);
+            }
+            if (!march || any_burgers) {
+                for (int k = 0; k < power_iters && e == hipSuccess; ++k)
+                    e = lx::launch_batch_power_sweep(d_inst, W.d_block_inst, total_blocks, W.d_partials, k, march, q);
+                if (e == hipSuccess)
+                    e = lx::launch_batch_power_final(d_inst, n, W.d_partials, power_iters - 1, safety, march, q);
+            }
         }
         return e;
     };
@@ -358,7 +505,10 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             cf.have = upto;
         }
         for (int L = first; L < first + count && e == hipSuccess; ++L) {
-            if (blk) {
+            if (march) {
+                e = lx::launch_batch_stream(d_inst, d_ctl, W.d_block_inst, total_blocks, da, db, W.d_partials, W.d_coef,
+                                            ld, ctx->xi, W.d_done, L, q);
+            } else if (blk) {
                 e = lx::launch_batch_block(d_inst, d_ctl, W.d_block_inst, total_blocks, any_burgers, th, W.d_partials,
                                            W.d_coef, ld, ctx->xi, W.d_done, L, q);
             } else if (pair) {
@@ -373,7 +523,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     };
     // what a captured pipeline bakes in: sizes, launch shape and addresses
     std::vector<long long> key{n, total_blocks, blk ? 1 : 0, pair ? 1 : 0, th, any_burgers ? 1 : 0, power_iters,
-                               ld, static_cast<long long>(ppw)};
+                               ld, static_cast<long long>(ppw), da, db, any_diffadv ? 1 : 0, power_per};
     {
         long long sb;
         std::memcpy(&sb, &safety, sizeof(sb));
@@ -462,7 +612,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         else if (r.status == LX_ENOTCONV && worst == LX_OK) worst = LX_ENOTCONV;
         const double N = static_cast<double>(b.nx) * b.ny;
         const double ub = b.kind == lx::kOpBurgersJ ? 8.0 : 0.0;
-        if (blk) {
+        if (windows) {
             // counted on the device by the launches that did work
             bytes += N * f.bytes_pp;
             max_iter = std::max(max_iter, f.n_levels);
@@ -479,10 +629,12 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             bytes += N * ((24.0 + ub) + (32.0 + ub) * std::max(f.iter - 1, 0));
             max_iter = std::max(max_iter, f.iter);
         }
-        bytes += N * (16.0 + ub) * power_iters;
+        const int sweeps = march && b.kind == lx::kOpDiffAdv ? (power_iters + power_per - 1) / power_per : power_iters;
+        bytes += N * (16.0 + ub) * sweeps;   // a marching launch reads and writes once for its sweeps
     }
     S.n_apply = max_iter;
-    S.depth = per;
+    S.depth = depth_min;
+    S.marching = march ? 1 : 0;
     S.bytes = bytes;
     if (timing) {
         S.plan_ms = lx_internal_elapsed(ctx->tev[0], ctx->tev[1]);
@@ -495,7 +647,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     // as many window launches as this call needed (every instance's working
     // launches and the one that publishes it); a replay that needed more
     // than it holds is captured again.
-    if (blk && W.use_graphs && !timing) {
+    if (windows && W.use_graphs && !timing) {
         int needed = 1;
         for (int i = 0; i < n; ++i) needed = std::max(needed, h_ctl[i].slot[2].n_work + 1);
         needed = std::min(needed, last + 1);
@@ -562,6 +714,8 @@ extern "C" lx_status lx_tune_batched(lx_ctx* ctx, int n, const lx_instance* inst
             for (int ppw : {4096, 8192, 16384, 32768}) cands.push_back(lx::BatchShape{depth, th, ppw});
         }
     }
+    // the default rule (register marching where every instance allows it)
+    if (even && min_side >= lx::kPowerStreamDepth) cands.push_back(lx::BatchShape{});
     const std::vector<int> cls = batch_class(n, inst);
     const int saved_depth = ctx->depth_forced, saved_th = ctx->pair_th;
     ctx->depth_forced = 0;
@@ -585,7 +739,10 @@ extern "C" lx_status lx_tune_batched(lx_ctx* ctx, int n, const lx_instance* inst
         std::sort(ms.begin(), ms.end());
         const double med = ms[ms.size() / 2];
         char line[96];
-        std::snprintf(line, sizeof(line), "%d %d %d %.4f\n", c.depth, c.th, c.ppw, med);
+        // the default rule: its depth, the tile rows it does not use, 0 points
+        const bool rule = c.depth == 0;
+        std::snprintf(line, sizeof(line), "%d %d %d %.4f\n", rule ? ctx->stats.depth : c.depth,
+                      rule ? (burgers ? 8 : 16) : c.th, c.ppw, med);
         rep += line;
         if (med < best_ms) {
             best_ms = med;

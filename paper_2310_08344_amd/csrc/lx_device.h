@@ -139,8 +139,9 @@ struct BatchInst {
     int nx, ny;
     int vec;                 // columns per lane (2 when nx is even and rows are 16-byte aligned)
     int l;                   // phi order
-    int tiles_x, tiles_y;    // tiles of the Leja kernel in use (one- or two-iteration layout)
-    int ptiles_x, ptiles_y;  // tiles of the power-iteration sweeps (kBatchTx * vec x kBatchTy * kBatchPowerRows)
+    int tiles_x, tiles_y;    // tiles of the Leja kernel in use, or strips and bands of register-marching windows
+    int ptiles_x, ptiles_y;  // tiles of the power-iteration sweeps (kBatchTx * vec x kBatchTy * kBatchPowerRows),
+                             // or strips and bands of the register-marching ones
     int wg_begin, nb;        // workgroups [wg_begin, wg_begin + nb) of each launch
     int has_x0;              // x0 given; else a splitmix64 vector in y[1]
     long part_off;           // offset of its partial sums: [2][nb][2]
@@ -250,12 +251,15 @@ hipError_t launch_combine(const double* x, const double* y, const double* z, dou
 
 // Batched launches: every workgroup serves the instance block_inst[b].
 hipError_t launch_batch_fill_x0(BatchInst* insts, const int* block_inst, int nblocks, hipStream_t s);
+// the norms of the start vectors (given_only: of the given ones of
+// diffusion-advection instances, and of every Burgers instance's)
 hipError_t launch_batch_power_norm(const BatchInst* insts, const int* block_inst, int nblocks, double* partials,
-                                   hipStream_t s);
+                                   bool given_only, hipStream_t s);
+// burgers_only: the other instances are left alone
 hipError_t launch_batch_power_sweep(const BatchInst* insts, const int* block_inst, int nblocks, double* partials,
-                                    int k, hipStream_t s);
+                                    int k, bool burgers_only, hipStream_t s);
 hipError_t launch_batch_power_final(BatchInst* insts, int n_inst, const double* partials, int k_last,
-                                    double safety, hipStream_t s);
+                                    double safety, bool burgers_only, hipStream_t s);
 // Newton coefficients (coeffs.hip): the columns [j0, j1) of the divided-
 // difference tables, j1 <= rows <= kMaxCoefRows, rows points in all; coef[k ld
 // + j] = d_j for j0 <= j < j1.  j0 = 0 starts the tables; a later launch goes
@@ -301,5 +305,23 @@ hipError_t launch_batch_block(const BatchInst* insts, LoopCtl* ctls, const int* 
 hipError_t launch_batch_sweep(const BatchInst* insts, LoopCtl* ctls, const int* block_inst, int nblocks,
                               double* partials, const double* coef, int ld, const double* xi, unsigned* done,
                               int m, hipStream_t s);
+// Batched windows by register marching (batch_stream.hip; every instance with
+// nx even, sides >= 10, 16-byte aligned vectors of at most 2^30 bytes, out2
+// set; tiles_x = stream_strips(nx, depth) strips by tiles_y bands): depth da
+// (6) for the diffusion-advection instances and db (4 or 6; 0 = there are
+// none) for the Burgers ones.
+hipError_t launch_batch_stream(const BatchInst* insts, LoopCtl* ctls, const int* block_inst, int nblocks, int da,
+                               int db, double* partials, const double* coef, int ld, const double* xi, unsigned* done,
+                               int L, hipStream_t s);
+// Power iteration of the diffusion-advection instances by register marching,
+// nlev <= kPowerStreamDepth sweeps in launch b (ptiles_x = stream_strips(nx,
+// kPowerStreamDepth) strips by ptiles_y bands; Burgers instances are left
+// alone).  Launch 0 scales a given start vector, or with scale_own every one,
+// by the norm launch_batch_power_norm recorded.  An instance's partial sums
+// need 2 nb (1 + kPowerStreamDepth) doubles.  Then the estimates.
+hipError_t launch_batch_power_stream(const BatchInst* insts, const int* block_inst, int nblocks, double* partials,
+                                     int b, int nlev, int prev, bool scale_own, hipStream_t s);
+hipError_t launch_batch_power_stream_final(BatchInst* insts, int n_inst, const double* partials, int b, int nlev,
+                                           double safety, hipStream_t s);
 
 }  // namespace lx

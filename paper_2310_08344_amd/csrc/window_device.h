@@ -234,8 +234,11 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
         w.pin[k] = gptr(end ? a.p2[k] : ((w.win & 1) ? a.p2[k] : a.p[k]));
         w.pout[k] = gptr(w.redo ? a.p[k] : ((w.win & 1) ? a.p[k] : a.p2[k]));
     }
-    w.yin = gptr((w.win == 0) ? a.v : static_cast<const double*>(a.ybuf[(w.win - 1) & 1]));
-    w.yout = gptr(static_cast<double*>(a.ybuf[w.win & 1]));
+    // selects, not a[win & 1]: indexing would keep a batch's arguments in memory
+    double* const y0 = static_cast<double*>(a.ybuf[0]);
+    double* const y1 = static_cast<double*>(a.ybuf[1]);
+    w.yin = gptr(w.win == 0 ? a.v : static_cast<const double*>((w.win & 1) ? y0 : y1));
+    w.yout = gptr((w.win & 1) ? y1 : y0);
     return true;
 }
 
