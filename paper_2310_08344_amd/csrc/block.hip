@@ -388,7 +388,6 @@ __device__ __forceinline__ void block_launch(const SweepArgs& a, const int L, co
 
 template <int OP, int K, int TH, int D>
 __global__ __launch_bounds__(kBlockThreads) void leja_block(SweepArgs a, const int L) {
-    if (loop_ended(gptr(a.ctl))) return;
     __shared__ BlockLds<OP, TH, D> S;
     block_launch<OP, K, TH, D>(a, L, static_cast<int>(blockIdx.x), true, S, nullptr);
 }
@@ -408,7 +407,6 @@ __global__ __launch_bounds__(kBlockThreads) void batch_block_kernel(const BatchI
     const int i = block_inst[blockIdx.x];
     const BatchInst& I = insts[i];
     LoopCtl* __restrict__ ctl = ctls + i;
-    if (loop_ended(ctl)) return;
     if (flat_tid() == 0) {
         a = SweepArgs{};
         a.nx = I.nx;

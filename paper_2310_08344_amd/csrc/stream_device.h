@@ -741,7 +741,6 @@ __device__ __forceinline__ void ring_windows(const SweepArgs& a, const WindowPla
 // to FP32 levels on the device, window_enter; both precisions in one kernel).
 template <int OP, int K, int D, bool F32, bool kLaunch0 = false>
 __device__ __forceinline__ void leja_stream_body(const SweepArgs& a, const int L, const int wg, unsigned* done) {
-    if (loop_ended(a.ctl)) return;
     WindowPlan<K> w;
     if (!window_enter<OP, K, D, true, F32>(a, L, wg, done, w)) return;
     double sy[D], sp[K][D];

@@ -121,33 +121,94 @@ __device__ __forceinline__ void stv_nt(T* __restrict__ p, const T (&o)[V]) {
     }
 }
 
-// Sums NV values over the workgroup in a fixed order (butterfly within each
-// 64-lane wavefront, then wavefronts in index order); every thread receives
-// the result.
+// a and b with the upper 32 lanes of a exchanged for the lower 32 of b
+// (kHalf), or the odd rows of 16 lanes of a for the even ones of b.
+template <bool kHalf>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+    unsigned al = static_cast<unsigned>(__double2loint(a)), ah = static_cast<unsigned>(__double2hiint(a));
+    unsigned bl = static_cast<unsigned>(__double2loint(b)), bh = static_cast<unsigned>(__double2hiint(b));
+    if constexpr (kHalf) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+        a = __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0]));
+        b = __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+        a = __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0]));
+        b = __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
+    }
+}
+
+constexpr int log2_up(const int n) { return n <= 1 ? 0 : 1 + log2_up((n + 1) / 2); }
+
+// Sums NV <= 64 values over the wavefront in a fixed order: every step halves
+// the values a lane holds, adding its half of them to what another lane held
+// of the same ones (NV - 1 additions instead of the 6 NV of one butterfly per
+// value).  Returns, in lane l, the sum of value l >> (6 - log2_up(NV))
+// (values past NV are 0).  Every lane must be active.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV]) {
-    __shared__ double red[NV][kBlockThreads / 64];
-    __shared__ double out[NV];
-    const int tid = flat_tid();
-    const int lane = tid & 63, wid = tid >> 6;
+__device__ __forceinline__ double wave_sums(const double (&v)[NV]) {
+    constexpr int p = log2_up(NV), P = 1 << p;
+    static_assert(NV <= 64, "one lane per value at most");
+    double t[P];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double x = v[q];
+    for (int q = 0; q < P; ++q) t[q] = q < NV ? v[q] : 0.0;
+    const int lane = flat_tid() & 63;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[q] = x;
+    for (int step = 0; step < 6; ++step) {
+        const int mask = 32 >> step;
+        if (step < p) {
+            const int half = P >> (step + 1);
+#pragma unroll
+            for (int q = 0; q < half; ++q) {
+                if (step == 0) {
+                    lane_swap<true>(t[q], t[q + half]);
+                    t[q] += t[q + half];
+                } else if (step == 1) {
+                    lane_swap<false>(t[q], t[q + half]);
+                    t[q] += t[q + half];
+                } else {
+                    const bool up = (lane & mask) != 0;
+                    const double keep = up ? t[q + half] : t[q], give = up ? t[q] : t[q + half];
+                    t[q] = keep + __shfl_xor(give, mask, 64);
+                }
+            }
+        } else {
+            t[0] += __shfl_xor(t[0], mask, 64);
+        }
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) red[q][wid] = v[q];
-    }
+    return t[0];
+}
+
+// Sums NV values over the workgroup of at most NW wavefronts in a fixed order
+// (wave_sums, then the wavefronts in index order); thread q < NV receives the
+// sum of value q, the others nothing of use.  Ends before the sums are read by
+// other threads: no barrier follows.
+template <int NV, int NW = kBlockThreads / 64>
+__device__ __forceinline__ double block_sums(const double (&v)[NV]) {
+    __shared__ double red[NW][NV];
+    constexpr int p = log2_up(NV);
+    const int tid = flat_tid(), lane = tid & 63, wid = tid >> 6;
+    const double s = wave_sums<NV>(v);
+    const int q = lane >> (6 - p);
+    if (q < NV && (lane & ((1 << (6 - p)) - 1)) == 0) red[wid][q] = s;
     __syncthreads();
+    double r = 0.0;
     if (tid < NV) {
         const int nw = (block_threads() + 63) >> 6;
-        double s = 0.0;
-        for (int w = 0; w < nw; ++w) s += red[tid][w];
-        out[tid] = s;
+        for (int w = 0; w < nw; ++w) r += red[w][tid];
     }
+    return r;
+}
+
+// The same, and every thread receives all the sums.
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV]) {
+    __shared__ double out[NV];
+    const int tid = flat_tid();
+    const double r = block_sums<NV>(v);
+    if (tid < NV) out[tid] = r;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NV; ++q) v[q] = out[q];
@@ -201,18 +262,53 @@ __device__ __forceinline__ bool loop_ended(const LoopCtl* ctl) {
     return s_end != 0;
 }
 
-// Adds the nb partial records of NV values written by the previous launch,
-// in workgroup-index order per lane and then block_sum's fixed tree: every
-// workgroup of the grid obtains bitwise the same totals.
+// Adds the nb partial records of NV values written by the previous launch:
+// consecutive lanes hold consecutive values, 64 / NV records at a time per
+// wavefront, each lane in record order, then the lanes of a value and the
+// wavefronts in index order, so every workgroup of the grid obtains bitwise
+// the same totals.  Thread q < NV receives total q.
+template <int NV, int NW = kBlockThreads / 64>
+__device__ __forceinline__ double record_totals(const double* __restrict__ P, const int nb) {
+    static_assert(NV <= 64, "a record per wavefront at least");
+    constexpr int G = 64 / NV;
+    __shared__ double red[NW][NV];
+    const int tid = flat_tid(), lane = tid & 63, wid = tid >> 6;
+    const int nw = (block_threads() + 63) >> 6;
+    double acc = 0.0;
+    if (lane < G * NV) {
+        const int step = nw * G * NV, end = nb * NV;
+        int o = wid * G * NV + lane;
+        // four loads in flight, added in order
+        for (; o + 3 * step < end; o += 4 * step) {
+            double x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = P[o + i * step];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc += x[i];
+        }
+        for (; o < end; o += step) acc += P[o];
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) s += __shfl(acc, (lane + g * NV) & 63, 64);
+    if (lane < NV) red[wid][lane] = s;
+    __syncthreads();
+    double r = 0.0;
+    if (tid < NV)
+        for (int w = 0; w < nw; ++w) r += red[w][tid];
+    return r;
+}
+
+// The same for every thread.
 template <int NV>
 __device__ __forceinline__ void sum_partials(const double* __restrict__ P, int nb, double (&tot)[NV]) {
+    __shared__ double out[NV];
+    const double r = record_totals<NV>(P, nb);
+    if (flat_tid() < NV) out[flat_tid()] = r;
+    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NV; ++q) tot[q] = 0.0;
-    for (int b = flat_tid(); b < nb; b += block_threads()) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) tot[q] += P[b * NV + q];
-    }
-    block_sum<NV>(tot);
+    for (int q = 0; q < NV; ++q) tot[q] = out[q];
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------

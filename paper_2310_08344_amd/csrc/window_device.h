@@ -32,9 +32,63 @@ __device__ __forceinline__ double lane_neighbour(const double v, const double ol
     return __hiloint2double(hi, lo);
 }
 
-// The state entering a launch from the state of the previous launch and its
-// partial sums tot[(j-1)(1+K) + q], q = 0: |y_{m+j}|^2, q = 1+k: |p_k|^2
-// after term m+j (j = 1..D).
+// What the stop rule says about a window, from its norms: the term at which
+// each output stops (D: it may go on, or stops there), with its last error
+// estimate and norm.
+template <int K>
+struct WindowVerdict {
+    bool nonfinite, any_stop, capped;
+    bool stop[K];
+    int j[K];
+    double err[K], pnorm[K], ynorm;
+};
+
+// Applies the stop rule at the terms m+1 .. m+D of a window, one lane per
+// norm: lane q holds norm q = (j-1)(1+K) + r of the window, r = 0: y_{m+j},
+// r = 1+k: output k after term m+j.  Taken in order, an output is tested at
+// j = 1, 2, .. until it stops (its estimate passes, or m + j reaches
+// max_iters); a non-finite norm or estimate at a tested term ends the loop.
+// Every lane of the wavefront must be active; all receive the verdict.
+template <int K, int D>
+__device__ __forceinline__ WindowVerdict<K> window_verdict(const LoopCtl& ctl, const int m, const int (&active)[K],
+                                                           const double norm, const double coef) {
+    constexpr int R = 1 + K;
+    const int lane = flat_tid() & 63, j = lane / R + 1;
+    const bool live = lane < D * R && lane % R != 0;
+    const double yn = __shfl(norm, (j - 1) * R & 63, 64);
+    const double e = fabs(coef) * yn;
+    const double thr = ctl.rtol * norm + ctl.atol;
+    const bool fin = isfinite(norm) && isfinite(e);
+    const bool pass = live && fin && e <= thr;
+    const bool cap = live && fin && !(e <= thr) && m + j >= ctl.max_iters;
+    const unsigned long long b_pass = __ballot(pass), b_cap = __ballot(cap), b_bad = __ballot(live && !fin);
+    WindowVerdict<K> v;
+    v.nonfinite = v.any_stop = v.capped = false;
+    int last = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        unsigned long long mine = 0;   // the lanes of output k
+#pragma unroll
+        for (int i = 0; i < D; ++i) mine |= 1ull << (i * R + 1 + k);
+        const unsigned long long ends = (b_pass | b_cap) & mine;
+        const int q = ends != 0 ? __ffsll(static_cast<long long>(ends)) - 1 : (D - 1) * R + 1 + k;
+        v.j[k] = q / R + 1;
+        v.stop[k] = active[k] && ends != 0;
+        v.err[k] = __shfl(e, q, 64);
+        v.pnorm[k] = __shfl(norm, q, 64);
+        if (active[k]) {
+            if ((b_bad & mine & ((2ull << q) - 1)) != 0) v.nonfinite = true;
+            if (ends != 0) v.any_stop = true;
+            if (((b_cap >> q) & 1) != 0) v.capped = true;
+            last = v.j[k] > last ? v.j[k] : last;
+        }
+    }
+    v.ynorm = __shfl(norm, last > 0 ? (last - 1) * R : 0, 64);
+    return v;
+}
+
+// The state entering a launch from the state of the previous launch and, if
+// that was a window, the verdict on it.
 //
 // kFp32 (FP32 sweeps): a window forms its levels and writes y_{m+D} in FP32
 // (out32) once, at the last term of the window before it, every output
@@ -42,8 +96,8 @@ __device__ __forceinline__ double lane_neighbour(const double v, const double ol
 // then on every window does.  in32: the window's y_m is stored in FP32.  A
 // re-execution keeps the precision of the window it repeats.
 template <int K, int D, bool kFp32 = false>
-__device__ __forceinline__ SweepState block_decide(const SweepArgs& a, const LoopCtl& ctl, const SweepState& prev,
-                                                   const double (&tot)[D * (1 + K)]) {
+__device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const SweepState& prev,
+                                                   const WindowVerdict<K>& v) {
     SweepState nx = prev;
     if (prev.blk_mode == 1) {
         // the window was re-executed with its stops: the outputs that took all
@@ -62,47 +116,28 @@ __device__ __forceinline__ SweepState block_decide(const SweepArgs& a, const Loo
         return nx;
     }
     const int m = prev.iter;
-    bool stopped = false, nonfinite = false, notconv = false;
-    int nt[K];
+    bool any_active = false;
 #pragma unroll
-    for (int k = 0; k < K; ++k) nt[k] = prev.active[k] ? D : 0;
-    for (int j = 1; j <= D; ++j) {
-        const double ynorm = sqrt(tot[(j - 1) * (1 + K)]) * a.inv_sqrtN;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (nt[k] != D) continue;   // inactive, or stopped earlier in this window
-            const double pn = sqrt(tot[(j - 1) * (1 + K) + 1 + k]) * a.inv_sqrtN;
-            const double e = fabs(gptr(a.coef)[k * a.ld + m + j]) * ynorm;
-            const double thr = ctl.rtol * pn + ctl.atol;
-            nx.err[k] = e;
-            nx.pnorm[k] = pn;
-            nx.ynorm = ynorm;
-            if (!isfinite(pn) || !isfinite(e)) {
-                nonfinite = true;
-            } else if (e <= thr) {
-                nt[k] = -j;   // stopped after term m+j (also when j = D)
-                nx.iters[k] = m + j;
-                stopped = true;
-            } else if (m + j >= ctl.max_iters) {
-                nt[k] = -j;
-                nx.iters[k] = m + j;
-                stopped = true;
-                notconv = true;
-            }
-        }
+    for (int k = 0; k < K; ++k) {
+        if (!prev.active[k]) continue;
+        any_active = true;
+        nx.err[k] = v.err[k];
+        nx.pnorm[k] = v.pnorm[k];
+        if (v.stop[k]) nx.iters[k] = m + v.j[k];
     }
-    if (nonfinite) {
+    if (any_active) nx.ynorm = v.ynorm;
+    if (v.nonfinite) {
         nx.status = 4;   // LX_ENONFINITE
         nx.done = 1;
         return nx;
     }
-    if (stopped) {
+    if (v.any_stop) {
         // re-execute the window with the stops: nt[k] = -j for an output
         // that stopped after term m+j, D for one that goes on, 0 otherwise
         nx.blk_mode = 1;
 #pragma unroll
-        for (int k = 0; k < K; ++k) nx.nt[k] = nt[k];
-        if (notconv) nx.status = 3;   // LX_ENOTCONV
+        for (int k = 0; k < K; ++k) nx.nt[k] = !prev.active[k] ? 0 : (v.stop[k] ? -v.j[k] : D);
+        if (v.capped) nx.status = 3;   // LX_ENOTCONV
     } else {
         nx.iter = m + D;
         nx.in32 = prev.out32;
@@ -110,7 +145,9 @@ __device__ __forceinline__ SweepState block_decide(const SweepArgs& a, const Loo
             bool small = true;
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                if (nt[k] == D && !(nx.err[k] <= ctl.fp32_switch * (ctl.rtol * nx.pnorm[k] + ctl.atol))) small = false;
+                if (prev.active[k] &&
+                    !(nx.err[k] <= ctl.fp32_switch * (ctl.rtol * nx.pnorm[k] + ctl.atol)))
+                    small = false;
             if (small) nx.out32 = 1;
         }
     }
@@ -135,10 +172,18 @@ struct WindowPlan {
 };
 
 // Entry of launch L of the window loop as workgroup `wg` of the a.nb that
-// serve this grid: the decision from the previous launch's partial sums.
-// Workgroup 0 records the state; when the loop has ended it publishes
-// slot[2] and, if `done` is given, counts the grid as finished.  Returns
-// false when this launch has nothing to do (the same in every thread).
+// serve this grid (at most NW wavefronts each): the decision from the previous
+// launch's partial sums.  Workgroup 0 records the state; when the loop has
+// ended it publishes slot[2] and, if `done` is given, counts the grid as
+// finished.  Returns false when this launch has nothing to do (the same in
+// every thread), also once the loop has ended.
+//
+// Every workgroup of every launch pays for this before its first level, so it
+// is a short chain: the end flag, the state, the partial sums and the
+// coefficients are loaded at once, the norms and their tests take a lane each.
+// Before, one thread tested term after term behind a butterfly per value: a
+// window of four on a 64^2 grid, all latency, went from 14.6 to 10.3 us, the
+// windows of eight of 4096^2 (three outputs) from 215 to 196.
 //
 // kEndCopy: in a re-execution, an output that stopped after the window's
 // last term (j = D) is not recomputed: the window's own result is exact.
@@ -149,7 +194,7 @@ struct WindowPlan {
 // y_{m+D} to ybuf[w & 1]; it reads the outputs from p (w even) or p2 (w odd)
 // and writes them to the other; a re-execution writes stopped outputs to p,
 // the caller's buffer, so every final result lands there.
-template <int OP, int K, int D, bool kEndCopy = false, bool kFp32 = false>
+template <int OP, int K, int D, bool kEndCopy = false, bool kFp32 = false, int NW = kBlockThreads / 64>
 __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, const int wg, unsigned* done,
                                              WindowPlan<K>& w) {
     LoopCtl* __restrict__ ctl = gptr(a.ctl);
@@ -176,37 +221,55 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
             if (wg == 0) ctl->slot[0] = st;
         }
     } else {
-        double tot[NV];
-        sum_partials<NV>(gptr(a.partials) + static_cast<long>((L - 1) & 1) * a.nb * NV, a.nb, tot);
-        if (tid == 0) {
-            SweepState st = block_decide<K, D, kFp32>(a, *ctl, ctl->slot[(L - 1) & 1], tot);
-            if (!st.done) {
-                // algorithmic bytes per point: y in (and out, unless a
-                // re-execution), and per output written p (in and out; the
-                // first window only writes it)
-                const bool rd = st.blk_mode == 1;
-                st.n_work += 1;
-                double b = 0.0;
-                int lev = rd ? 0 : D;
-                for (int k = 0; k < K; ++k) {
-                    const bool end = kEndCopy && rd && st.nt[k] == -D;   // exact already: copied or kept
-                    const bool w_k = rd ? (st.nt[k] < 0 && (!end || (st.iter / D) % 2 == 0)) : st.nt[k] != 0;
-                    if (w_k) b += st.iter == 0 && !end ? 8.0 : 16.0;
-                    if (rd && !end && -st.nt[k] > lev) lev = -st.nt[k];
+        // wavefront 0 decides; its lanes load what they need before the sums
+        const SweepState* __restrict__ ps = &ctl->slot[(L - 1) & 1];
+        const int lane = tid & 63;
+        int ended = 0, m = 0, active[K];
+        double cf = 0.0;
+        if (tid < 64) {
+            if (tid == 0) ended = __hip_atomic_load(&ctl->slot[2].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            m = ps->iter;
+#pragma unroll
+            for (int k = 0; k < K; ++k) active[k] = ps->active[k];
+            // (past the end of the loop m may lie beyond the last window)
+            const int r = lane % (1 + K), j = m + lane / (1 + K) + 1;
+            if (lane < NV && r > 0) cf = gptr(a.coef)[(r - 1) * a.ld + (j < a.ld ? j : a.ld - 1)];
+        }
+        const double tot = record_totals<NV, NW>(gptr(a.partials) + static_cast<long>((L - 1) & 1) * a.nb * NV, a.nb);
+        if (tid < 64) {
+            const double norm = lane < NV ? sqrt(tot) * a.inv_sqrtN : 0.0;
+            const WindowVerdict<K> v = window_verdict<K, D>(*ctl, m, active, norm, cf);
+            if (tid == 0) {
+                SweepState st = block_decide<K, D, kFp32>(*ctl, *ps, v);
+                if (ended) st.done = 1;
+                if (!st.done) {
+                    // algorithmic bytes per point: y in (and out, unless a
+                    // re-execution), and per output written p (in and out; the
+                    // first window only writes it)
+                    const bool rd = st.blk_mode == 1;
+                    st.n_work += 1;
+                    double b = 0.0;
+                    int lev = rd ? 0 : D;
+                    for (int k = 0; k < K; ++k) {
+                        const bool end = kEndCopy && rd && st.nt[k] == -D;   // exact already: copied or kept
+                        const bool w_k = rd ? (st.nt[k] < 0 && (!end || (st.iter / D) % 2 == 0)) : st.nt[k] != 0;
+                        if (w_k) b += st.iter == 0 && !end ? 8.0 : 16.0;
+                        if (rd && !end && -st.nt[k] > lev) lev = -st.nt[k];
+                    }
+                    // y in (and out), and u, when levels are formed
+                    const double yb = st.in32 ? 4.0 : 8.0, ob = st.out32 ? 4.0 : 8.0;
+                    if (!rd || lev > 0) b += yb + (rd ? 0.0 : ob) + (OP == kOpBurgersJ ? ob : 0.0);
+                    st.bytes_pp += b;
+                    st.n_levels += lev;
+                    if (!rd && st.out32) st.n_fp32 += D;
                 }
-                // y in (and out), and u, when levels are formed
-                const double yb = st.in32 ? 4.0 : 8.0, ob = st.out32 ? 4.0 : 8.0;
-                if (!rd || lev > 0) b += yb + (rd ? 0.0 : ob) + (OP == kOpBurgersJ ? ob : 0.0);
-                st.bytes_pp += b;
-                st.n_levels += lev;
-                if (!rd && st.out32) st.n_fp32 += D;
-            }
-            s_cur = st;
-            if (wg == 0) {
-                ctl->slot[L & 1] = st;
-                if (st.done) {
-                    publish_final(ctl, a.pub, st);   // this launch does no work
-                    if (done != nullptr) atomicAdd(done, 1u);
+                s_cur = st;
+                if (wg == 0 && !ended) {
+                    ctl->slot[L & 1] = st;
+                    if (st.done) {
+                        publish_final(ctl, a.pub, st);   // this launch does no work
+                        if (done != nullptr) atomicAdd(done, 1u);
+                    }
                 }
             }
         }
@@ -242,13 +305,10 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
     return true;
 }
 
-template <int K, int D>
-__device__ __forceinline__ void window_exit_sums(const SweepArgs& a, int L, int wg, double (&v)[D * (1 + K)]);
-
 // Exit of a window launch: the workgroup's sums of squares of every level
 // (sy[j-1]: y_{m+j}) and of every output after each term (sp[k][j-1]), in a
 // fixed order, into this workgroup's record of partials[L & 1].
-template <int K, int D>
+template <int K, int D, int NW = kBlockThreads / 64>
 __device__ __forceinline__ void window_exit(const SweepArgs& a, const int L, const int wg, const double (&sy)[D],
                                             const double (&sp)[K][D]) {
     constexpr int NV = D * (1 + K);
@@ -259,21 +319,9 @@ __device__ __forceinline__ void window_exit(const SweepArgs& a, const int L, con
 #pragma unroll
         for (int k = 0; k < K; ++k) v[j * (1 + K) + 1 + k] = sp[k][j];
     }
-    window_exit_sums<K, D>(a, L, wg, v);
-}
-
-// The same from the packed record v[(j-1)(1+K) + q] (q = 0: y_{m+j}, 1+k:
-// output k), this thread's share.
-template <int K, int D>
-__device__ __forceinline__ void window_exit_sums(const SweepArgs& a, const int L, const int wg,
-                                                 double (&v)[D * (1 + K)]) {
-    constexpr int NV = D * (1 + K);
-    block_sum<NV>(v);
-    if (flat_tid() == 0) {
-        double* __restrict__ Pp = gptr(a.partials) + static_cast<long>(L & 1) * a.nb * NV + static_cast<long>(wg) * NV;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) Pp[q] = v[q];
-    }
+    const double s = block_sums<NV, NW>(v);
+    if (flat_tid() < NV)
+        gptr(a.partials)[static_cast<long>(L & 1) * a.nb * NV + static_cast<long>(wg) * NV + flat_tid()] = s;
 }
 
 }  // namespace dev
