@@ -137,7 +137,8 @@ typedef struct {
     double step_err;        /* lx_exprb_step with LX_EXPRB32: embedded error  */
     int substeps;           /* substeps taken (lx_leja_opts.substeps)         */
     int marching;           /* 1: the windows (lx_spectrum: the power sweeps)
-                               ran by register marching, 0 otherwise         */
+                               ran by register marching, 0 otherwise (on
+                               register tiles too)                           */
     int batch_graph;        /* lx_phi_leja_batched: 1 when the call replayed a
                                captured pipeline (lx_set_batch_graphs)       */
 } lx_stats;
@@ -483,8 +484,9 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * `sweeps` timed iterations per candidate, after two warm-up launches, on
  * scratch vectors the call allocates and frees): the one-sweep shapes
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of
- * two iterations per launch and (diffusion-advection operators) of windows
- * of three, four and six (tile rows th, workgroups).  It keeps the fastest
+ * two iterations per launch, of windows of three to eight on LDS tiles and
+ * by register marching (tile rows th or bands, workgroups), and, for FP64
+ * with any nx, windows on register tiles.  It keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration
  * shape with its depth, and of the two the one with the lower time per
@@ -498,7 +500,8 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * candidate: "depth tx ty rows vec workgroups microseconds_per_iteration",
  * rows being ry for depth 1, th for LDS-tile depths 2..6 (whose workgroups
  * are 64 x 4) and the number of bands for register-marching windows, which
- * report depth as 100 + D.
+ * report depth as 100 + D; windows on register tiles report 100 + D with
+ * tx ty = 64 8 and the tile's rows.
  * Errors: LX_EINVAL (op invalid, K out of range, sweeps outside 1..200),
  * LX_ENOMEM. */
 lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* report, size_t report_len);
@@ -521,7 +524,12 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
  * buffer per output, allocated on first use).  Windows run either on LDS
  * tiles (th 8 or 16; larger th is taken as 16; depths 3, 4, 6) or by
  * register marching (lx_set_window_kernel; depths 4, 6, 8); depth 0
- * restores the automatic choice (the tuned entry, else 2).
+ * restores the automatic choice: the tuned entry, else, with no launch
+ * shape forced, windows on register tiles (FP64, any nx and alignment, sides
+ * beyond the halo of a window: 8 iterations for LX_OP_DIFFADV2D with K <= 3
+ * and LX_OP_BURGERS2D with K <= 2, 6 for LX_OP_DIFFADV2D_UP3 with K = 1) on
+ * small and odd grids and by register marching on larger ones, else 2.
+ * Automatic windows whose buffers cannot be allocated run as depth 2.
  * Depths 2..8 apply to grids with even nx and 16-byte aligned vectors; on
  * LDS tiles (FP64 sweeps) 3 and 4 to the diffusion-advection operators and
  * the Burgers Jacobian, 6 to LX_OP_DIFFADV2D (others fall back to 4, then
@@ -537,8 +545,10 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
 lx_status lx_set_depth(lx_ctx* ctx, int depth, int th, int nb);
 
 /* Which kernel later windows (depth >= 3) and power iterations run on:
- * kind 0 = automatic (windows as the tuned entry says, else LDS tiles;
- * power iteration by register marching where it applies), 1 = LDS tiles
+ * kind 0 = automatic (windows as lx_set_depth's automatic choice says, LDS
+ * tiles for a forced depth with no tuned entry; power iteration on register
+ * tiles for small grids and odd grids of the diffusion-advection operators,
+ * by register marching for larger ones where it applies), 1 = LDS tiles
  * for both (leja_block, power_block), 2 = register marching where it
  * applies (leja_stream: the five-point operators, FP64 or FP32 sweeps, at
  * the depths lx_set_depth lists; power_stream: LX_OP_DIFFADV2D; even nx,

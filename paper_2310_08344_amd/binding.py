@@ -288,7 +288,7 @@ class Context:
     def tune(self, op: Operator, K: int = 1, sweeps: int = 10) -> list:
         """Times the candidate launch shapes (lx_tune); returns
         [(depth, tx, ty, rows, vec, workgroups, microseconds per iteration), ...]
-        with rows = ry (depth 1) or tile rows th (depth 2)."""
+        with rows = ry (depth 1) or tile rows (more)."""
         buf = C.create_string_buffer(8192)
         self._check(self.lib.c.lx_tune(self._h, C.byref(op), int(K), int(sweeps), buf, C.c_size_t(8192)))
         rows = []

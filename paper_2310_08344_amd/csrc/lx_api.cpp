@@ -36,6 +36,12 @@ using lx::Tile;
 
 namespace {
 
+// Power iterations of at most this many points run on register tiles.  us for
+// 20 sweeps, register tiles / marching: 64^2 36 / 85, 1024^2 57 / 76, 1400^2 90 /
+// 76; register / LDS tiles, Burgers: 64^2 49 / 59, 1024^2 77 / 105, 2048^2 211 /
+// 255; third-order upwind: 1024^2 81 / 96, 2048^2 241 / 237.
+constexpr long kRtilePowerPoints = 5L << 18, kRtilePowerPointsTiles = 1L << 22;
+constexpr double kRtileRhoMin = 1e-8, kRtileRhoMax = 1e17;
 constexpr int kCoefStep = 16;   // least Newton coefficients formed by one launch
 
 lx_status fail(lx_ctx* ctx, lx_status s, const char* fmt, ...) {
@@ -257,7 +263,7 @@ void load_tune_cache(lx_ctx* ctx) {
                         &kind, &nx, &ny, &K, &prec, &t.tx, &t.ty, &t.ry, &t.vec, &t.nb, &t.depth, &t.th, &t.pnb,
                         &t.stream, &t.bands, &t.snb) == 16 &&
             valid_tile(t) && t.depth >= 1 && t.depth <= 8 && t.depth != 5 && t.depth != 7 &&
-            (t.th == 8 || t.th == 16 || t.th == 32) && t.pnb >= 0 && (t.stream == 0 || t.stream == 1) &&
+            (t.th == 8 || t.th == 16 || t.th == 32) && t.pnb >= 0 && t.stream >= 0 && t.stream <= 2 &&
             t.bands >= 0 && t.snb >= 0) {
             ctx->tuned[std::make_tuple(kind, nx, ny, K, prec)] = t;
             continue;
@@ -322,15 +328,78 @@ bool stream_ok(const lx_operator& op, int K, int depth) {
            lx::stream_has(opcode_of(op.kind), K, depth, op.prec == LX_FP32_SWEEP);
 }
 
+// Whether a call may run its windows (its power iteration) on register tiles:
+// FP64, sides beyond the halo of a window (a power launch).
+bool rtile_ok(const lx_operator& op, int depth) {
+    const int halo = depth * (op.kind == LX_OP_DIFFADV2D_UP3 ? 2 : 1);
+    return depth > 0 && op.prec == LX_FP64 && op.nx > halo && op.ny > halo;
+}
+
+// The automatic window kernel of a call (nothing forced, nothing tuned), by
+// what lx_tune measures (us per iteration, register tiles against the best of
+// marching and LDS tiles).  Register tiles win while a launch is short:
+//   five-point, one output   64^2 1.64 / 2.24, 1024^2 2.7 / 3.7, 1400^2 4.9 / 5.2,
+//   2048 x 1500 7.1 / 6.1;  three outputs 1024^2 3.9 / 5.2, 1400^2 7.3 / 7.4,
+//   2048 x 1500 10.8 / 8.3;
+//   Burgers, one output      512^2 2.0 / 3.2, 1400^2 6.3 / 7.9, 2048 x 1500 9.0 / 9.1,
+//   2048^2 12.8 / 10.0;
+//   third-order upwind       64^2 2.2 / 2.75, 1000^2 3.7 / 4.6, 4096^2 36.8 / 38.4
+//   (every size: it has no marching windows).
+// Beyond that marching in windows as deep as there are, except that the
+// Burgers Jacobian's windows of six need vectors beyond the Infinity Cache
+// (one output: 2048^2 11.4 against 10.0 with four, 4096^2 27.5 against 35.9),
+// where two outputs, which have no windows of six, run on register tiles
+// again (4096^2 40.6 / 52.3).  Every odd grid runs on register tiles (its only
+// windows; 1201 x 1100 3.2, one iteration per launch 17.8).
+// Fills t and returns true, or returns false where windows do not apply.
+bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
+    const long N = static_cast<long>(op.nx) * op.ny;
+    const bool even = vec2_ok && op.nx % 2 == 0;
+    const int rd = lx::rtile_depth(opcode_of(op.kind), K);
+    const bool burgers = op.kind == LX_OP_BURGERS2D;
+    constexpr long M = 1L << 20, kBeyondCache = 8 * M;
+    int sd = 0;   // the depth of marching windows, 0: none
+    for (int d : {8, 6, 4}) {
+        if (burgers && d == 6 && N <= kBeyondCache) continue;
+        if (sd == 0 && even && stream_ok(op, K, d)) sd = d;
+    }
+    const bool small = N <= (burgers ? 3 * M : 2 * M) || (burgers && K == 2 && N > kBeyondCache);
+    if (rtile_ok(op, rd) && (sd == 0 || small)) {
+        t.stream = 2;
+        t.depth = rd;
+        return true;
+    }
+    if (sd != 0) {
+        t.stream = 1;
+        t.depth = sd;
+        t.bands = t.snb = 0;
+        return true;
+    }
+    return false;
+}
+
 // Iterations per launch for this call: forced by lx_set_depth, else the
-// tuned entry's, else two.  Two or more need FP64 sweeps and 16-byte pairs;
+// tuned entry's, else auto_windows', else two.  Two or more need FP64 sweeps and 16-byte pairs;
 // windows of three or more need sides of depth x radius cells (else two),
 // and six the five-point diffusion-advection operator (else four).
-void choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok, Tile& t) {
+// windows_ok = false leaves the automatic choice at two (no memory for windows).
+// Returns true if windows were the automatic choice.
+bool choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok, Tile& t, bool windows_ok) {
     const bool pair_ok = op.prec == LX_FP64 && vec2_ok && op.nx % 2 == 0;
     // register-marching windows also take FP32 sweeps
     const bool march_ok = vec2_ok && op.nx % 2 == 0;
     auto it = ctx->tuned.find(std::make_tuple(op.kind, op.nx, op.ny, K, op.prec));
+    t.stream = 0;
+    if (ctx->depth_forced == 0 && ctx->win_kind == 0 && ctx->forced.tx == 0 && ctx->pair_th == 0 && ctx->pair_nb == 0) {
+        if (it == ctx->tuned.end()) {
+            if (windows_ok && auto_windows(op, K, vec2_ok, t)) return true;
+        } else if (const int rd = lx::rtile_depth(opcode_of(op.kind), K);
+                   it->second.stream == 2 && it->second.depth == rd && rtile_ok(op, rd)) {
+            t.stream = 2;
+            t.depth = it->second.depth;
+            return false;
+        }
+    }
     int depth = 2;
     if (ctx->depth_forced != 0) depth = ctx->depth_forced;
     else if (it != ctx->tuned.end()) depth = it->second.depth;
@@ -338,15 +407,14 @@ void choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok,
     // wrap allows only on sides of at least that many cells
     // windows by register marching: forced by lx_set_window_kernel, else the
     // tuned entry's choice; eight iterations only that way
-    const bool tuned_stream = it != ctx->tuned.end() && it->second.stream && it->second.depth == depth;
-    t.stream = 0;
+    const bool tuned_stream = it != ctx->tuned.end() && it->second.stream == 1 && it->second.depth == depth;
     if (march_ok && depth >= 3 && (ctx->win_kind == 2 || (ctx->win_kind == 0 && tuned_stream)) &&
         stream_ok(op, K, depth)) {
         t.stream = 1;
         t.depth = depth;
         t.bands = ctx->win_bands != 0 ? ctx->win_bands : (tuned_stream ? it->second.bands : 0);
         t.snb = ctx->win_nb != 0 ? ctx->win_nb : (tuned_stream ? it->second.snb : 0);
-        return;
+        return false;
     }
     if (depth == 8) depth = 6;
     const int halo = depth * (op.kind == LX_OP_DIFFADV2D_UP3 ? 2 : 1);
@@ -365,6 +433,7 @@ void choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok,
     // a radius-2 stencil stages 8 edge cells per row, and three or four
     // iterations per launch hold two levels in LDS: tiles of at most 16 rows
     if ((op.kind == LX_OP_DIFFADV2D_UP3 || t.depth >= 3) && t.th > 16) t.th = 16;
+    return false;
 }
 
 lx_status ensure_blk_ws(lx_ctx* ctx, int K) {
@@ -431,7 +500,13 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     bool vec2 = aligned16(q.v) && (q.u == nullptr || aligned16(q.u));
     for (int k = 0; k < K; ++k) vec2 = vec2 && aligned16(q.out[k]);
     Tile t = pick_tile(ctx, op, K, vec2);
-    choose_depth(ctx, op, K, vec2, t);
+    const bool rule = choose_depth(ctx, op, K, vec2, t, true);
+    if (rule && q.scratch == nullptr && ensure_blk_ws(ctx, K) != LX_OK) {
+        // no memory for a second buffer per output: two iterations per launch
+        (void)hipGetLastError();
+        (void)choose_depth(ctx, op, K, vec2, t, false);
+    }
+    const bool vec_rt = vec2 && nx % 2 == 0;   // register tiles load whole pairs
     const bool pair = t.depth == 2;
     const bool blk = t.depth >= 3;          // speculative windows of D iterations
     const int D = t.depth;
@@ -481,7 +556,14 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     SweepArgs a{};
     a.nx = nx;
     a.ny = ny;
-    if (t.stream) {
+    int rw = 0;   // rows per lane of register tiles
+    if (t.stream == 2) {
+        const lx::RtileGrid g = lx::rtile_grid(opcode_of(op.kind), D, nx, ny, vec_rt);
+        a.tiles_x = g.tiles_x;
+        a.tiles_y = g.tiles_y;
+        a.nb = g.nb;
+        rw = g.rw;
+    } else if (t.stream == 1) {
         const StreamGrid g = stream_grid(opcode_of(op.kind), fp32, nx, ny, K, D, t.bands, t.snb, false);
         a.tiles_x = g.strips;
         a.tiles_y = g.bands;
@@ -561,7 +643,8 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
             const int L = launched;
             s = ensure_coeffs(coeffs_for(L + 1));
             if (s != LX_OK) return s;
-            if (t.stream) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
+            if (t.stream == 2) LX_HIP(ctx, lx::launch_leja_rtile(opcode, K, rw, vec_rt, a, L, ctx->stream));
+            else if (t.stream == 1) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
             else if (blk) LX_HIP(ctx, lx::launch_leja_block(opcode, K, t.th, D, a, L, ctx->stream));
             else if (pair) LX_HIP(ctx, lx::launch_leja_pair(opcode, K, t.th, a, L, ctx->stream));
             else LX_HIP(ctx, lx::launch_leja_sweep(opcode, K, fp32, t, a, L, ctx->stream));
@@ -641,7 +724,7 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
         }
     }
     S.depth = per;
-    S.marching = t.stream ? 1 : 0;
+    S.marching = t.stream == 1 ? 1 : 0;
     S.bytes = bytes;
     S.plan_ms = plan_ms;
     if (timing && S.n_launch > 0) {
@@ -856,34 +939,61 @@ lx_status run_leja_sub(lx_ctx* ctx, const LejaCall& q) {
     return worst;
 }
 
-// Power iteration by register marching (power_stream): up to
-// kPowerStreamDepth sweeps per launch, normalised at launch boundaries.  The
-// unnormalised levels grow at most like the Gershgorin bound g of A (the
-// start of a launch has norm 1), so a launch makes at most 140 / log10(g)
-// levels: their squares stay below 1e280 (below 1e300 for a first launch
-// that takes x0 unscaled with ||x0||^2 <= 1e20).
-lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, int iters, double safety,
-                          double* rho_hat, double* c, double* gamma) {
-    constexpr int DP = lx::kPowerStreamDepth;
+// Power iteration by register marching (power_stream: up to
+// kPowerStreamDepth sweeps per launch) or on register tiles (power_rtile:
+// rtile_power_depth), normalised at launch boundaries.  The unnormalised
+// levels grow at most like the Gershgorin bound g of A (the start of a launch
+// has norm 1), so a launch makes at most 140 / log10(g) levels: their squares
+// stay below 1e280 (below 1e300 for a first launch that takes x0 unscaled
+// with ||x0||^2 <= 1e20).  The bound of a Burgers Jacobian is not known to the
+// host: for register tiles the caller looks at the result (kRtileRho).
+lx_status spectrum_deep(lx_ctx* ctx, const lx_operator& op, const double* u, const double* x0, int iters,
+                        double safety, bool tiles, bool vec, double* rho_hat, double* c, double* gamma) {
+    const int opcode = opcode_of(op.kind);
+    const int DP = tiles ? lx::rtile_power_depth(opcode) : lx::kPowerStreamDepth;
     const int nx = op.nx, ny = op.ny;
     const long N = static_cast<long>(nx) * ny;
-    double pk[9];
-    diffadv_stencil9(op, 0.0, 1.0, pk);
-    const double g = std::fabs(pk[0]) + std::fabs(pk[1]) + std::fabs(pk[2]) + std::fabs(pk[3]) + std::fabs(pk[4]);
-    const int cap = g > 10.0 ? static_cast<int>(140.0 / std::log10(g)) : DP;
-    const int per = std::max(1, std::min(DP, cap));
-    const StreamGrid sg = stream_grid(lx::kOpDiffAdv, false, nx, ny, 1, DP, 0, 0, true);
     PowerArgs a{};
     a.nx = nx;
     a.ny = ny;
-    a.tiles_x = sg.strips;
-    a.tiles_y = sg.bands;
-    a.nb = sg.nb;
-    a.cE = pk[0];
-    a.cW = pk[1];
-    a.cN = pk[2];
-    a.cS = pk[3];
-    a.cC = pk[4];
+    a.u = u;
+    double g = 0.0;
+    if (is_diffadv(op.kind)) {
+        double pk[9];
+        diffadv_stencil9(op, 0.0, 1.0, pk);
+        for (double v : pk) g += std::fabs(v);
+        a.cE = pk[0];
+        a.cW = pk[1];
+        a.cN = pk[2];
+        a.cS = pk[3];
+        a.cC = pk[4];
+        a.cE2 = pk[5];
+        a.cW2 = pk[6];
+        a.cN2 = pk[7];
+        a.cS2 = pk[8];
+    } else {
+        double pk[5];
+        lx::stencil_coeffs(1, op.dx, op.dy, op.D, op.vx, op.vy, op.nu, 0.0, 1.0, pk);
+        a.kx = pk[0];
+        a.ky = pk[1];
+        a.gx = pk[2];
+        a.gy = pk[3];
+    }
+    const int cap = g > 10.0 ? static_cast<int>(140.0 / std::log10(g)) : DP;
+    const int per = std::max(1, std::min(DP, cap));
+    int rw = 0;
+    if (tiles) {
+        const lx::RtileGrid rg = lx::rtile_grid(opcode, DP, nx, ny, vec);
+        a.tiles_x = rg.tiles_x;
+        a.tiles_y = rg.tiles_y;
+        a.nb = rg.nb;
+        rw = rg.rw;
+    } else {
+        const StreamGrid sg = stream_grid(lx::kOpDiffAdv, false, nx, ny, 1, DP, 0, 0, true);
+        a.tiles_x = sg.strips;
+        a.tiles_y = sg.bands;
+        a.nb = sg.nb;
+    }
     lx_status s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb) * (1 + DP));
     if (s != LX_OK) return s;
     a.partials = ctx->partials;
@@ -905,15 +1015,18 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
         for (int b = 0; b < nblk; ++b) {
             nlev = (b == nblk - 1) ? iters - per * (nblk - 1) : per;
             const double* in = (b == 0) ? x0 : ctx->ybuf[(b - 1) & 1];
-            LX_HIP(ctx, lx::launch_power_stream(a, in, ctx->ybuf[b & 1], b, nlev, prev, raw, ctx->stream));
+            double* out = ctx->ybuf[b & 1];
+            LX_HIP(ctx, tiles ? lx::launch_power_rtile(opcode, rw, vec, a, in, out, b, nlev, prev, raw, ctx->stream)
+                              : lx::launch_power_stream(a, in, out, b, nlev, prev, raw, ctx->stream));
             if (ctx->timing) LX_HIP(ctx, hipEventRecord(ctx->tev[b + 1], ctx->stream));
             prev = nlev;
         }
         ctx->h_rho->done = 0;
-        LX_HIP(ctx, lx::launch_power_stream_final(a, nblk - 1, nlev, raw, ctx->stream));
+        LX_HIP(ctx, tiles ? lx::launch_power_rtile_final(opcode, a, nblk - 1, nlev, raw, ctx->stream)
+                          : lx::launch_power_stream_final(a, nblk - 1, nlev, raw, ctx->stream));
         return wait_rho(ctx, &rho);
     };
-    const bool raw = per == DP && iters >= DP;
+    const bool raw = tiles || (per == DP && iters >= DP);
     s = run(raw);
     if (s != LX_OK) return s;
     if (raw && !std::isfinite(rho)) {
@@ -924,9 +1037,9 @@ lx_status spectrum_stream(lx_ctx* ctx, const lx_operator& op, const double* x0, 
     S.n_apply = iters;
     S.n_launch = nblk;
     S.depth = per;
-    S.marching = 1;
+    S.marching = tiles ? 0 : 1;
     S.rho_hat = rho;
-    S.bytes = 16.0 * static_cast<double>(N) * nblk;
+    S.bytes = (op.kind == LX_OP_BURGERS2D ? 24.0 : 16.0) * static_cast<double>(N) * nblk;   // + u per launch
     if (ctx->timing) {
         LX_HIP(ctx, hipEventSynchronize(ctx->tev[nblk]));
         S.loop_ms = elapsed(ctx->tev[0], ctx->tev[nblk]);
@@ -1100,12 +1213,31 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         x0 = ctx->ybuf[1];
     }
     const bool vec2 = aligned16(x0) && (d_u == nullptr || aligned16(d_u));
+    // register tiles where a launch is short (and for every odd grid of the
+    // diffusion-advection operators); an estimate outside kRtileRho, where a
+    // launch's unnormalised levels could lose range, is formed again below
+    const bool vec_rt = vec2 && nx % 2 == 0;
+    lx_operator op64 = *op;
+    op64.prec = LX_FP64;
+    if (ctx->win_kind == 0 && rtile_ok(op64, lx::rtile_power_depth(opcode_of(op->kind))) &&
+        (vec_rt ? N <= (op->kind == LX_OP_DIFFADV2D ? kRtilePowerPoints : kRtilePowerPointsTiles)
+                : is_diffadv(op->kind))) {
+        double rho = 0.0;
+        s = spectrum_deep(ctx, *op, d_u, x0, iters, safety, true, vec_rt, &rho, c, gamma);
+        if (s == LX_OK && rho >= kRtileRhoMin && rho <= kRtileRhoMax) {
+            if (rho_hat) *rho_hat = rho;
+            return LX_OK;
+        }
+        if (s != LX_OK && s != LX_ENONFINITE) return s;
+        ctx->stats = lx_stats{};
+        if (d_x0 == nullptr) LX_HIP(ctx, lx::launch_fill_splitmix(ctx->ybuf[1], N, 0ull, ctx->stream));
+    }
     // kPowerBlockDepth sweeps per launch on LDS tiles (the basis read and
     // written once per launch, the Burgers state once per launch); odd or
     // narrow grids and unaligned vectors one sweep per launch
     if (ctx->win_kind != 1 && op->kind == LX_OP_DIFFADV2D && vec2 && nx % 2 == 0 && nx >= lx::kPowerStreamDepth &&
         ny >= lx::kPowerStreamDepth && N * 8 <= (1L << 30))
-        return spectrum_stream(ctx, *op, x0, iters, safety, rho_hat, c, gamma);
+        return spectrum_deep(ctx, *op, d_u, x0, iters, safety, false, true, rho_hat, c, gamma);
     constexpr int PD = lx::kPowerBlockDepth;
     const int pcode = opcode_of(op->kind);
     const int ph = PD * (op->kind == LX_OP_DIFFADV2D_UP3 ? 2 : 1);   // halo of a power launch
@@ -1618,7 +1750,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
     if (sweeps < 1 || sweeps > 200) return fail(ctx, LX_EINVAL, "sweeps %d outside 1..200", sweeps);
     const int nx = op->nx, ny = op->ny;
     const size_t N = static_cast<size_t>(nx) * ny;
-    const int ld = sweeps + 16;   // windows read up to 2 depths past the timed sweeps
+    const int ld = sweeps + 32;   // windows read up to 3 depths past the timed sweeps
     s = ensure_xi(ctx, ld);
     if (s != LX_OK) return s;
     // scratch: K outputs (+ the Burgers state), all zero, so that values stay
@@ -1862,10 +1994,61 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
                 }
             }
         }
-        if (!(best_pair_us < best_us)) {
-            best.depth = 1;
-            best.stream = 0;
+    }
+    // windows on register tiles (any nx)
+    const int rd = lx::rtile_depth(opcode, K);
+    if (rtile_ok(*op, rd)) {
+        s = ensure_blk_ws(ctx, K);
+        if (s != LX_OK) return cleanup(s);
+        const lx::RtileGrid g = lx::rtile_grid(opcode, rd, nx, ny, nx % 2 == 0);
+        SweepArgs a{};
+        a.nx = nx;
+        a.ny = ny;
+        a.tiles_x = g.tiles_x;
+        a.tiles_y = g.tiles_y;
+        a.nb = g.nb;
+        a.ld = ld;
+        set_stencil(a, *op, -2.0, 1.0);
+        a.inv_sqrtN = 1.0 / std::sqrt(static_cast<double>(N));
+        a.v = ctx->ybuf[0];
+        a.ybuf[0] = ctx->ybuf[0];
+        a.ybuf[1] = ctx->ybuf[1];
+        a.u = op->kind == LX_OP_BURGERS2D ? scratch + static_cast<size_t>(K) * N : nullptr;
+        for (int k = 0; k < K; ++k) {
+            a.p[k] = scratch + static_cast<size_t>(k) * N;
+            a.p2[k] = ctx->blk_ws[k];
         }
+        a.coef = ctx->coef;
+        a.xi = ctx->xi;
+        s = ensure_partials(ctx, 2 * static_cast<size_t>(rd) * a.nb * (1 + K));
+        if (s != LX_OK) return cleanup(s);
+        a.partials = ctx->partials;
+        a.ctl = ctx->ctl;
+        if (hipMemcpyAsync(ctx->ctl, &init, sizeof(LoopCtl), hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
+            return cleanup(fail(ctx, LX_EDEVICE, "state upload failed"));
+        const int n = std::max(1, sweeps / rd);
+        const bool vec = nx % 2 == 0;
+        hipError_t e = hipSuccess;
+        for (int L = 0; L < 2 && e == hipSuccess; ++L) e = lx::launch_leja_rtile(opcode, K, g.rw, vec, a, L, ctx->stream);
+        if (e == hipSuccess) e = hipEventRecord(ctx->tev[0], ctx->stream);
+        for (int L = 2; L < n + 2 && e == hipSuccess; ++L)
+            e = lx::launch_leja_rtile(opcode, K, g.rw, vec, a, L, ctx->stream);
+        if (e == hipSuccess) e = hipEventRecord(ctx->tev[1], ctx->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(ctx->tev[1]);
+        if (e != hipSuccess) return cleanup(fail(ctx, LX_EDEVICE, "tuning launch failed: %s", hipGetErrorString(e)));
+        const double us = elapsed(ctx->tev[0], ctx->tev[1]) * 1e3 / (static_cast<double>(rd) * n);
+        char line[112];
+        std::snprintf(line, sizeof(line), "%d 64 8 %d 2 %d %.3f\n", 100 + rd, 8 * g.rw, a.nb, us);
+        rep += line;
+        if (us < best_pair_us) {
+            best_pair_us = us;
+            best.depth = rd;
+            best.stream = 2;
+        }
+    }
+    if (!(best_pair_us < best_us)) {
+        best.depth = 1;
+        best.stream = 0;
     }
     const double best_iter_us = std::min(best_us, best_pair_us);
     ctx->tuned[std::make_tuple(op->kind, nx, ny, K, op->prec)] = best;

@@ -60,7 +60,7 @@ struct Tile {
     int depth = 1;           // Leja iterations per launch: 1 (leja_sweep), 2 (leja_pair), 3+ (windows)
     int th = 16;             // tile rows of leja_pair and leja_block (their tiles are 128 columns wide)
     int pnb = 1024;          // workgroups of leja_pair and leja_block
-    int stream = 0;          // windows by register streaming (leja_stream) instead of LDS tiles
+    int stream = 0;          // windows on LDS tiles (0), by register streaming (1), on register tiles (2)
     int bands = 0;           // leja_stream: bands of rows (0: one resident round of wavefronts)
     int snb = 0;             // leja_stream: workgroups (0: as many as hold the items, up to one round)
     int cols() const { return tx * vec; }
@@ -226,6 +226,26 @@ constexpr int kPowerStreamDepth = 10;
 hipError_t launch_power_stream(const PowerArgs& a, const double* in, double* out, int b, int nlev, int prev,
                                bool raw0, hipStream_t s);
 hipError_t launch_power_stream_final(const PowerArgs& a, int b, int nlev, bool raw0, hipStream_t s);
+// Windows and power iteration on register tiles (rtile.hip), FP64: 128 columns
+// by 8 rw rows (rw 4 or 8) per workgroup of eight wavefronts, output tiles and
+// // their halo; any nx (vec: nx even and every vector 16-byte aligned), sides of
+// more than depth x radius cells.
+int rtile_depth(int op, int K);   // iterations per window launch of this kind; 0: there is none
+constexpr int rtile_power_depth(int op) { return op == 0 ? 8 : 4; }   // sweeps per power launch (kOpDiffAdv: 8)
+struct RtileGrid {
+    int tiles_x, tiles_y, nb, rw;
+};
+// tiles and workgroups of a grid: rows of 4 per lane while one round of
+// workgroups (256) holds the tiles, else 8
+RtileGrid rtile_grid(int op, int depth, int nx, int ny, bool vec);
+// a.tiles_x, a.tiles_y and a.nb as rtile_grid gave them; partials as
+// launch_leja_block
+hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, const SweepArgs& a, int L, hipStream_t s);
+// as launch_power_stream, with rtile_power_depth(op) in place of its depth
+// (raw0 allows any nlev)
+hipError_t launch_power_rtile(int op, int rw, bool vec, const PowerArgs& a, const double* in, double* out, int b,
+                              int nlev, int prev, bool raw0, hipStream_t s);
+hipError_t launch_power_rtile_final(int op, const PowerArgs& a, int b, int nlev, bool raw0, hipStream_t s);
 hipError_t launch_fill_splitmix(double* x, long n, unsigned long long seed, hipStream_t s);
 hipError_t launch_to_fp32(const double* x, float* y, long n, hipStream_t s);
 // kind 0: z = x (copy); kind 1: z = 1.5 x - 0.5 y.  n even.
