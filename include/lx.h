@@ -479,8 +479,9 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
 
 /* ---- launch shapes and measurement ------------------------------------ */
 
-/* Times every candidate launch shape of the Leja loop for this operator,
- * grid, output count K and precision on the context's stream (about
+/* Times every candidate launch shape (of at most 8192 workgroups) of the
+ * Leja loop for this operator, grid, output count K and precision on the
+ * context's stream (about
  * `sweeps` timed iterations per candidate, after two warm-up launches, on
  * scratch vectors the call allocates and frees): the one-sweep shapes
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of

@@ -42,6 +42,12 @@ namespace {
 // 255; third-order upwind: 1024^2 81 / 96, 2048^2 241 / 237.
 constexpr long kRtilePowerPoints = 5L << 18, kRtilePowerPointsTiles = 1L << 22;
 constexpr double kRtileRhoMin = 1e-8, kRtileRhoMax = 1e17;
+// Every workgroup adds the records of all workgroups of the launch before, so
+// the tuner leaves out shapes of one workgroup per tile with more workgroups
+// than this.  us per iteration, the fastest such shape / the fastest of the
+// others: 2049 x 2047 97 / 42, 4096^2 307 / 90, 8192^2 629 / 406; timing them was
+// half to four fifths of the tuner's time there (8192^2 1560 ms, now 460).
+constexpr int kTuneWorkgroups = 8192;
 constexpr int kCoefStep = 16;   // least Newton coefficients formed by one launch
 
 lx_status fail(lx_ctx* ctx, lx_status s, const char* fmt, ...) {
@@ -1803,6 +1809,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
             const int tiles = tiles_of(t, nx, ny);
             for (int nb : {0, 2048, 1024, 512}) {
                 if (nb != 0 && nb >= tiles) continue;   // same as one workgroup per tile
+                if (nb == 0 && tiles > kTuneWorkgroups) continue;
                 t.nb = nb;
                 cands.push_back(t);
             }
@@ -1877,6 +1884,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
                 const int tiles = tiles_x * ((ny + th - 1) / th);
                 for (int pnb : {0, 2048, 1536, 1024, 768, 512, 256}) {
                     if (pnb != 0 && pnb >= tiles) continue;
+                    if (pnb == 0 && tiles > kTuneWorkgroups) continue;
                     if (depth >= 3 && pnb > 1024) continue;
                     SweepArgs a{};
                     a.nx = nx;
