@@ -536,8 +536,9 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
  * the Burgers Jacobian, 6 to LX_OP_DIFFADV2D (others fall back to 4, then
  * 2), each with sides of at least depth times the stencil radius; register
  * marching to LX_OP_DIFFADV2D (FP64: depth 4 for K <= 4, 6 and 8 for
- * K <= 3) and LX_OP_BURGERS2D (depth 4 for K <= 2, 6 for K = 1), and to
- * FP32 sweeps of both for K <= 2 at depth 4 and K = 1 at 6 (windows switch
+ * K <= 3), LX_OP_BURGERS2D (depth 4 for K <= 2, 6 for K = 1) and
+ * LX_OP_DIFFADV2D_UP3 (depths 4 and 6 for K = 1), and to
+ * FP32 sweeps of the first two for K <= 2 at depth 4 and K = 1 at 6 (windows switch
  * to FP32 levels on the device); depth 8 otherwise falls back to 6; other
  * calls use depth 1 (FP32 sweeps: one per launch).
  * Results agree with depth 1 to rounding (the outputs take the same terms
@@ -551,15 +552,16 @@ lx_status lx_set_depth(lx_ctx* ctx, int depth, int th, int nb);
  * tiles for small grids and odd grids of the diffusion-advection operators,
  * by register marching for larger ones where it applies), 1 = LDS tiles
  * for both (leja_block, power_block), 2 = register marching where it
- * applies (leja_stream: the five-point operators, FP64 or FP32 sweeps, at
- * the depths lx_set_depth lists; power_stream: LX_OP_DIFFADV2D; even nx,
- * sides >= depth, 16-byte aligned vectors of at most 2^30 bytes).
+ * applies (leja_stream: the operators and precisions and the depths that
+ * lx_set_depth lists; power_stream: LX_OP_DIFFADV2D; even nx, sides of at
+ * least depth times the stencil radius, 16-byte aligned vectors of at most
+ * 2^30 bytes).
  * Register marching gives every wavefront a strip of 128 columns (its
- * output columns and depth columns on each side) and a band of rows, which
- * it walks from top to bottom forming all levels of the window in
- * registers; for LX_OP_DIFFADV2D at depths 4, 6 and 8 every level also passes
- * through a small ring in LDS, from which each output row takes its terms
- * depth rows later.  bands: bands of rows (0 = one resident round of wavefronts);
+ * output columns and depth times the radius columns on each side) and a
+ * band of rows, which it walks from top to bottom forming all levels of the
+ * window in registers; for the diffusion-advection operators every level also
+ * passes through a small ring in LDS, from which each output row takes its
+ * terms depth times the radius rows later.  bands: bands of rows (0 = one resident round of wavefronts);
  * nb: workgroups of four wavefronts (0 = automatic).  Results are the same
  * as with LDS tiles up to the order of the norm reductions.
  * Errors: LX_EINVAL (kind not 0..2, bands < 0, nb < 0). */

@@ -325,11 +325,11 @@ struct LejaCall {
 };
 
 // Whether a call may run its windows by register marching at this depth
-// (the five-point operators, FP64 or FP32 sweeps).
+// (the kernels there are: stream_has).
 bool stream_ok(const lx_operator& op, int K, int depth) {
-    if (op.kind != LX_OP_DIFFADV2D && op.kind != LX_OP_BURGERS2D) return false;
+    const int halo = depth * (op.kind == LX_OP_DIFFADV2D_UP3 ? 2 : 1);
     // vectors of at most 2^30 bytes (the kernel's buffer offsets)
-    return op.nx % 2 == 0 && op.nx >= depth && op.ny >= depth &&
+    return op.nx % 2 == 0 && op.nx >= halo && op.ny >= halo &&
            static_cast<long>(op.nx) * op.ny * 8 <= (1L << 30) &&
            lx::stream_has(opcode_of(op.kind), K, depth, op.prec == LX_FP32_SWEEP);
 }
@@ -349,8 +349,8 @@ bool rtile_ok(const lx_operator& op, int depth) {
 //   2048 x 1500 10.8 / 8.3;
 //   Burgers, one output      512^2 2.0 / 3.2, 1400^2 6.3 / 7.9, 2048 x 1500 9.0 / 9.1,
 //   2048^2 12.8 / 10.0;
-//   third-order upwind       64^2 2.2 / 2.75, 1000^2 3.7 / 4.6, 4096^2 36.8 / 38.4
-//   (every size: it has no marching windows).
+//   third-order upwind       64^2 2.2 / 2.75, 1000^2 3.7 / 4.6, 1400^2 6.8 / 7.4,
+//   1400 x 1800 9.5 / 8.3, 2048^2 11.4 / 9.8, 8192^2 133 / 79.
 // Beyond that marching in windows as deep as there are, except that the
 // Burgers Jacobian's windows of six need vectors beyond the Infinity Cache
 // (one output: 2048^2 11.4 against 10.0 with four, 4096^2 27.5 against 35.9),
@@ -461,7 +461,7 @@ int pair_grid(int pnb, int tiles) {
 }
 
 // Grid of a register-marching launch (leja_stream, power_stream): strips of
-// at most 128 - 2D output columns (stream_strips) by bands of rows, one item
+// at most 128 - 2DR output columns (stream_strips) by bands of rows, one item
 // per wavefront.  By default the bands make one resident round of wavefronts
 // (no partial second round), with bands of at least 4D rows so that the D
 // rows staged above and below a band stay a small share of it; workgroups
@@ -473,7 +473,7 @@ struct StreamGrid {
 
 StreamGrid stream_grid(int op, bool fp32, int nx, int ny, int K, int D, int bands, int nb, bool power) {
     StreamGrid g;
-    g.strips = lx::stream_strips(nx, D);
+    g.strips = lx::stream_strips(nx, D * (op == lx::kOpDiffAdv3 ? 2 : 1));
     const int resident = lx::stream_resident(op, K, D, fp32, power ? 1 : 0);
     const int waves = (resident > 0 ? resident : 512) * (lx::kBlockThreads / 64);
     int by = bands;

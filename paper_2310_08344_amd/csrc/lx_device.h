@@ -194,16 +194,16 @@ int power_block_resident(int op);
 hipError_t launch_power_block(int op, const PowerArgs& a, const double* in, double* out, int b, int nlev,
                               hipStream_t s);
 hipError_t launch_power_block_final(const PowerArgs& a, int b, int nlev, hipStream_t s);
-// Windows by register streaming (stream.hip; the five-point
-// diffusion-advection operator or the Burgers Jacobian (a.u, and a.u32 for
-// FP32 sweeps), nx even, sides >= depth, 16-byte aligned vectors); fp32:
+// Windows by register streaming (stream.hip; a diffusion-advection
+// operator or the Burgers Jacobian (a.u, and a.u32 for FP32 sweeps), nx even,
+// sides >= depth x radius, 16-byte aligned vectors); fp32:
 // FP32 sweeps (the device switches windows to FP32 levels, LoopCtl
-// fp32_switch); a.tiles_x = stream_strips(nx, depth) strips of at most
-// 128 - 2 depth output columns (edges on 128-byte lines where that costs at
+// fp32_switch); a.tiles_x = stream_strips(nx, depth x radius) strips of at most
+// 128 - 2 depth x radius output columns (edges on 128-byte lines where that costs at
 // most four of them) by a.tiles_y (1..ny) bands of rows, a.nb
 // workgroups of four wavefronts that each take items (strip, band) in turn;
 // partials as launch_leja_block.
-int stream_strips(int nx, int depth);
+int stream_strips(int nx, int halo);
 // whether leja_stream is built for this operator (kOp*), K outputs, depth
 // and precision mode
 bool stream_has(int op, int K, int depth, bool fp32);

@@ -1,6 +1,6 @@
 // Windows of D Leja iterations per launch by register streaming (gfx950),
-// for the five-point diffusion-advection operator and the Burgers Jacobian,
-// FP64 or FP32 levels; and power iteration with many sweeps per launch in
+// for the diffusion-advection operators and the Burgers Jacobian, FP64 or (not
+// the third-order upwind operator) FP32 levels; and power iteration with many sweeps per launch in
 // the same way.
 //
 // The window semantics are those of leja_block (window_device.h): every
@@ -23,12 +23,13 @@
 // tiles); along x the strip's side columns are formed by two wavefronts
 // (128 columns per at most 128 - 2D outputs).
 //
-// The outputs: for the diffusion-advection operator (ring windows, below)
+// The outputs: for the diffusion-advection operators (ring windows, below)
 // every level also goes into a small ring in LDS and the outputs of row
 // t - D take all their terms at step t; otherwise (the Burgers Jacobian) an
 // output row enters the registers when level 0 reaches it, takes term j
 // when level j does, and leaves after its last term, D + 1 rows of every
-// output in flight.  Rings of depth 7 or 8 (28 KB or 35 KB per wavefront)
+// output in flight.  Rings of depth 7 or 8 (28 KB or 35 KB per wavefront),
+// and of depth 6 with radius 2 (38 KB),
 // leave room in LDS for one wavefront per SIMD: those windows have a kernel
 // of their own, allowed the registers of a single wavefront.
 //
@@ -175,8 +176,9 @@ __global__ __launch_bounds__(kBlockThreads) void power_stream_final(PowerArgs a,
 
 // The register-marching window kernels there are: the five-point
 // diffusion-advection operator at depth 4 (K <= 4), 6 (K <= 3) and 8 (K <= 3)
-// in FP64, and the Burgers Jacobian at depth 4 (K <= 2) and 6 (K = 1); FP32
-// sweeps for K <= 2 at depths 4 and 6 (K = 1) of both operators.
+// in FP64, the Burgers Jacobian at depth 4 (K <= 2) and 6 (K = 1), and the
+// third-order upwind operator at depths 4 and 6 (K = 1); FP32 sweeps of the
+// first two for K <= 2 at depths 4 and 6 (K = 1).
 #define LX_STREAM_KERNELS(X)                                                                              \
     X(kOpDiffAdv, 1, 4, false) X(kOpDiffAdv, 2, 4, false) X(kOpDiffAdv, 3, 4, false)                      \
     X(kOpDiffAdv, 4, 4, false) X(kOpDiffAdv, 1, 6, false) X(kOpDiffAdv, 2, 6, false)                      \
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(kBlockThreads) void power_stream_final(PowerArgs a,
     X(kOpDiffAdv, 3, 8, false) X(kOpBurgersJ, 1, 4, false) X(kOpBurgersJ, 2, 4, false)                    \
     X(kOpBurgersJ, 1, 6, false) X(kOpDiffAdv, 1, 4, true) X(kOpDiffAdv, 2, 4, true)                       \
     X(kOpDiffAdv, 1, 6, true) X(kOpBurgersJ, 1, 4, true) X(kOpBurgersJ, 2, 4, true)                       \
-    X(kOpBurgersJ, 1, 6, true)
+    X(kOpBurgersJ, 1, 6, true) X(kOpDiffAdv3, 1, 4, false) X(kOpDiffAdv3, 1, 6, false)
 
 // the kernel of a (operator, K, depth, precision) combination, and its launch
 template <int OP, int K, int D, bool F32>
@@ -212,19 +214,20 @@ const void* stream_kernel(int op, int K, int depth, bool f32) {
 
 }  // namespace
 
-int stream_strips(int nx, int depth) {
-    const int unit = strip_unit(nx, depth);
-    const int out_units = (128 - 2 * depth) / unit;   // column units a strip outputs
+int stream_strips(int nx, int halo) {
+    const int unit = strip_unit(nx, halo);
+    const int out_units = (128 - 2 * halo) / unit;   // column units a strip outputs
     return ((nx / unit) + out_units - 1) / out_units;
 }
 
 bool stream_has(int op, int K, int depth, bool fp32) { return stream_kernel(op, K, depth, fp32) != nullptr; }
 
 hipError_t launch_leja_stream(int op, int K, int depth, bool fp32, const SweepArgs& a, int L, hipStream_t s) {
-    if (!stream_has(op, K, depth, fp32) || a.nb < 1 || a.nx % 2 != 0 || a.nx < depth || a.ny < depth)
+    const int halo = depth * (op == kOpDiffAdv3 ? 2 : 1);
+    if (!stream_has(op, K, depth, fp32) || a.nb < 1 || a.nx % 2 != 0 || a.nx < halo || a.ny < halo)
         return hipErrorInvalidValue;
     if (op == kOpBurgersJ && (a.u == nullptr || (fp32 && a.u32 == nullptr))) return hipErrorInvalidValue;
-    if (a.tiles_x != stream_strips(a.nx, depth) || a.tiles_y < 1 || a.tiles_y > a.ny) return hipErrorInvalidValue;
+    if (a.tiles_x != stream_strips(a.nx, halo) || a.tiles_y < 1 || a.tiles_y > a.ny) return hipErrorInvalidValue;
     if (static_cast<long>(a.nx) * a.ny * 8 > static_cast<long>(kFar)) return hipErrorInvalidValue;
 #define LX_STREAM_LAUNCH(O, KK, DD, F)                                                                         \
     if (op == (O) && K == (KK) && depth == (DD) && fp32 == (F)) {                                              \

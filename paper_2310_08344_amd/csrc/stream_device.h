@@ -26,12 +26,13 @@ struct StreamItem {
 };
 
 // Strip edges fall on 128-byte lines (16 FP64 columns) where that costs at
-// most four of a strip's 128 - 2 depth output columns, else on column pairs.
+// most four of a strip's 128 - 2 halo output columns, else on column pairs
+// (halo: the levels of a launch times the stencil's radius).
 // An output row segment that ends inside a line shares that line with the
 // neighbouring strip, and the nontemporal output loads then fetch it twice
 // (the shared line does not stay in L2 between the two wavefronts' loads).
-__host__ __device__ constexpr int strip_unit(const int nx, const int depth) {
-    return (nx % 16 == 0 && (128 - 2 * depth) % 16 <= 4) ? 16 : 2;
+__host__ __device__ constexpr int strip_unit(const int nx, const int halo) {
+    return (nx % 16 == 0 && (128 - 2 * halo) % 16 <= 4) ? 16 : 2;
 }
 
 __device__ __forceinline__ StreamItem stream_geom(const int i, const int nx, const int ny, const int sx,
@@ -120,6 +121,23 @@ __device__ __forceinline__ P2<T> stream_complete(const StenT<T>& st, const P2<T>
     P2<T> o;
     o.x = fma(st.c3, N.x, q.x);
     o.y = fma(st.c3, N.y, q.y);
+    return o;
+}
+
+// stream_partial for the third-order upwind operator (stencil_d3's operand
+// order, whose last term is row C + 2): rows S2 and S before C and N after it.
+template <typename T>
+__device__ __forceinline__ P2<T> stream_partial_r2(const StenT<T>& st, const T e0, const T e1, const T e2, const T cc,
+                                                   const P2<T> S2, const P2<T> S, const P2<T> C, const P2<T> N) {
+#pragma clang fp contract(off)
+    const T w = nbr<true>(C.y), w2 = nbr<true>(C.x);     // columns j - 1 and j - 2
+    const T e = nbr<false>(C.x), e2c = nbr<false>(C.y);  // columns j + 2 and j + 3
+    P2<T> o;
+    o.x = fma(st.c3, N.x, fma(st.c2, S.x, fma(st.c1, C.y, fma(st.c0, w, cc * C.x))));
+    o.y = fma(st.c3, N.y, fma(st.c2, S.y, fma(st.c1, e, fma(st.c0, C.x, cc * C.y))));
+    o.x = fma(e2, S2.x, fma(e1, e, fma(e0, w2, o.x)));
+    o.y = fma(e2, S2.y, fma(e1, e2c, fma(e0, w, o.y)));
+    asm volatile("" : "+v"(o.x), "+v"(o.y));   // as in stream_partial
     return o;
 }
 
@@ -378,13 +396,15 @@ __device__ __forceinline__ void stream_copy_item(const WindowPlan<K>& w, const S
 }
 
 // ---------------------------------------------------------------------------
-// Ring windows (the five-point diffusion-advection operator, D <= 6).
+// Ring windows (the diffusion-advection operators: radius 1, and the
+// third-order upwind one of radius 2).
 //
 // The same levels as stream_window_item, formed the same way, but the
-// outputs are completed D steps later: level j of row t - j, formed at step
-// t, also goes into a ring in LDS, and at step t the outputs of row t - D
-// take their terms 1 .. D in order from the rings (level D is the one just
-// formed).  An output row is then one row of registers for one step, not
+// outputs are completed D steps later (radius 1): level j of row t - j, formed
+// at step t, also goes into a ring in LDS, and at step t the outputs of row
+// t - D take their terms 1 .. D in order from the rings (level D is the one
+// just formed).  With radius R every lag is R rows per level: level j is
+// formed on row t - jR, and the outputs of row t - DR are completed.  An output row is then one row of registers for one step, not
 // D rows for D steps, so three outputs at depth six fit one wavefront, and
 // every row loaded for a later step sits in a register of its own that is
 // read once and then loaded again: nothing loaded is moved, so no step waits
@@ -395,18 +415,22 @@ __device__ __forceinline__ void stream_copy_item(const WindowPlan<K>& w, const S
 // memory operations issued after it.  Results, sums of squares and the
 // order of every operation are those of stream_window_item.
 //
-// Ring of level j (1 <= j < D): Ring<D>::size(j) >= D - j slots of one row
-// (64 lanes x a column pair), a power of two: row r in slot r mod size.  At
-// step t the slot of row t - D is read before row t - j is written (the
-// only rows alive are t - D .. t - j - 1).  The step loop is unrolled by a
+// Radius 2 (FP64, one output) at 8192^2: bound by memory, 79 us per iteration
+// in windows of six (4.6 TB/s), 109 in windows of four, where register tiles,
+// which form twice the cells, take 133; 4096^2 21.7 (37).
+//
+// Ring of level j (1 <= j < D): size(j) >= (D - j) R slots of one row (64 lanes
+// x a column pair), a power of two: row r in slot r mod size.  At step t the
+// slot of row t - DR is read before row t - jR is written (the only rows alive
+// are t - DR .. t - jR - 1).  The step loop is unrolled by a
 // multiple of every ring size, so every slot is a fixed LDS offset.
 // ---------------------------------------------------------------------------
 
-template <int D>
+template <int D, int RAD = 1>
 struct Ring {
     static constexpr int size(const int j) {
         int s = 1;
-        while (s < D - j) s *= 2;
+        while (s < (D - j) * RAD) s *= 2;
         return s;
     }
     static constexpr int base(const int j) {
@@ -422,11 +446,12 @@ struct Ring {
 };
 
 template <int OP, int D>
-constexpr bool kRingWindows = OP == kOpDiffAdv && D >= 3 && D <= 8;
+constexpr bool kRingWindows =
+    (OP == kOpDiffAdv && D >= 3 && D <= 8) || (OP == kOpDiffAdv3 && D >= 3 && D <= 6);
 
 // ring windows whose rings leave room for one wavefront per SIMD
 template <int OP, int D>
-constexpr bool kDeepRing = kRingWindows<OP, D> && D >= 7;
+constexpr bool kDeepRing = kRingWindows<OP, D> && D >= (OP == kOpDiffAdv3 ? 6 : 7);
 
 // Buffer resources (raw, byte offsets).  An offset at or past the size
 // reads zeros and writes nothing; kFar is past every buffer a ring window
@@ -499,20 +524,23 @@ struct RingWin {
 // levels formed, D in a window, fewer in a re-execution whose outputs take
 // no term past J (it writes no y); kShared: every output starts from the
 // rows of base[0] (a first window without copies: y_m), loaded once per
-// step.  ring: this wavefront's Ring<D>::slots rows, lane-major.
-template <int K, int D, typename T, bool kFirst, bool kIn32, int J = D, bool kShared = false>
+// step.  ring: this wavefront's Ring<D, radius<OP>()>::slots rows, lane-major.
+template <int OP, int K, int D, typename T, bool kFirst, bool kIn32, int J = D, bool kShared = false>
 __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const StreamItem it, const int lane,
                                                  P2<T>* __restrict__ ring, double (&sy)[D], double (&sp)[K][D]) {
-    using R = Ring<D>;
+    using R = Ring<D, radius<OP>()>;
     using Y0 = typename std::conditional<kIn32, float2, double2>::type;   // level 0 as stored
     constexpr int Y = R::ahead_y, P = R::ahead_p, U = R::unroll;
+    constexpr int RAD = radius<OP>(), H = D * RAD;
     const int nx = rw.nx, ny = rw.ny;
-    const int rc = 2 * lane - D;                 // strip column of this lane's pair
+    const int rc = 2 * lane - H;                 // strip column of this lane's pair
     const int gcol = wrap(it.xs + rc, nx);
     const bool ocol = rc >= 0 && rc < it.ws;
     const double mcol = ocol ? 1.0 : 0.0;
-    const int T_ = it.hb + 2 * D;
+    const int T_ = it.hb + 2 * H;
     const StenT<T> st = sten_as<T>(rw.st);
+    const T e0 = static_cast<T>(rw.st.e0), e1 = static_cast<T>(rw.st.e1), e2 = static_cast<T>(rw.st.e2),
+            e3 = static_cast<T>(rw.st.e3);
     T cc[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) cc[j] = static_cast<T>(rw.cc[j]);
@@ -524,20 +552,23 @@ __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const 
     const unsigned rowY = static_cast<unsigned>(nx) * sizeof(Y0) / 2;
     const unsigned allY = rowY * static_cast<unsigned>(ny);
 
-    P2<T> lc[D], lq[D];
+    // radius 2: lb, la are the rows before lc
+    P2<T> lc[D], lq[D], lb[RAD == 2 ? D : 1], la[RAD == 2 ? D : 1];
 #pragma unroll
     for (int j = 0; j < D; ++j) lc[j] = lq[j] = P2<T>{0, 0};
-    // level 0, rows t .. t + Y - 1 (staged row t is y_m's row yb - D + t)
+#pragma unroll
+    for (int j = 0; j < (RAD == 2 ? D : 1); ++j) la[j] = lb[j] = P2<T>{0, 0};
+    // level 0, rows t .. t + Y - 1 (staged row t is y_m's row yb - H + t)
     Y0 yq[Y];
-    unsigned yoff = static_cast<unsigned>(wrap(it.yb - D, ny)) * rowY;
+    unsigned yoff = static_cast<unsigned>(wrap(it.yb - H, ny)) * rowY;
 #pragma unroll
     for (int i = 0; i < Y; ++i) {
         yq[i] = buf_ld<Y0>(rw.yin, ycol, yoff);
         yoff += rowY;
         if (yoff >= allY) yoff -= allY;
     }
-    // the rows the outputs start from, rows t - D .. t - D + P - 1 (none
-    // before step 2D is an output row)
+    // the rows the outputs start from, rows t - H .. t - H + P - 1 (none
+    // before step 2H is an output row)
     constexpr int KB = kShared ? 1 : K;
     double2 bq[KB][P];
 #pragma unroll
@@ -552,9 +583,9 @@ __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const 
         yq[u % Y] = buf_ld<Y0>(rw.yin, ycol, yoff);
         yoff += rowY;
         if (yoff >= allY) yoff -= allY;
-        // output row t - D (band row t - 2D) starts from its loaded row;
-        // row t - D + P is loaded in its place
-        const int os = t - 2 * D, ol = os + P;
+        // output row t - H (band row t - 2H) starts from its loaded row;
+        // row t - H + P is loaded in its place
+        const int os = t - 2 * H, ol = os + P;
         const bool vs = os >= 0 && os < it.hb, vl = ol >= 0 && ol < it.hb;
         const unsigned so = vs ? static_cast<unsigned>(it.yb + os) * row8 : kFar;
         const unsigned lo = vl ? static_cast<unsigned>(it.yb + ol) * row8 : kFar;
@@ -576,16 +607,24 @@ __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const 
         const double mo = vs ? mcol : 0.0;
 #pragma unroll
         for (int j = 1; j <= J; ++j) {
-            // cur: level j-1 at row t-j+1; y: level j at row t-j
-            const P2<T> y = stream_complete<T>(st, lq[j - 1], cur);
-            lq[j - 1] = stream_partial<T>(st, cc[j - 1], lc[j - 1], cur);
+            // cur: level j-1 at row t-(j-1)R; y: level j at row t-jR
+            P2<T> y;
+            if constexpr (RAD == 2) {
+                y = P2<T>{fma(e3, cur.x, lq[j - 1].x), fma(e3, cur.y, lq[j - 1].y)};
+                lq[j - 1] = stream_partial_r2<T>(st, e0, e1, e2, cc[j - 1], la[j - 1], lb[j - 1], lc[j - 1], cur);
+                la[j - 1] = lb[j - 1];
+                lb[j - 1] = lc[j - 1];
+            } else {
+                y = stream_complete<T>(st, lq[j - 1], cur);
+                lq[j - 1] = stream_partial<T>(st, cc[j - 1], lc[j - 1], cur);
+            }
             lc[j - 1] = cur;
             cur = y;
-            // level j at row t - D
+            // level j at row t - H
             P2<T> yr = y;
             if (j < D) {
-                P2<T>* slot_r = ring + (R::base(j) + ((u - D) & (R::size(j) - 1))) * 64;
-                P2<T>* slot_w = ring + (R::base(j) + ((u - j) & (R::size(j) - 1))) * 64;
+                P2<T>* slot_r = ring + (R::base(j) + ((u - H) & (R::size(j) - 1))) * 64;
+                P2<T>* slot_w = ring + (R::base(j) + ((u - j * RAD) & (R::size(j) - 1))) * 64;
                 yr = slot_r[lane];
                 slot_w[lane] = y;
             }
@@ -598,7 +637,7 @@ __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const 
                 sp[k][j - 1] = fma(mo, p[k].x * p[k].x + p[k].y * p[k].y, sp[k][j - 1]);
             }
         }
-        // row t - D is complete: y_{m+D} and every output
+        // row t - H is complete: y_{m+D} and every output
         buf_st<P2<T>>(cur, rw.yout, ocolT + (vs ? static_cast<unsigned>(it.yb + os) * rowT : kFar));
 #pragma unroll
         for (int k = 0; k < K; ++k) buf_st<double2, kNontemporal>(p[k], rw.pout[k], ocol8 + so);
@@ -613,30 +652,30 @@ __device__ __forceinline__ void ring_window_item(const RingWin<K, D>& rw, const 
 }
 
 // This wavefront's items of a ring window launch.
-template <int K, int D, typename T, bool kFirst, bool kIn32, int J = D, bool kShared = false>
+template <int OP, int K, int D, typename T, bool kFirst, bool kIn32, int J = D, bool kShared = false>
 __device__ __forceinline__ void ring_items(const RingWin<K, D>& rw, const SweepArgs& a, const int wg, const int lane,
                                            double2* __restrict__ ring, double (&sy)[D], double (&sp)[K][D]) {
     const int items = a.tiles_x * a.tiles_y, G = a.nb * kStreamWaves;
     for (int i = stream_wave(wg, a.nb); i < items; i += G)
-        ring_window_item<K, D, T, kFirst, kIn32, J, kShared>(
-            rw, stream_geom(i, a.nx, a.ny, a.tiles_x, a.tiles_y, strip_unit(a.nx, D)), lane,
+        ring_window_item<OP, K, D, T, kFirst, kIn32, J, kShared>(
+            rw, stream_geom(i, a.nx, a.ny, a.tiles_x, a.tiles_y, strip_unit(a.nx, D * radius<OP>())), lane,
             reinterpret_cast<P2<T>*>(ring), sy, sp);
 }
 
 // A re-execution (FP64 levels, not the first window) forms only the levels
 // its outputs' terms need: J = jmax.
-template <int K, int D, int J>
+template <int OP, int K, int D, int J>
 __device__ __forceinline__ void ring_redo(const int jmax, const RingWin<K, D>& rw, const SweepArgs& a, const int wg,
                                           const int lane, double2* __restrict__ ring, double (&sy)[D],
                                           double (&sp)[K][D]) {
     if constexpr (J < D) {
         if (jmax == J) {
-            ring_items<K, D, double, false, false, J>(rw, a, wg, lane, ring, sy, sp);
+            ring_items<OP, K, D, double, false, false, J>(rw, a, wg, lane, ring, sy, sp);
             return;
         }
-        ring_redo<K, D, J + 1>(jmax, rw, a, wg, lane, ring, sy, sp);
+        ring_redo<OP, K, D, J + 1>(jmax, rw, a, wg, lane, ring, sy, sp);
     } else {
-        ring_items<K, D, double, false, false, D>(rw, a, wg, lane, ring, sy, sp);
+        ring_items<OP, K, D, double, false, false, D>(rw, a, wg, lane, ring, sy, sp);
     }
 }
 
@@ -644,13 +683,14 @@ __device__ __forceinline__ void ring_redo(const int jmax, const RingWin<K, D>& r
 // launch's buffers and coefficients set up once.
 // kLaunch0: launch 0, always the first window, neither re-executed nor
 // copying, whose outputs all start from y_m: only that form is compiled.
-template <int K, int D, bool F32, bool kLaunch0>
+template <int OP, int K, int D, bool F32, bool kLaunch0>
 __device__ __forceinline__ void ring_windows(const SweepArgs& a, const WindowPlan<K>& w, const int wg, const int lane,
                                              double2* __restrict__ ring_mem, double (&sy)[D], double (&sp)[K][D]) {
     RingWin<K, D> rw;
     rw.nx = a.nx;
     rw.ny = a.ny;
-    rw.st = Sten{a.aW, a.aE, a.aS, a.aN, a.aC, 0.0, 0.0, 0.0, 0.0};
+    if constexpr (OP == kOpDiffAdv3) rw.st = Sten{a.aW, a.aE, a.aS, a.aN, a.aC, a.aW2, a.aE2, a.aS2, a.aN2};
+    else rw.st = Sten{a.aW, a.aE, a.aS, a.aN, a.aC, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < D; ++j) rw.cc[j] = a.aC - a.xi[w.m + j];
     const unsigned n = static_cast<unsigned>(a.nx) * static_cast<unsigned>(a.ny);
@@ -671,18 +711,18 @@ __device__ __forceinline__ void ring_windows(const SweepArgs& a, const WindowPla
         for (int j = 1; j <= D; ++j) rw.dk[k][j] = j <= w.nt[k] ? a.coef[k * a.ld + w.m + j] : 0.0;
     }
     // this wavefront's rings, cleared once so that rows no output takes
-    // (before step 2D of the first item) hold finite values
+    // (before step 2H of the first item) hold finite values
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    double2* ring = ring_mem + wave * Ring<D>::slots * 64;
+    double2* ring = ring_mem + wave * Ring<D, radius<OP>()>::slots * 64;
 #pragma unroll
-    for (int i = 0; i < Ring<D>::slots; ++i) ring[i * 64 + lane] = double2{0.0, 0.0};
-    if (win32) {
-        if (first) ring_items<K, D, float, true, false>(rw, a, wg, lane, ring, sy, sp);
-        else if (in32) ring_items<K, D, float, false, true>(rw, a, wg, lane, ring, sy, sp);
-        else ring_items<K, D, float, false, false>(rw, a, wg, lane, ring, sy, sp);
+    for (int i = 0; i < Ring<D, radius<OP>()>::slots; ++i) ring[i * 64 + lane] = double2{0.0, 0.0};
+    if (F32 && win32) {
+        if (first) ring_items<OP, K, D, float, true, false>(rw, a, wg, lane, ring, sy, sp);
+        else if (in32) ring_items<OP, K, D, float, false, true>(rw, a, wg, lane, ring, sy, sp);
+        else ring_items<OP, K, D, float, false, false>(rw, a, wg, lane, ring, sy, sp);
     } else if (first) {
-        if constexpr (kLaunch0) ring_items<K, D, double, true, false, D, true>(rw, a, wg, lane, ring, sy, sp);
-        else ring_items<K, D, double, true, false>(rw, a, wg, lane, ring, sy, sp);
+        if constexpr (kLaunch0) ring_items<OP, K, D, double, true, false, D, true>(rw, a, wg, lane, ring, sy, sp);
+        else ring_items<OP, K, D, double, true, false>(rw, a, wg, lane, ring, sy, sp);
     } else if constexpr (!kLaunch0) {
         // a window in which one output still takes terms, or a re-execution
         // that recomputes one output and copies none, runs the one-output
@@ -700,7 +740,7 @@ __device__ __forceinline__ void ring_windows(const SweepArgs& a, const WindowPla
 #pragma unroll
         for (int k = 0; k < K; ++k) copies = copies || w.copy[k];
         if (w.redo && !(K > 1 && nact == 1 && !copies)) {
-            ring_redo<K, D, 1>(w.jmax, rw, a, wg, lane, ring, sy, sp);
+            ring_redo<OP, K, D, 1>(w.jmax, rw, a, wg, lane, ring, sy, sp);
         } else if (K > 1 && nact == 1) {
             RingWin<1, D> r1;
             r1.nx = rw.nx;
@@ -722,15 +762,15 @@ __device__ __forceinline__ void ring_windows(const SweepArgs& a, const WindowPla
             double s1[1][D];
 #pragma unroll
             for (int j = 0; j < D; ++j) s1[0][j] = 0.0;
-            if (w.redo) ring_redo<1, D, 1>(w.jmax, r1, a, wg, lane, ring, sy, s1);
-            else ring_items<1, D, double, false, false>(r1, a, wg, lane, ring, sy, s1);
+            if (w.redo) ring_redo<OP, 1, D, 1>(w.jmax, r1, a, wg, lane, ring, sy, s1);
+            else ring_items<OP, 1, D, double, false, false>(r1, a, wg, lane, ring, sy, s1);
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
                 for (int j = 0; j < D; ++j)
                     if (k == kact) sp[k][j] += s1[0][j];
         } else {
-            ring_items<K, D, double, false, false>(rw, a, wg, lane, ring, sy, sp);
+            ring_items<OP, K, D, double, false, false>(rw, a, wg, lane, ring, sy, sp);
         }
     }
 }
@@ -761,11 +801,11 @@ __device__ __forceinline__ void leja_stream_body(const SweepArgs& a, const int L
         for (int k = 0; k < K; ++k) any = any || w.copy[k];
         if (any)
             for (int i = stream_wave(wg, a.nb); i < items; i += G)
-                stream_copy_item<K>(w, stream_geom(i, a.nx, a.ny, a.tiles_x, a.tiles_y, strip_unit(a.nx, D)), lane,
-                                    a.nx);
+                stream_copy_item<K>(w, stream_geom(i, a.nx, a.ny, a.tiles_x, a.tiles_y,
+                                                   strip_unit(a.nx, D * radius<OP>())), lane, a.nx);
     } else if constexpr (kRingWindows<OP, D>) {
-        __shared__ double2 ring_mem[kStreamWaves * Ring<D>::slots * 64];
-        ring_windows<K, D, F32, kLaunch0>(a, w, wg, lane, ring_mem, sy, sp);
+        __shared__ double2 ring_mem[kStreamWaves * Ring<D, radius<OP>()>::slots * 64];
+        ring_windows<OP, K, D, F32, kLaunch0>(a, w, wg, lane, ring_mem, sy, sp);
     } else {
         // the window's coefficients
         double dk[K][D + 1], cc[D];
