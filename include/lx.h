@@ -486,8 +486,8 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * scratch vectors the call allocates and frees): the one-sweep shapes
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of
  * two iterations per launch, of windows of three to eight on LDS tiles and
- * by register marching (tile rows th or bands, workgroups), and, for FP64
- * with any nx, windows on register tiles.  It keeps the fastest
+ * by register marching (tile rows th or bands, workgroups), and, with any
+ * nx, windows on register tiles.  It keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration
  * shape with its depth, and of the two the one with the lower time per
@@ -526,9 +526,9 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
  * tiles (th 8 or 16; larger th is taken as 16; depths 3, 4, 6) or by
  * register marching (lx_set_window_kernel; depths 4, 6, 8); depth 0
  * restores the automatic choice: the tuned entry, else, with no launch
- * shape forced, windows on register tiles (FP64, any nx and alignment, sides
- * beyond the halo of a window: 8 iterations for LX_OP_DIFFADV2D with K <= 3
- * and LX_OP_BURGERS2D with K <= 2, 6 for LX_OP_DIFFADV2D_UP3 with K = 1) on
+ * shape forced, windows on register tiles (any nx and alignment, sides
+ * beyond the halo of a window, FP32 sweeps too: 8 iterations for LX_OP_DIFFADV2D with K <= 3
+ * and LX_OP_BURGERS2D with K <= 2, 6 for LX_OP_DIFFADV2D_UP3 with K = 1 in FP64) on
  * small and odd grids and by register marching on larger ones, else 2.
  * Automatic windows whose buffers cannot be allocated run as depth 2.
  * Depths 2..8 apply to grids with even nx and 16-byte aligned vectors; on

@@ -335,10 +335,12 @@ bool stream_ok(const lx_operator& op, int K, int depth) {
 }
 
 // Whether a call may run its windows (its power iteration) on register tiles:
-// FP64, sides beyond the halo of a window (a power launch).
+// sides beyond the halo of a window (a power launch); FP32 sweeps of the
+// radius-1 operators.
 bool rtile_ok(const lx_operator& op, int depth) {
-    const int halo = depth * (op.kind == LX_OP_DIFFADV2D_UP3 ? 2 : 1);
-    return depth > 0 && op.prec == LX_FP64 && op.nx > halo && op.ny > halo;
+    const bool up3 = op.kind == LX_OP_DIFFADV2D_UP3;
+    const int halo = depth * (up3 ? 2 : 1);
+    return depth > 0 && (op.prec == LX_FP64 || !up3) && op.nx > halo && op.ny > halo;
 }
 
 // The automatic window kernel of a call (nothing forced, nothing tuned), by
@@ -354,8 +356,11 @@ bool rtile_ok(const lx_operator& op, int depth) {
 // Beyond that marching in windows as deep as there are, except that the
 // Burgers Jacobian's windows of six need vectors beyond the Infinity Cache
 // (one output: 2048^2 11.4 against 10.0 with four, 4096^2 27.5 against 35.9),
-// where two outputs, which have no windows of six, run on register tiles
-// again (4096^2 40.6 / 52.3).  Every odd grid runs on register tiles (its only
+// where two outputs, which have no windows of six, and FP32 sweeps run on
+// register tiles again (4096^2 39.9 / 51.9; FP32, one output 26.6 / 28.5).  FP32
+// sweeps else as FP64 (Burgers 512^2 1.95 / 4.7, 1400^2 5.6 / 8.2; five-point
+// 1400^2 4.8 / 4.9, 2048^2 9.9 / 6.4; three outputs have no marching windows:
+// 4096^2 39, one iteration per launch 152).  Every odd grid runs on register tiles (its only
 // windows; 1201 x 1100 3.2, one iteration per launch 17.8).
 // Fills t and returns true, or returns false where windows do not apply.
 bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
@@ -369,7 +374,7 @@ bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
         if (burgers && d == 6 && N <= kBeyondCache) continue;
         if (sd == 0 && even && stream_ok(op, K, d)) sd = d;
     }
-    const bool small = N <= (burgers ? 3 * M : 2 * M) || (burgers && K == 2 && N > kBeyondCache);
+    const bool small = N <= (burgers ? 3 * M : 2 * M) || (burgers && (K == 2 || op.prec != LX_FP64) && N > kBeyondCache);
     if (rtile_ok(op, rd) && (sd == 0 || small)) {
         t.stream = 2;
         t.depth = rd;
@@ -649,7 +654,7 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
             const int L = launched;
             s = ensure_coeffs(coeffs_for(L + 1));
             if (s != LX_OK) return s;
-            if (t.stream == 2) LX_HIP(ctx, lx::launch_leja_rtile(opcode, K, rw, vec_rt, a, L, ctx->stream));
+            if (t.stream == 2) LX_HIP(ctx, lx::launch_leja_rtile(opcode, K, rw, vec_rt, fp32, a, L, ctx->stream));
             else if (t.stream == 1) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
             else if (blk) LX_HIP(ctx, lx::launch_leja_block(opcode, K, t.th, D, a, L, ctx->stream));
             else if (pair) LX_HIP(ctx, lx::launch_leja_pair(opcode, K, t.th, a, L, ctx->stream));
@@ -2022,6 +2027,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
         a.ybuf[0] = ctx->ybuf[0];
         a.ybuf[1] = ctx->ybuf[1];
         a.u = op->kind == LX_OP_BURGERS2D ? scratch + static_cast<size_t>(K) * N : nullptr;
+        a.u32 = ctx->u32;
         for (int k = 0; k < K; ++k) {
             a.p[k] = scratch + static_cast<size_t>(k) * N;
             a.p2[k] = ctx->blk_ws[k];
@@ -2037,10 +2043,10 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
         const int n = std::max(1, sweeps / rd);
         const bool vec = nx % 2 == 0;
         hipError_t e = hipSuccess;
-        for (int L = 0; L < 2 && e == hipSuccess; ++L) e = lx::launch_leja_rtile(opcode, K, g.rw, vec, a, L, ctx->stream);
+        for (int L = 0; L < 2 && e == hipSuccess; ++L) e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, ctx->stream);
         if (e == hipSuccess) e = hipEventRecord(ctx->tev[0], ctx->stream);
         for (int L = 2; L < n + 2 && e == hipSuccess; ++L)
-            e = lx::launch_leja_rtile(opcode, K, g.rw, vec, a, L, ctx->stream);
+            e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, ctx->stream);
         if (e == hipSuccess) e = hipEventRecord(ctx->tev[1], ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(ctx->tev[1]);
         if (e != hipSuccess) return cleanup(fail(ctx, LX_EDEVICE, "tuning launch failed: %s", hipGetErrorString(e)));

@@ -226,9 +226,9 @@ constexpr int kPowerStreamDepth = 10;
 hipError_t launch_power_stream(const PowerArgs& a, const double* in, double* out, int b, int nlev, int prev,
                                bool raw0, hipStream_t s);
 hipError_t launch_power_stream_final(const PowerArgs& a, int b, int nlev, bool raw0, hipStream_t s);
-// Windows and power iteration on register tiles (rtile.hip), FP64: 128 columns
-// by 8 rw rows (rw 4 or 8) per workgroup of eight wavefronts, output tiles and
-// // their halo; any nx (vec: nx even and every vector 16-byte aligned), sides of
+// Windows (FP64, or FP32 sweeps of the radius-1 operators) and power iteration
+// on register tiles (rtile.hip): 128 columns by 8 rw rows (rw 4 or 8) per
+// workgroup of eight wavefronts, output tiles and their halo; any nx (vec: nx even and every vector 16-byte aligned), sides of
 // more than depth x radius cells.
 int rtile_depth(int op, int K);   // iterations per window launch of this kind; 0: there is none
 constexpr int rtile_power_depth(int op) { return op == 0 ? 8 : 4; }   // sweeps per power launch (kOpDiffAdv: 8)
@@ -240,7 +240,7 @@ struct RtileGrid {
 RtileGrid rtile_grid(int op, int depth, int nx, int ny, bool vec);
 // a.tiles_x, a.tiles_y and a.nb as rtile_grid gave them; partials as
 // launch_leja_block
-hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, const SweepArgs& a, int L, hipStream_t s);
+hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, bool fp32, const SweepArgs& a, int L, hipStream_t s);
 // as launch_power_stream, with rtile_power_depth(op) in place of its depth
 // (raw0 allows any nlev)
 hipError_t launch_power_rtile(int op, int rw, bool vec, const PowerArgs& a, const double* in, double* out, int b,

@@ -23,7 +23,7 @@
 // what bounds larger grids: vector FP64 work and LDS row exchange.
 // us per iteration, against the fastest other kernel: 64 x 64 1.64 (2.24),
 // 1024 x 1024 with three outputs 3.9 (5.2), 2049 x 2047 11.4 (one iteration per
-// launch, 42), third-order upwind 4096 x 4096 36.8 (38.4).
+// launch, 42), FP32 sweeps of the Burgers Jacobian at 512 x 512 1.95 (4.7).
 #include <hip/hip_runtime.h>
 
 #include "lx_device.h"
@@ -103,41 +103,50 @@ struct RtLane {
     }
 };
 
-// A column pair of a row: one 16-byte access where pairs are whole and
-// aligned (kVec), else two of 8 bytes.
-template <bool kVec>
-__device__ __forceinline__ double2 rt_ld(const double* __restrict__ p, const long row, const int c0, const int c1) {
-    if constexpr (kVec) return *reinterpret_cast<const double2*>(p + row + c0);
-    else return double2{p[row + c0], p[row + c1]};
+// A column pair of a row: one access where pairs are whole and aligned (kVec),
+// else two.
+template <bool kVec, typename S>
+__device__ __forceinline__ P2<S> rt_ld(const S* __restrict__ p, const long row, const int c0, const int c1) {
+    if constexpr (kVec) return *reinterpret_cast<const P2<S>*>(p + row + c0);
+    else return P2<S>{p[row + c0], p[row + c1]};
 }
 
-template <bool kVec>
-__device__ __forceinline__ void rt_st(double* __restrict__ p, const long row, const int c0, const int c1, const bool o0,
-                                      const bool o1, const double2 v) {
+template <bool kVec, typename S>
+__device__ __forceinline__ void rt_st(S* __restrict__ p, const long row, const int c0, const int c1, const bool o0,
+                                      const bool o1, const P2<S> v) {
     if constexpr (kVec) {
-        if (o0) *reinterpret_cast<double2*>(p + row + c0) = v;
+        if (o0) *reinterpret_cast<P2<S>*>(p + row + c0) = v;
     } else {
         if (o0) p[row + c0] = v.x;
         if (o1) p[row + c1] = v.y;
     }
 }
 
+// Sten in the arithmetic of the levels.
+template <typename T>
+struct RtSten {
+    T c0, c1, c2, c3, e0, e1, e2, e3;
+    __device__ __forceinline__ explicit RtSten(const Sten& s)
+        : c0(static_cast<T>(s.c0)), c1(static_cast<T>(s.c1)), c2(static_cast<T>(s.c2)), c3(static_cast<T>(s.c3)),
+          e0(static_cast<T>(s.e0)), e1(static_cast<T>(s.e1)), e2(static_cast<T>(s.e2)), e3(static_cast<T>(s.e3)) {}
+};
+
 // The next level of a wavefront's rows, in place: y, with the R rows above
 // (up, nearest last) and below (dn, nearest first); for the Burgers Jacobian
 // u on the same rows and one above and below.
-template <int OP, int RW>
-__device__ __forceinline__ void rt_level(const Sten& st, const double cc, double2 (&y)[RW],
-                                         const double2 (&up)[OP == kOpDiffAdv3 ? 2 : 1],
-                                         const double2 (&dn)[OP == kOpDiffAdv3 ? 2 : 1],
-                                         const double2 (&u)[OP == kOpBurgersJ ? RW + 2 : 1]) {
+template <int OP, int RW, typename T>
+__device__ __forceinline__ void rt_level(const RtSten<T>& st, const T cc, P2<T> (&y)[RW],
+                                         const P2<T> (&up)[OP == kOpDiffAdv3 ? 2 : 1],
+                                         const P2<T> (&dn)[OP == kOpDiffAdv3 ? 2 : 1],
+                                         const P2<T> (&u)[OP == kOpBurgersJ ? RW + 2 : 1]) {
     if constexpr (OP == kOpDiffAdv3) {
-        double2 a2 = up[0], a1 = up[1];
+        P2<T> a2 = up[0], a1 = up[1];
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            const double2 C = y[r];
-            const double2 n1 = r + 1 < RW ? y[r + 1 < RW ? r + 1 : 0] : dn[0];
-            const double2 n2 = r + 2 < RW ? y[r + 2 < RW ? r + 2 : 0] : dn[r + 2 - RW < 0 ? 0 : r + 2 - RW];
-            const double wy = nbr<true>(C.y), wx = nbr<true>(C.x), ex = nbr<false>(C.x), ey = nbr<false>(C.y);
+            const P2<T> C = y[r];
+            const P2<T> n1 = r + 1 < RW ? y[r + 1 < RW ? r + 1 : 0] : dn[0];
+            const P2<T> n2 = r + 2 < RW ? y[r + 2 < RW ? r + 2 : 0] : dn[r + 2 - RW < 0 ? 0 : r + 2 - RW];
+            const T wy = nbr<true>(C.y), wx = nbr<true>(C.x), ex = nbr<false>(C.x), ey = nbr<false>(C.y);
             y[r].x = stencil_d3(st.c0, st.c1, st.c2, st.c3, cc, st.e0, st.e1, st.e2, st.e3, wy, C.y, a1.x, n1.x, C.x,
                                 wx, ex, a2.x, n2.x);
             y[r].y = stencil_d3(st.c0, st.c1, st.c2, st.c3, cc, st.e0, st.e1, st.e2, st.e3, C.x, ex, a1.y, n1.y, C.y,
@@ -146,18 +155,18 @@ __device__ __forceinline__ void rt_level(const Sten& st, const double cc, double
             a1 = C;
         }
     } else {
-        double2 above = up[0];
+        P2<T> above = up[0];
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            const double2 C = y[r];
-            const double2 N = r + 1 < RW ? y[r + 1 < RW ? r + 1 : 0] : dn[0];
-            const double w = nbr<true>(C.y), e = nbr<false>(C.x);
+            const P2<T> C = y[r];
+            const P2<T> N = r + 1 < RW ? y[r + 1 < RW ? r + 1 : 0] : dn[0];
+            const T w = nbr<true>(C.y), e = nbr<false>(C.x);
             if constexpr (OP == kOpDiffAdv) {
                 y[r].x = stencil_da(st.c0, st.c1, st.c2, st.c3, cc, w, C.y, above.x, N.x, C.x);
                 y[r].y = stencil_da(st.c0, st.c1, st.c2, st.c3, cc, C.x, e, above.y, N.y, C.y);
             } else {
-                const double2 uS = u[r], uC = u[r + 1], uN = u[r + 2];
-                const double uw = nbr<true>(uC.y), ue = nbr<false>(uC.x);
+                const P2<T> uS = u[r], uC = u[r + 1], uN = u[r + 2];
+                const T uw = nbr<true>(uC.y), ue = nbr<false>(uC.x);
                 y[r].x = stencil_bu(st.c0, st.c1, st.c2, st.c3, cc, w, C.y, above.x, N.x, C.x, uw, uC.y, uS.x, uN.x);
                 y[r].y = stencil_bu(st.c0, st.c1, st.c2, st.c3, cc, C.x, e, above.y, N.y, C.y, uC.x, ue, uS.y, uN.y);
             }
@@ -168,16 +177,16 @@ __device__ __forceinline__ void rt_level(const Sten& st, const double cc, double
 
 // A wavefront's first and last R rows of a level, for its neighbours in the
 // tile; two buffers, so one barrier per level is enough.
-template <int R>
+template <int R, typename T = double>
 struct RtExchange {
-    double2 row[2][kRtWaves][2 * R][64];
+    P2<T> row[2][kRtWaves][2 * R][64];
 };
 
 // Writes this wavefront's edge rows, waits, and reads the neighbours' (the
 // tile's first and last wavefront read their own: such rows are invalid).
-template <int R, int RW>
-__device__ __forceinline__ void rt_exchange(RtExchange<R>& ex, const int buf, const double2 (&y)[RW], double2 (&up)[R],
-                                            double2 (&dn)[R]) {
+template <int R, int RW, typename T>
+__device__ __forceinline__ void rt_exchange(RtExchange<R, T>& ex, const int buf, const P2<T> (&y)[RW], P2<T> (&up)[R],
+                                            P2<T> (&dn)[R]) {
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
 #pragma unroll
@@ -201,8 +210,142 @@ __device__ __forceinline__ Sten sweep_sten(const SweepArgs& a) {
     else return Sten{a.kx, a.ky, a.gx, a.gy, a.kC, 0.0, 0.0, 0.0, 0.0};
 }
 
+// The tiles of this workgroup in a window launch, the levels in T (FP32 levels
+// of FP32 sweeps: the basis and the stencil arithmetic; outputs, terms and sums
+// stay FP64).  s_d[k][j] = d_{m+j} of output k (0 past its last term), s_cc[j-1]
+// the centre of level j.
+template <int OP, int K, int D, int RW, bool kVec, typename T>
+__device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K>& w, const Sten& sten, const int wg,
+                                          const double (&s_d)[K][D + 1], const double (&s_cc)[D],
+                                          RtExchange<radius<OP>(), T>& ex, double (&sy)[D], double (&sp)[K][D]) {
+    constexpr int R = radius<OP>(), H = D * R;
+    const RtSten<T> st(sten);
+    const int nx = a.nx, ny = a.ny, unit = kVec ? 2 : 1;
+    const bool store_y = !w.redo, first = w.win == 0;
+    const RtSpan span = rt_span(wg, a.nb, a.tiles_x * a.tiles_y);
+    int buf = 0;
+    for (int t = span.first; t < span.end; t += span.step) {
+        const RtGeom g = rt_geom(t, nx, ny, a.tiles_x, a.tiles_y, unit);
+        const RtLane<H, RW> ln(g, nx);
+        const bool outs = ln.any_out();
+        P2<T> y[RW], u[OP == kOpBurgersJ ? RW + 2 : 1];
+        double2 p[K][RW];
+        // where the levels are FP32, the p_0 = d_0 y_0 of a first window are formed
+        // here, from y_0 as stored; else once the first barrier has passed
+        constexpr bool kF = sizeof(T) == sizeof(float);
+        if constexpr (kF) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int r = 0; r < RW; ++r) p[k][r] = double2{0.0, 0.0};
+        }
+        if (w.jmax > 0) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const long row = ln.row(r, nx, ny);
+                if constexpr (kF) {
+                    if (w.in32) {
+                        y[r] = rt_ld<kVec>(reinterpret_cast<const float*>(w.yin), row, ln.c0, ln.c1);
+                    } else {
+                        const double2 v = rt_ld<kVec>(w.yin, row, ln.c0, ln.c1);
+                        y[r] = as_t2<float>(v);
+                        if (first) {
+#pragma unroll
+                            for (int k = 0; k < K; ++k) {
+                                const double d0 = a.coef[k * a.ld + w.m];
+                                p[k][r].x = d0 * v.x;
+                                p[k][r].y = d0 * v.y;
+                            }
+                        }
+                    }
+                } else {
+                    y[r] = rt_ld<kVec>(w.yin, row, ln.c0, ln.c1);
+                }
+            }
+            if constexpr (OP == kOpBurgersJ) {
+                const T* __restrict__ us;
+                if constexpr (kF) us = a.u32;
+                else us = a.u;
+#pragma unroll
+                for (int r = 0; r < RW + 2; ++r) u[r] = rt_ld<kVec>(us, ln.row(r - 1, nx, ny), ln.c0, ln.c1);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            // the first window starts from p_0 = d_0 y_0 (also when it is
+            // re-executed); a copy reads the window's own result
+            const bool rd = outs && (w.nt[k] > 0 || w.copy[k]) && !(first && !w.copy[k]);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                if (!kF || w.copy[k]) p[k][r] = double2{0.0, 0.0};
+                if (rd && ln.out_row(r) && (ln.o0 || ln.o1)) p[k][r] = rt_ld<kVec>(w.pin[k], ln.row(r, nx, ny), ln.c0, ln.c1);
+            }
+        }
+        double fr[RW];   // 1 for output rows
+#pragma unroll
+        for (int r = 0; r < RW; ++r) fr[r] = ln.out_row(r) ? 1.0 : 0.0;
+#pragma unroll
+        for (int j = 1; j <= D; ++j) {
+            if (j > w.jmax) continue;
+            P2<T> up[R], dn[R];
+            rt_exchange<R, RW, T>(ex, buf, y, up, dn);
+            buf ^= 1;
+            if (!kF && j == 1 && first) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (!w.copy[k]) {
+                        const double d0 = s_d[k][0];
+#pragma unroll
+                        for (int r = 0; r < RW; ++r) {
+                            const double2 v = as_d2<T>(y[r]);
+                            p[k][r].x = d0 * v.x;
+                            p[k][r].y = d0 * v.y;
+                        }
+                    }
+            }
+            if (!ln.at_work(j * R)) continue;
+            rt_level<OP, RW, T>(st, static_cast<T>(s_cc[j - 1]), y, up, dn, u);
+            if (!outs) continue;
+            double s = 0.0;
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const double2 v = as_d2<T>(y[r]);
+                const double y1 = kVec ? v.y : (ln.o1 ? v.y : 0.0);
+                s = fma(fr[r], fma(y1, y1, v.x * v.x), s);
+            }
+            sy[j - 1] += ln.o0 ? s : 0.0;   // lanes outside the output columns count for nothing
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const double d = s_d[k][j];
+                double q = 0.0;
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    const double2 v = as_d2<T>(y[r]);
+                    p[k][r].x = fma(d, v.x, p[k][r].x);
+                    p[k][r].y = fma(d, v.y, p[k][r].y);
+                    const double p1 = kVec ? p[k][r].y : (ln.o1 ? p[k][r].y : 0.0);
+                    q = fma(fr[r], fma(p1, p1, p[k][r].x * p[k][r].x), q);
+                }
+                sp[k][j - 1] += ln.o0 ? q : 0.0;
+            }
+        }
+        if (outs) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                if (!ln.out_row(r)) continue;
+                const long row = ln.row(r, nx, ny);
+                if (store_y) rt_st<kVec>(reinterpret_cast<T*>(w.yout), row, ln.c0, ln.c1, ln.o0, ln.o1, y[r]);
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (w.nt[k] > 0 || w.copy[k]) rt_st<kVec>(w.pout[k], row, ln.c0, ln.c1, ln.o0, ln.o1, p[k][r]);
+            }
+        }
+    }
+}
+
 // Launch L of the window loop: a.tiles_x by a.tiles_y tiles, a.nb workgroups.
-template <int OP, int K, int D, int RW, bool kVec>
+// F32: FP32 sweeps (windows switch to FP32 levels on the device, window_enter).
+template <int OP, int K, int D, int RW, bool kVec, bool F32>
 __global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int L) {
     constexpr int R = radius<OP>(), H = D * R;
     static_assert(RW >= R && kRtWaves * RW > 2 * H && kRtCols > 2 * H, "a tile has outputs");
@@ -210,7 +353,7 @@ __global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int 
     __shared__ double s_d[K][D + 1], s_cc[D];
     const int wg = static_cast<int>(blockIdx.x), tid = static_cast<int>(threadIdx.x);
     WindowPlan<K> w;
-    if (!window_enter<OP, K, D, true, false, kRtWaves>(a, L, wg, nullptr, w)) return;
+    if (!window_enter<OP, K, D, true, F32, kRtWaves>(a, L, wg, nullptr, w)) return;
     const Sten st = sweep_sten<OP>(a);
     if (tid < 64 * K && (tid & 63) <= D) {
         const int k = tid >> 6, j = tid & 63;
@@ -232,91 +375,15 @@ __global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int 
 #pragma unroll
         for (int k = 0; k < K; ++k) sp[k][j] = 0.0;
     }
-    const int nx = a.nx, ny = a.ny, unit = kVec ? 2 : 1;
-    const bool store_y = !w.redo, first = w.win == 0;
-    const RtSpan span = rt_span(wg, a.nb, a.tiles_x * a.tiles_y);
-    int buf = 0;
-    for (int t = span.first; t < span.end; t += span.step) {
-        const RtGeom g = rt_geom(t, nx, ny, a.tiles_x, a.tiles_y, unit);
-        const RtLane<H, RW> ln(g, nx);
-        const bool outs = ln.any_out();
-        double2 y[RW], p[K][RW], u[OP == kOpBurgersJ ? RW + 2 : 1];
-        if (w.jmax > 0) {
-#pragma unroll
-            for (int r = 0; r < RW; ++r) y[r] = rt_ld<kVec>(w.yin, ln.row(r, nx, ny), ln.c0, ln.c1);
-            if constexpr (OP == kOpBurgersJ) {
-#pragma unroll
-                for (int r = 0; r < RW + 2; ++r) u[r] = rt_ld<kVec>(a.u, ln.row(r - 1, nx, ny), ln.c0, ln.c1);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            // the first window starts from p_0 = d_0 y_0 (also when it is
-            // re-executed); a copy reads the window's own result
-            const bool rd = outs && (w.nt[k] > 0 || w.copy[k]) && !(first && !w.copy[k]);
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                p[k][r] = double2{0.0, 0.0};
-                if (rd && ln.out_row(r) && (ln.o0 || ln.o1)) p[k][r] = rt_ld<kVec>(w.pin[k], ln.row(r, nx, ny), ln.c0, ln.c1);
-            }
-        }
-        double fr[RW];   // 1 for output rows
-#pragma unroll
-        for (int r = 0; r < RW; ++r) fr[r] = ln.out_row(r) ? 1.0 : 0.0;
-#pragma unroll
-        for (int j = 1; j <= D; ++j) {
-            if (j > w.jmax) continue;
-            double2 up[R], dn[R];
-            rt_exchange<R, RW>(ex, buf, y, up, dn);
-            buf ^= 1;
-            if (j == 1 && first) {
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (!w.copy[k]) {
-                        const double d0 = s_d[k][0];
-#pragma unroll
-                        for (int r = 0; r < RW; ++r) {
-                            p[k][r].x = d0 * y[r].x;
-                            p[k][r].y = d0 * y[r].y;
-                        }
-                    }
-            }
-            if (!ln.at_work(j * R)) continue;
-            rt_level<OP, RW>(st, s_cc[j - 1], y, up, dn, u);
-            if (!outs) continue;
-            double s = 0.0;
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const double y1 = kVec ? y[r].y : (ln.o1 ? y[r].y : 0.0);
-                s = fma(fr[r], fma(y1, y1, y[r].x * y[r].x), s);
-            }
-            sy[j - 1] += ln.o0 ? s : 0.0;   // lanes outside the output columns count for nothing
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double d = s_d[k][j];
-                double q = 0.0;
-#pragma unroll
-                for (int r = 0; r < RW; ++r) {
-                    p[k][r].x = fma(d, y[r].x, p[k][r].x);
-                    p[k][r].y = fma(d, y[r].y, p[k][r].y);
-                    const double p1 = kVec ? p[k][r].y : (ln.o1 ? p[k][r].y : 0.0);
-                    q = fma(fr[r], fma(p1, p1, p[k][r].x * p[k][r].x), q);
-                }
-                sp[k][j - 1] += ln.o0 ? q : 0.0;
-            }
-        }
-        if (outs) {
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                if (!ln.out_row(r)) continue;
-                const long row = ln.row(r, nx, ny);
-                if (store_y) rt_st<kVec>(w.yout, row, ln.c0, ln.c1, ln.o0, ln.o1, y[r]);
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (w.nt[k] > 0 || w.copy[k]) rt_st<kVec>(w.pout[k], row, ln.c0, ln.c1, ln.o0, ln.o1, p[k][r]);
-            }
+    if constexpr (F32) {
+        if (w.win32) {
+            rt_window<OP, K, D, RW, kVec, float>(a, w, st, wg, s_d, s_cc,
+                                                 reinterpret_cast<RtExchange<R, float>&>(ex), sy, sp);
+            window_exit<K, D, kRtWaves>(a, L, wg, sy, sp);
+            return;
         }
     }
+    rt_window<OP, K, D, RW, kVec, double>(a, w, st, wg, s_d, s_cc, ex, sy, sp);
     window_exit<K, D, kRtWaves>(a, L, wg, sy, sp);
 }
 
@@ -351,6 +418,7 @@ __global__ __launch_bounds__(kRtThreads) void power_rtile(PowerArgs a, const dou
     if constexpr (OP == kOpDiffAdv) st = Sten{a.cW, a.cE, a.cS, a.cN, a.cC, 0.0, 0.0, 0.0, 0.0};
     else if constexpr (OP == kOpDiffAdv3) st = Sten{a.cW, a.cE, a.cS, a.cN, a.cC, a.cW2, a.cE2, a.cS2, a.cN2};
     else st = Sten{a.kx, a.ky, a.gx, a.gy, -2.0 * a.kx - 2.0 * a.ky, 0.0, 0.0, 0.0, 0.0};
+    const RtSten<double> rst(st);
     double sy[DP + 1];   // [DP]: level 0
 #pragma unroll
     for (int j = 0; j <= DP; ++j) sy[j] = 0.0;
@@ -389,10 +457,10 @@ __global__ __launch_bounds__(kRtThreads) void power_rtile(PowerArgs a, const dou
         for (int j = 1; j <= DP; ++j) {
             if (j > nlev) continue;
             double2 up[R], dn[R];
-            rt_exchange<R, RW>(ex, buf, y, up, dn);
+            rt_exchange<R, RW, double>(ex, buf, y, up, dn);
             buf ^= 1;
             if (!ln.at_work(j * R)) continue;
-            rt_level<OP, RW>(st, st.c4, y, up, dn, u);
+            rt_level<OP, RW, double>(rst, st.c4, y, up, dn, u);
             sy[j - 1] += sum();
         }
         if (outs) {
@@ -426,18 +494,19 @@ __global__ __launch_bounds__(kBlockThreads) void power_rtile_final(PowerArgs a, 
     }
 }
 
-// the register-tile kernels there are: (operator, outputs, depth)
+// the register-tile kernels there are: (operator, outputs, depth), the
+// radius-1 operators also for FP32 sweeps
 #define LX_RTILE_KERNELS(X)                                                                     \
     X(kOpDiffAdv, 1, 8) X(kOpDiffAdv, 2, 8) X(kOpDiffAdv, 3, 8) X(kOpBurgersJ, 1, 8)            \
     X(kOpBurgersJ, 2, 8) X(kOpDiffAdv3, 1, 6)
 
-template <int OP, int K, int D>
+template <int OP, int K, int D, bool F32>
 void rtile_launch(const SweepArgs& a, const int rw, const bool vec, const int L, hipStream_t s) {
     const dim3 grid(a.nb), block(kRtThreads);
-    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true>), grid, block, 0, s, a, L);
-    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false>), grid, block, 0, s, a, L);
-    else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true>), grid, block, 0, s, a, L);
-    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false>), grid, block, 0, s, a, L);
+    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true, F32>), grid, block, 0, s, a, L);
+    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false, F32>), grid, block, 0, s, a, L);
+    else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32>), grid, block, 0, s, a, L);
+    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32>), grid, block, 0, s, a, L);
 }
 
 template <int OP, int DP>
@@ -490,13 +559,16 @@ static bool rtile_fits(int op, int depth, int nx, int ny, int tiles_x, int tiles
     return w <= kRtCols - 2 * H && h <= kRtWaves * rw - 2 * H;
 }
 
-hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, const SweepArgs& a, int L, hipStream_t s) {
+hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, bool fp32, const SweepArgs& a, int L,
+                             hipStream_t s) {
     if (!rtile_fits(op, rtile_depth(op, K), a.nx, a.ny, a.tiles_x, a.tiles_y, a.nb, rw, vec)) return hipErrorInvalidValue;
-    if (op == kOpBurgersJ && a.u == nullptr) return hipErrorInvalidValue;
-#define LX_RTILE_LAUNCH(O, KK, DD)                      \
-    if (op == (O) && K == (KK)) {                       \
-        rtile_launch<(O), (KK), (DD)>(a, rw, vec, L, s); \
-        return hipGetLastError();                       \
+    if (op == kOpBurgersJ && (a.u == nullptr || (fp32 && a.u32 == nullptr))) return hipErrorInvalidValue;
+    if (fp32 && op == kOpDiffAdv3) return hipErrorInvalidValue;
+#define LX_RTILE_LAUNCH(O, KK, DD)                                                          \
+    if (op == (O) && K == (KK)) {                                                           \
+        if (fp32) rtile_launch<(O), (KK), (DD), ((O) != kOpDiffAdv3)>(a, rw, vec, L, s);     \
+        else rtile_launch<(O), (KK), (DD), false>(a, rw, vec, L, s);                        \
+        return hipGetLastError();                                                           \
     }
     LX_RTILE_KERNELS(LX_RTILE_LAUNCH)
 #undef LX_RTILE_LAUNCH

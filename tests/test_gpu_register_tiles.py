@@ -153,3 +153,25 @@ def test_power_iteration_of_badly_scaled_vectors_and_operators(ctx, scale, nx):
     op.D, op.vx, op.vy = op.D * s, op.vx * s, op.vy * s
     rho, _, _ = ctx.spectrum(op, x0=dev(v), iters=20)
     assert abs(rho - rho_o * s) <= 1e-12 * rho_o * s
+
+
+@pytest.mark.parametrize("switch", [1e4, 0.0])
+@pytest.mark.parametrize("kind,nx,ny,ls", [("da", 10, 12, [1]), ("da", 113, 33, [0, 2]), ("da", 256, 192, [1, 2, 3]),
+                                           ("da", 1001, 640, [0, 1, 3]), ("bu", 11, 9, [1]), ("bu", 112, 50, [0, 3]),
+                                           ("bu", 900, 701, [1, 2])])
+def test_register_tiles_fp32_levels(ctx, kind, nx, ny, ls, switch):
+    """FP32 sweeps on register tiles: the basis and the stencil in FP32 once
+    every term is small (0: from the first window), everything else in FP64;
+    within the solve's tolerance of the FP64 oracle with the default switch,
+    1e-5 with FP32 throughout (the bounds of the other FP32 window kernels)."""
+    case = _case(kind, nx, ny, 2 * nx + ny)
+    op, A, u, v, h, c, g = case
+    op.prec = B.LX_FP32_SWEEP
+    say("register tiles fp32", kind, nx, ny, ls, switch)
+    r, o = _solve(ctx, case, ls, 0, rtol=1e-8, max_iters=300, fp32_switch=switch)
+    assert r.status == B.LX_OK and r.stats["depth"] == 8 and r.stats["marching"] == 0
+    assert r.stats["n_fp32"] % 8 == 0 and (switch > 0 or r.stats["n_fp32"] > 0)
+    ref = leja_phi(A, v, [(l, 1.0, 1.0) for l in ls], h, c, g, 1e-8, 0.0, 300)
+    errs = [rel(a, b) for a, b in zip(o, ref.p)]
+    say("fp32 register tile errors", errs, r.iters, ref.iters, r.stats["n_fp32"])
+    assert max(errs) <= (1e-8 if switch > 0 else 1e-5)
