@@ -1124,16 +1124,8 @@ void lx_destroy(lx_ctx* ctx) {
     for (double* p : ctx->blk_ws) (void)hipFree(p);
     (void)hipFree(ctx->u32);
     (void)hipFree(ctx->partials);
-    (void)hipFree(ctx->ctl);
-    (void)hipFree(ctx->coef);
-    (void)hipFree(ctx->coef_state);
-    (void)hipFree(ctx->xi);
-    (void)hipHostFree(ctx->h_ctl);
-    (void)hipHostFree(ctx->h_poll);
-    (void)hipHostFree(ctx->h_progress);
-    (void)hipHostFree(ctx->h_rho);
-    (void)hipHostFree(ctx->h_coef);
-    (void)hipHostFree(ctx->h_xi);
+    (void)hipFree(ctx->small_mem);
+    (void)hipHostFree(ctx->pinned_mem);
     for (hipEvent_t e : ctx->poll_ev)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : ctx->tev) (void)hipEventDestroy(e);
@@ -1161,22 +1153,33 @@ lx_status lx_create(lx_ctx** out, size_t n_max, int k_max, void* stream) {
     // 4096 workgroups (grown on demand for larger grids)
     ctx->partials_len = 2 * static_cast<size_t>(1 + k_max) * 4096;
     if (hipMalloc(&ctx->partials, sizeof(double) * ctx->partials_len) != hipSuccess) return bail(LX_ENOMEM);
-    if (hipMalloc(&ctx->ctl, sizeof(LoopCtl)) != hipSuccess) return bail(LX_ENOMEM);
-    if (hipMalloc(&ctx->coef, sizeof(double) * k_max * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
-    if (hipMalloc(&ctx->coef_state, sizeof(double) * k_max * 2 * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
-    if (hipMalloc(&ctx->xi, sizeof(double) * lx::kMaxPoints) != hipSuccess) return bail(LX_ENOMEM);
-    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_ctl), sizeof(LoopCtl), hipHostMallocDefault) != hipSuccess)
+    // one allocation for the small device buffers and one for the pinned ones:
+    // a call costs tens of microseconds, as much as a small solve
+    constexpr size_t kAlign = 256, kTable = sizeof(double) * lx::kMaxPoints;
+    size_t dev_bytes = 0, pin_bytes = 0;
+    auto place = [&](size_t& total, size_t bytes) {
+        const size_t at = total;
+        total += (bytes + kAlign - 1) / kAlign * kAlign;
+        return at;
+    };
+    const size_t d_ctl = place(dev_bytes, sizeof(LoopCtl)), d_coef = place(dev_bytes, kTable * k_max),
+                 d_state = place(dev_bytes, kTable * k_max * 2), d_xi = place(dev_bytes, kTable);
+    const size_t p_ctl = place(pin_bytes, sizeof(LoopCtl)), p_poll = place(pin_bytes, sizeof(SweepState)),
+                 p_progress = place(pin_bytes, sizeof(int)), p_rho = place(pin_bytes, sizeof(lx::RhoRecord)),
+                 p_coef = place(pin_bytes, kTable * k_max), p_xi = place(pin_bytes, kTable);
+    if (hipMalloc(&ctx->small_mem, dev_bytes) != hipSuccess) return bail(LX_ENOMEM);
+    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->pinned_mem), pin_bytes, hipHostMallocDefault) != hipSuccess)
         return bail(LX_ENOMEM);
-    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_poll), sizeof(SweepState), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->h_progress), sizeof(int), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ctx->h_rho), sizeof(lx::RhoRecord), hipHostMallocDefault) != hipSuccess)
-        return bail(LX_ENOMEM);
-    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_coef), sizeof(double) * k_max * lx::kMaxPoints,
-                      hipHostMallocDefault) != hipSuccess)
-        return bail(LX_ENOMEM);
-    if (hipHostMalloc(reinterpret_cast<void**>(&ctx->h_xi), sizeof(double) * lx::kMaxPoints, hipHostMallocDefault) !=
-        hipSuccess)
-        return bail(LX_ENOMEM);
+    ctx->ctl = reinterpret_cast<LoopCtl*>(ctx->small_mem + d_ctl);
+    ctx->coef = reinterpret_cast<double*>(ctx->small_mem + d_coef);
+    ctx->coef_state = reinterpret_cast<double*>(ctx->small_mem + d_state);
+    ctx->xi = reinterpret_cast<double*>(ctx->small_mem + d_xi);
+    ctx->h_ctl = reinterpret_cast<LoopCtl*>(ctx->pinned_mem + p_ctl);
+    ctx->h_poll = reinterpret_cast<SweepState*>(ctx->pinned_mem + p_poll);
+    ctx->h_progress = reinterpret_cast<int*>(ctx->pinned_mem + p_progress);
+    ctx->h_rho = reinterpret_cast<lx::RhoRecord*>(ctx->pinned_mem + p_rho);
+    ctx->h_coef = reinterpret_cast<double*>(ctx->pinned_mem + p_coef);
+    ctx->h_xi = reinterpret_cast<double*>(ctx->pinned_mem + p_xi);
     for (auto& e : ctx->poll_ev)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail(LX_EDEVICE);
     std::memset(ctx->h_ctl, 0, sizeof(LoopCtl));

@@ -65,12 +65,14 @@ struct lx_ctx {
     std::vector<double*> blk_ws;            // second buffer per output of speculative windows
     double* partials = nullptr;
     size_t partials_len = 0;
+    char* small_mem = nullptr;              // ctl, coef, coef_state and xi
     lx::LoopCtl* ctl = nullptr;
     double* coef = nullptr;                 // k_max * kMaxPoints
     double* coef_state = nullptr;           // k_max divided-difference tables' rows (2 * ld each)
     double* xi = nullptr;                   // kMaxPoints
     int xi_uploaded = 0;
-    // pinned host staging
+    // pinned host staging, all in pinned_mem
+    char* pinned_mem = nullptr;
     lx::LoopCtl* h_ctl = nullptr;           // initial loop control (pinned)
     // what running kernels write to the host (pinned)
     lx::SweepState* h_poll = nullptr;       // a Leja loop's final state
