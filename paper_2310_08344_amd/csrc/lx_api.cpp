@@ -549,8 +549,9 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
         upto = std::min(upto, NC);
         if (upto <= have) return LX_OK;
         // at least kCoefStep more: a launch costs more than a few columns
-        upto = std::min(std::max(upto, have + kCoefStep), NC);
+        // (register tiles form the columns after the first themselves)
         const bool first = have == 0;
+        if (t.stream != 2 || !first) upto = std::min(std::max(upto, have + kCoefStep), NC);
         if (upto > rows) {   // tables with more rows start over (the same values again)
             rows = lx::coef_rows(upto, NC);
             have = 0;
@@ -654,8 +655,21 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
             const int L = launched;
             s = ensure_coeffs(coeffs_for(L + 1));
             if (s != LX_OK) return s;
-            if (t.stream == 2) LX_HIP(ctx, lx::launch_leja_rtile(opcode, K, rw, vec_rt, fp32, a, L, ctx->stream));
-            else if (t.stream == 1) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
+            if (t.stream == 2) {
+                // the columns of the next launch, unless its table has to grow
+                lx::CoefJob job{};
+                const int upto = std::min(coeffs_for(L + 2), NC);
+                if (upto > have && upto <= rows && rows <= lx::kCoefJobRows) {
+                    for (int k = 0; k < K; ++k) job.s[k] = ca.s[k];
+                    job.state = ctx->coef_state;
+                    job.coef = ctx->coef;
+                    job.rows = rows;
+                    job.j0 = have;
+                    job.j1 = upto;
+                    have = upto;
+                }
+                LX_HIP(ctx, lx::launch_leja_rtile(opcode, K, rw, vec_rt, fp32, a, L, job, ctx->stream));
+            } else if (t.stream == 1) LX_HIP(ctx, lx::launch_leja_stream(opcode, K, D, fp32, a, L, ctx->stream));
             else if (blk) LX_HIP(ctx, lx::launch_leja_block(opcode, K, t.th, D, a, L, ctx->stream));
             else if (pair) LX_HIP(ctx, lx::launch_leja_pair(opcode, K, t.th, a, L, ctx->stream));
             else LX_HIP(ctx, lx::launch_leja_sweep(opcode, K, fp32, t, a, L, ctx->stream));
@@ -2046,10 +2060,10 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
         const int n = std::max(1, sweeps / rd);
         const bool vec = nx % 2 == 0;
         hipError_t e = hipSuccess;
-        for (int L = 0; L < 2 && e == hipSuccess; ++L) e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, ctx->stream);
+        for (int L = 0; L < 2 && e == hipSuccess; ++L) e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, lx::CoefJob{}, ctx->stream);
         if (e == hipSuccess) e = hipEventRecord(ctx->tev[0], ctx->stream);
         for (int L = 2; L < n + 2 && e == hipSuccess; ++L)
-            e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, ctx->stream);
+            e = lx::launch_leja_rtile(opcode, K, g.rw, vec, fp32, a, L, lx::CoefJob{}, ctx->stream);
         if (e == hipSuccess) e = hipEventRecord(ctx->tev[1], ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(ctx->tev[1]);
         if (e != hipSuccess) return cleanup(fail(ctx, LX_EDEVICE, "tuning launch failed: %s", hipGetErrorString(e)));

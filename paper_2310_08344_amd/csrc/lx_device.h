@@ -239,8 +239,10 @@ struct RtileGrid {
 // workgroups (256) holds the tiles, else 8
 RtileGrid rtile_grid(int op, int depth, int nx, int ny, bool vec);
 // a.tiles_x, a.tiles_y and a.nb as rtile_grid gave them; partials as
-// launch_leja_block
-hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, bool fp32, const SweepArgs& a, int L, hipStream_t s);
+// launch_leja_block; job: coefficient columns for the launches after this one
+struct CoefJob;
+hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, bool fp32, const SweepArgs& a, int L,
+                             const CoefJob& job, hipStream_t s);
 // as launch_power_stream, with rtile_power_depth(op) in place of its depth
 // (raw0 allows any nlev)
 hipError_t launch_power_rtile(int op, int rw, bool vec, const PowerArgs& a, const double* in, double* out, int b,
@@ -305,6 +307,16 @@ hipError_t launch_batch_coeffs(const BatchInst* insts, int n_inst, const double*
 // Rows a table is started with so that d_0 .. d_{upto-1} exist: 128, then
 // 256, then as many as there are (ld), so that the common loop does not carry
 // rows it never reads.
+// Columns [j0, j1) of a loop's tables (0 < j0; none: j1 <= j0), formed by the
+// window launch before the one that reads them, a workgroup per output beside
+// the tiles'; at most kCoefJobRows rows.
+constexpr int kCoefJobRows = 512;
+struct CoefJob {
+    CoefSeries s[kKMax];
+    double* state;
+    double* coef;
+    int rows, j0, j1;
+};
 constexpr int coef_rows(int upto, int ld) {
     const int r = upto <= 128 ? 128 : (upto <= 256 ? 256 : kMaxCoefRows);
     return r < ld ? r : ld;

@@ -26,6 +26,7 @@
 // launch, 42), FP32 sweeps of the Burgers Jacobian at 512 x 512 1.95 (4.7).
 #include <hip/hip_runtime.h>
 
+#include "coef_device.h"
 #include "lx_device.h"
 #include "stream_device.h"
 #include "tile_device.h"
@@ -346,12 +347,23 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
 // Launch L of the window loop: a.tiles_x by a.tiles_y tiles, a.nb workgroups.
 // F32: FP32 sweeps (windows switch to FP32 levels on the device, window_enter).
 template <int OP, int K, int D, int RW, bool kVec, bool F32>
-__global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int L) {
+__global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int L, const CoefJob job) {
     constexpr int R = radius<OP>(), H = D * R;
     static_assert(RW >= R && kRtWaves * RW > 2 * H && kRtCols > 2 * H, "a tile has outputs");
     __shared__ RtExchange<R> ex;
     __shared__ double s_d[K][D + 1], s_cc[D];
     const int wg = static_cast<int>(blockIdx.x), tid = static_cast<int>(threadIdx.x);
+    if (wg >= a.nb) {
+        // the workgroups past the tiles': output wg - nb's next coefficients,
+        // unless the loop has ended.  Eight columns take 4 to 6 us, less than a
+        // window; in launches of their own, 6 us for every second window, a
+        // solve of 64 x 64 took 149 us, now 127 (333 x 250 197, now 167).
+        const int k = wg - a.nb;
+        if (L > 0 && __hip_atomic_load(&a.ctl->slot[2].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+        advance_columns<false>(job.s[k], a.xi, job.state + static_cast<long>(k) * 2 * a.ld,
+                               job.coef + static_cast<long>(k) * a.ld, a.ld, job.rows, job.j0, job.j1);
+        return;
+    }
     WindowPlan<K> w;
     if (!window_enter<OP, K, D, true, F32, kRtWaves>(a, L, wg, nullptr, w)) return;
     const Sten st = sweep_sten<OP>(a);
@@ -501,12 +513,12 @@ __global__ __launch_bounds__(kBlockThreads) void power_rtile_final(PowerArgs a, 
     X(kOpBurgersJ, 2, 8) X(kOpDiffAdv3, 1, 6)
 
 template <int OP, int K, int D, bool F32>
-void rtile_launch(const SweepArgs& a, const int rw, const bool vec, const int L, hipStream_t s) {
-    const dim3 grid(a.nb), block(kRtThreads);
-    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true, F32>), grid, block, 0, s, a, L);
-    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false, F32>), grid, block, 0, s, a, L);
-    else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32>), grid, block, 0, s, a, L);
-    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32>), grid, block, 0, s, a, L);
+void rtile_launch(const SweepArgs& a, const int rw, const bool vec, const int L, const CoefJob& job, hipStream_t s) {
+    const dim3 grid(a.nb + (job.j1 > job.j0 ? K : 0)), block(kRtThreads);
+    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true, F32>), grid, block, 0, s, a, L, job);
+    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false, F32>), grid, block, 0, s, a, L, job);
+    else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32>), grid, block, 0, s, a, L, job);
+    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32>), grid, block, 0, s, a, L, job);
 }
 
 template <int OP, int DP>
@@ -560,14 +572,16 @@ static bool rtile_fits(int op, int depth, int nx, int ny, int tiles_x, int tiles
 }
 
 hipError_t launch_leja_rtile(int op, int K, int rw, bool vec, bool fp32, const SweepArgs& a, int L,
-                             hipStream_t s) {
+                             const CoefJob& job, hipStream_t s) {
+    if (job.j1 > job.j0 && (job.j0 < 1 || job.j1 > job.rows || job.rows > kCoefJobRows || job.rows > a.ld))
+        return hipErrorInvalidValue;
     if (!rtile_fits(op, rtile_depth(op, K), a.nx, a.ny, a.tiles_x, a.tiles_y, a.nb, rw, vec)) return hipErrorInvalidValue;
     if (op == kOpBurgersJ && (a.u == nullptr || (fp32 && a.u32 == nullptr))) return hipErrorInvalidValue;
     if (fp32 && op == kOpDiffAdv3) return hipErrorInvalidValue;
 #define LX_RTILE_LAUNCH(O, KK, DD)                                                          \
     if (op == (O) && K == (KK)) {                                                           \
-        if (fp32) rtile_launch<(O), (KK), (DD), ((O) != kOpDiffAdv3)>(a, rw, vec, L, s);     \
-        else rtile_launch<(O), (KK), (DD), false>(a, rw, vec, L, s);                        \
+        if (fp32) rtile_launch<(O), (KK), (DD), ((O) != kOpDiffAdv3)>(a, rw, vec, L, job, s); \
+        else rtile_launch<(O), (KK), (DD), false>(a, rw, vec, L, job, s);                    \
         return hipGetLastError();                                                           \
     }
     LX_RTILE_KERNELS(LX_RTILE_LAUNCH)

@@ -175,3 +175,39 @@ def test_register_tiles_fp32_levels(ctx, kind, nx, ny, ls, switch):
     errs = [rel(a, b) for a, b in zip(o, ref.p)]
     say("fp32 register tile errors", errs, r.iters, ref.iters, r.stats["n_fp32"])
     assert max(errs) <= (1e-8 if switch > 0 else 1e-5)
+
+
+@pytest.mark.parametrize("kind,ls,cfl", [("da", [0], 20.0), ("da", [0, 1, 3], 60.0), ("da", [1], 120.0),
+                                         ("up3", [1], 60.0)])
+def test_register_tile_windows_form_the_coefficients_they_need(ctx, kind, ls, cfl):
+    """Coefficients formed beside the tiles: bit for bit one iteration per
+    launch, whose coefficients come from launches of their own.  (The last
+    case needs coefficients below 1e-33, what a double-double table of values
+    up to 1 resolves: its loop diverges, in every kernel.)"""
+    case = _case(kind, 47, 53, 7, cfl=cfl)
+    say("register tile coefficients", kind, ls, cfl)
+    if kind == "up3":
+        for depth in (0, 1):
+            with pytest.raises(B.LxError, match="nonfinite"):
+                _solve(ctx, case, ls, depth, rtol=1e-9, max_iters=900)
+        return
+    r, o = _solve(ctx, case, ls, 0, rtol=1e-9, max_iters=900)
+    r1, o1 = _solve(ctx, case, ls, 1, rtol=1e-9, max_iters=900)
+    say("iterations", r.iters, r1.iters)
+    assert r.status == B.LX_OK and r.stats["depth"] == DEPTH[kind] and r1.stats["depth"] == 1
+    if r.iters == r1.iters:
+        assert all(np.array_equal(a, b) for a, b in zip(o, o1))
+    else:
+        assert max(rel(a, b) for a, b in zip(o, o1)) <= 1e-8
+
+
+@pytest.mark.parametrize("max_iters", [120, 121, 128, 130, 256, 300, 513, 700])
+def test_register_tile_loops_past_the_first_coefficient_table(ctx, max_iters):
+    """Loops that never converge, so that the tables grow to 256 rows and past
+    the 512 that a window launch forms beside its tiles."""
+    case = _case("da", 47, 53, 7, cfl=4.0)
+    say("register tile long loops", max_iters)
+    r, o = _solve(ctx, case, [0, 2], 0, rtol=1e-300, max_iters=max_iters, raise_on_error=False)
+    r1, o1 = _solve(ctx, case, [0, 2], 1, rtol=1e-300, max_iters=max_iters, raise_on_error=False)
+    assert r.status == r1.status == B.LX_ENOTCONV and r.iters == r1.iters == [max_iters] * 2
+    assert all(np.array_equal(a, b) for a, b in zip(o, o1))
