@@ -549,8 +549,8 @@ lx_status lx_set_depth(lx_ctx* ctx, int depth, int th, int nb);
 /* Which kernel later windows (depth >= 3) and power iterations run on:
  * kind 0 = automatic (windows as lx_set_depth's automatic choice says, LDS
  * tiles for a forced depth with no tuned entry; power iteration on register
- * tiles for small grids and odd grids of the diffusion-advection operators,
- * by register marching for larger ones where it applies), 1 = LDS tiles
+ * tiles, but by register marching for larger grids where it applies, and one
+ * sweep per launch for odd grids of the Burgers Jacobian), 1 = LDS tiles
  * for both (leja_block, power_block), 2 = register marching where it
  * applies (leja_stream: the operators and precisions and the depths that
  * lx_set_depth lists; power_stream: LX_OP_DIFFADV2D; even nx, sides of at

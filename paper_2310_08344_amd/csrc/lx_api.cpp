@@ -36,11 +36,13 @@ using lx::Tile;
 
 namespace {
 
-// Power iterations of at most this many points run on register tiles.  us for
-// 20 sweeps, register tiles / marching: 64^2 36 / 85, 1024^2 57 / 76, 1400^2 90 /
-// 76; register / LDS tiles, Burgers: 64^2 49 / 59, 1024^2 77 / 105, 2048^2 211 /
-// 255; third-order upwind: 1024^2 81 / 96, 2048^2 241 / 237.
-constexpr long kRtilePowerPoints = 5L << 18, kRtilePowerPointsTiles = 1L << 22;
+// Power iterations of the five-point operator on at most this many points run
+// on register tiles.  us for 20 sweeps, register tiles / marching: 64^2 36 / 85,
+// 1024^2 57 / 76, 1400^2 90 / 76.  The Burgers Jacobian and the third-order
+// upwind operator, which do not march, always do; register / LDS tiles, Burgers:
+// 64^2 49 / 59, 1024^2 77 / 105, 2048^2 174 / 256, 8192^2 1840 / 3680; third-order
+// upwind: 1024^2 81 / 96, 2048^2 186 / 237, 8192^2 1590 / 3060.
+constexpr long kRtilePowerPoints = 5L << 18;
 constexpr double kRtileRhoMin = 1e-8, kRtileRhoMax = 1e17;
 // Every workgroup adds the records of all workgroups of the launch before, so
 // the tuner leaves out shapes of one workgroup per tile with more workgroups
@@ -1241,15 +1243,13 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         x0 = ctx->ybuf[1];
     }
     const bool vec2 = aligned16(x0) && (d_u == nullptr || aligned16(d_u));
-    // register tiles where a launch is short (and for every odd grid of the
-    // diffusion-advection operators); an estimate outside kRtileRho, where a
+    // register tiles (odd grids: of the diffusion-advection operators); an estimate outside kRtileRho, where a
     // launch's unnormalised levels could lose range, is formed again below
     const bool vec_rt = vec2 && nx % 2 == 0;
     lx_operator op64 = *op;
     op64.prec = LX_FP64;
     if (ctx->win_kind == 0 && rtile_ok(op64, lx::rtile_power_depth(opcode_of(op->kind))) &&
-        (vec_rt ? N <= (op->kind == LX_OP_DIFFADV2D ? kRtilePowerPoints : kRtilePowerPointsTiles)
-                : is_diffadv(op->kind))) {
+        (vec_rt ? op->kind != LX_OP_DIFFADV2D || N <= kRtilePowerPoints : is_diffadv(op->kind))) {
         double rho = 0.0;
         s = spectrum_deep(ctx, *op, d_u, x0, iters, safety, true, vec_rt, &rho, c, gamma);
         if (s == LX_OK && rho >= kRtileRhoMin && rho <= kRtileRhoMax) {

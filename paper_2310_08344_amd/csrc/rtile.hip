@@ -346,8 +346,8 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
 
 // Launch L of the window loop: a.tiles_x by a.tiles_y tiles, a.nb workgroups.
 // F32: FP32 sweeps (windows switch to FP32 levels on the device, window_enter).
-template <int OP, int K, int D, int RW, bool kVec, bool F32>
-__global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int L, const CoefJob job) {
+template <int OP, int K, int D, int RW, bool kVec, bool F32, int kEu>
+__global__ __launch_bounds__(kRtThreads, kEu) void leja_rtile(SweepArgs a, const int L, const CoefJob job) {
     constexpr int R = radius<OP>(), H = D * R;
     static_assert(RW >= R && kRtWaves * RW > 2 * H && kRtCols > 2 * H, "a tile has outputs");
     __shared__ RtExchange<R> ex;
@@ -404,8 +404,8 @@ __global__ __launch_bounds__(kRtThreads) void leja_rtile(SweepArgs a, const int 
 // sums and records of power_stream (stream.hip).
 // ---------------------------------------------------------------------------
 
-template <int OP, int DP, int RW, bool kVec>
-__global__ __launch_bounds__(kRtThreads) void power_rtile(PowerArgs a, const double* __restrict__ in,
+template <int OP, int DP, int RW, bool kVec, int kEu>
+__global__ __launch_bounds__(kRtThreads, kEu) void power_rtile(PowerArgs a, const double* __restrict__ in,
                                                           double* __restrict__ out, const int b, const int nlev,
                                                           const int prev, const int raw0) {
     constexpr int R = radius<OP>(), H = DP * R;
@@ -512,27 +512,43 @@ __global__ __launch_bounds__(kBlockThreads) void power_rtile_final(PowerArgs a, 
     X(kOpDiffAdv, 1, 8) X(kOpDiffAdv, 2, 8) X(kOpDiffAdv, 3, 8) X(kOpBurgersJ, 1, 8)            \
     X(kOpBurgersJ, 2, 8) X(kOpDiffAdv3, 1, 6)
 
+// Launches of more than one round of workgroups of 8 rows per lane run the
+// kernels bounded to 128 registers, two workgroups per CU, so that one loads
+// while the other forms levels, where that costs few spills: power iteration
+// (us for 20 sweeps, one / two per CU: Burgers 1400^2 133 / 118, 2048^2 210 / 174;
+// third-order upwind 2048^2 240 / 186, 4095^2 535 / 447; five-point 2049^2 175 /
+// 139; within one round it costs 2 %) and the windows of the third-order upwind
+// operator (us per iteration 1201 x 1100 6.8 / 5.6, 2049 x 2047 13.9 / 10.7, 4095^2
+// 48 / 35).  The other windows spill in their levels (five-point 2048^2 10.5 /
+// 21.3).
+constexpr int kRtRound = 256;
+
 template <int OP, int K, int D, bool F32>
 void rtile_launch(const SweepArgs& a, const int rw, const bool vec, const int L, const CoefJob& job, hipStream_t s) {
     const dim3 grid(a.nb + (job.j1 > job.j0 ? K : 0)), block(kRtThreads);
-    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true, F32>), grid, block, 0, s, a, L, job);
-    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false, F32>), grid, block, 0, s, a, L, job);
-    else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32>), grid, block, 0, s, a, L, job);
-    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32>), grid, block, 0, s, a, L, job);
+    if (rw == 4 && vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, true, F32, 2>), grid, block, 0, s, a, L, job);
+    else if (rw == 4) hipLaunchKernelGGL((leja_rtile<OP, K, D, 4, false, F32, 2>), grid, block, 0, s, a, L, job);
+    else if (OP == kOpDiffAdv3 && a.nb > kRtRound) {
+        constexpr int kEu = OP == kOpDiffAdv3 ? 4 : 2;
+        if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32, kEu>), grid, block, 0, s, a, L, job);
+        else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32, kEu>), grid, block, 0, s, a, L, job);
+    } else if (vec) hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, true, F32, 2>), grid, block, 0, s, a, L, job);
+    else hipLaunchKernelGGL((leja_rtile<OP, K, D, 8, false, F32, 2>), grid, block, 0, s, a, L, job);
 }
 
 template <int OP, int DP>
 void power_rtile_launch(const PowerArgs& a, const double* in, double* out, const int rw, const bool vec, const int b,
                         const int nlev, const int prev, const int raw0, hipStream_t s) {
     const dim3 grid(a.nb), block(kRtThreads);
-    if (rw == 4 && vec)
-        hipLaunchKernelGGL((power_rtile<OP, DP, 4, true>), grid, block, 0, s, a, in, out, b, nlev, prev, raw0);
-    else if (rw == 4)
-        hipLaunchKernelGGL((power_rtile<OP, DP, 4, false>), grid, block, 0, s, a, in, out, b, nlev, prev, raw0);
-    else if (vec)
-        hipLaunchKernelGGL((power_rtile<OP, DP, 8, true>), grid, block, 0, s, a, in, out, b, nlev, prev, raw0);
-    else
-        hipLaunchKernelGGL((power_rtile<OP, DP, 8, false>), grid, block, 0, s, a, in, out, b, nlev, prev, raw0);
+#define LX_POWER_RTILE(RW, VEC, EU) \
+    hipLaunchKernelGGL((power_rtile<OP, DP, RW, VEC, EU>), grid, block, 0, s, a, in, out, b, nlev, prev, raw0)
+    if (rw == 4 && vec) LX_POWER_RTILE(4, true, 2);
+    else if (rw == 4) LX_POWER_RTILE(4, false, 2);
+    else if (a.nb > kRtRound && vec) LX_POWER_RTILE(8, true, 4);
+    else if (a.nb > kRtRound) LX_POWER_RTILE(8, false, 4);
+    else if (vec) LX_POWER_RTILE(8, true, 2);
+    else LX_POWER_RTILE(8, false, 2);
+#undef LX_POWER_RTILE
 }
 
 }  // namespace

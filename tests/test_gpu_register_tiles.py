@@ -211,3 +211,26 @@ def test_register_tile_loops_past_the_first_coefficient_table(ctx, max_iters):
     r1, o1 = _solve(ctx, case, [0, 2], 1, rtol=1e-300, max_iters=max_iters, raise_on_error=False)
     assert r.status == r1.status == B.LX_ENOTCONV and r.iters == r1.iters == [max_iters] * 2
     assert all(np.array_equal(a, b) for a, b in zip(o, o1))
+
+
+@pytest.mark.parametrize("kind,nx,ny", [("bu", 1400, 1300), ("up3", 1301, 1201), ("up3", 1302, 1200),
+                                        ("da", 1601, 1300)])
+def test_power_iteration_on_more_than_one_round_of_tiles(ctx, kind, nx, ny):
+    op, A, u, v, h, c, g = _case(kind, nx, ny, nx + 2 * ny)
+    say("register tile power, two workgroups per CU", kind, nx, ny)
+    rho, _, _ = ctx.spectrum(op, u=dev(u) if u is not None else None, x0=dev(v), iters=10)
+    rho_o, _ = power_iteration(A, v, 10)
+    assert abs(rho - rho_o) <= 1e-12 * rho_o
+
+
+@pytest.mark.parametrize("nx,ny", [(1201, 1100), (2049, 1040)])
+def test_upwind_windows_on_more_than_one_round_of_tiles(ctx, nx, ny):
+    case = _case("up3", nx, ny, 8, cfl=4.0)
+    say("upwind register tiles, two workgroups per CU", nx, ny)
+    r, o = _solve(ctx, case, [1], 0, rtol=1e-9, max_iters=100)
+    r1, o1 = _solve(ctx, case, [1], 1, rtol=1e-9, max_iters=100)
+    assert r.stats["depth"] == 6 and r1.stats["depth"] == 1
+    if r.iters == r1.iters:
+        assert np.array_equal(o[0], o1[0])
+    else:
+        assert rel(o[0], o1[0]) <= 1e-8
