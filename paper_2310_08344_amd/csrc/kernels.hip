@@ -23,6 +23,8 @@
 // XCD shortly before.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "lx_device.h"
 #include "sweep_device.h"
 
@@ -164,51 +166,124 @@ __global__ void to_fp32_kernel(const double* __restrict__ x, float* __restrict__
     }
 }
 
-// Burgers right-hand side pieces (one point per thread, used once per step)
-__device__ __forceinline__ double burgers_F_at(const double* __restrict__ u, int i, int j, int nx, int ny,
-                                               double nu, double dx, double dy) {
-    const int ie = (i + 1 == nx) ? 0 : i + 1, iw = (i == 0) ? nx - 1 : i - 1;
-    const int jn = (j + 1 == ny) ? 0 : j + 1, js = (j == 0) ? ny - 1 : j - 1;
-    const double c = u[static_cast<long>(j) * nx + i];
-    const double e = u[static_cast<long>(j) * nx + ie], w = u[static_cast<long>(j) * nx + iw];
-    const double nn = u[static_cast<long>(jn) * nx + i], s = u[static_cast<long>(js) * nx + i];
-    const double lap = (e - 2.0 * c + w) / (dx * dx) + (nn - 2.0 * c + s) / (dy * dy);
-    const double div = (e * e - w * w) / (2.0 * dx) + (nn * nn - s * s) / (2.0 * dy);
-    return nu * lap - 0.5 * div;
+// Burgers right-hand side pieces, once or twice per step: F(u), and the
+// remainder, on columns of kBurgersRows points per thread.
+//
+// Bound by memory: two passes over a grid take 13 us at 2048^2, three 20 us, at
+// the rate of a large copy.  A point has 4 quotients (12 for the remainder) by
+// the same four spacings, 11 instructions each as divisions; as products with
+// the rounded reciprocal, corrected once by the exact residual, 3, with the
+// quotient's rounding.  Together with 64-bit indices by division this took 22
+// and 46 us, now 20 and 26 (512^2: 4.2 and 8.0, now 4.1 and 4.7).
+constexpr int kBurgersRows = 4, kBurgersTx = 64, kBurgersTy = kBlockThreads / kBurgersTx;
+
+struct BurgersSpacing {
+    double nu, xx, yy, x2, y2;          // dx^2, dy^2, 2 dx, 2 dy
+    double rxx, ryy, rx2, ry2;          // their reciprocals
+};
+
+// x / d, r = 1 / d rounded
+template <bool kRecip>
+__device__ __forceinline__ double quotient(const double x, const double d, const double r) {
+    if constexpr (!kRecip) return x / d;
+    const double q = x * r;
+    return fma(fma(-q, d, x), r, q);
 }
 
-__global__ void burgers_hF_kernel(const double* __restrict__ u, double* __restrict__ out, int nx, int ny,
-                                  double nu, double dx, double dy, double h) {
-    const long n = static_cast<long>(nx) * ny;
-    for (long t = blockIdx.x * static_cast<long>(blockDim.x) + threadIdx.x; t < n;
-         t += static_cast<long>(gridDim.x) * blockDim.x) {
-        const int i = static_cast<int>(t % nx), j = static_cast<int>(t / nx);
-        out[t] = h * burgers_F_at(u, i, j, nx, ny, nu, dx, dy);
+template <bool kRecip>
+__device__ __forceinline__ double second_differences(const BurgersSpacing& g, const double c, const double e,
+                                                     const double w, const double n, const double s) {
+    return quotient<kRecip>(e - 2.0 * c + w, g.xx, g.rxx) + quotient<kRecip>(n - 2.0 * c + s, g.yy, g.ryy);
+}
+
+template <bool kRecip>
+__device__ __forceinline__ double burgers_F(const BurgersSpacing& g, const double c, const double e, const double w,
+                                            const double n, const double s) {
+    const double lap = second_differences<kRecip>(g, c, e, w, n, s);
+    const double div = quotient<kRecip>(e * e - w * w, g.x2, g.rx2) + quotient<kRecip>(n * n - s * s, g.y2, g.ry2);
+    return g.nu * lap - 0.5 * div;
+}
+
+// This thread's column and rows: rows j0 .. j0 + kBurgersRows - 1 of column i,
+// with the columns beside it.
+struct BurgersLane {
+    int i, ie, iw, j0;
+    __device__ __forceinline__ BurgersLane(const int nx, const int block) {
+        i = static_cast<int>(blockIdx.x) * kBurgersTx + static_cast<int>(threadIdx.x);
+        ie = i + 1 < nx ? i + 1 : 0;
+        iw = i > 0 ? i - 1 : nx - 1;
+        j0 = (block * kBurgersTy + static_cast<int>(threadIdx.y)) * kBurgersRows;
+    }
+    // row j0 - 1 + r of an ny-row grid (r <= kBurgersRows + 1); past the last
+    // row that a stored point needs, some row of the grid
+    __device__ __forceinline__ long row(const int r, const int nx, const int ny) const {
+        int j = j0 - 1 + r;
+        if (j < 0) j = ny - 1;
+        if (j >= ny) j = j == ny ? 0 : ny - 1;
+        return static_cast<long>(j) * nx;
+    }
+};
+
+template <bool kRecip>
+__global__ __launch_bounds__(kBlockThreads) void burgers_hF_kernel(const double* __restrict__ u,
+                                                                   double* __restrict__ out, const int nx,
+                                                                   const int ny, const BurgersSpacing g,
+                                                                   const double h) {
+    for (int b = static_cast<int>(blockIdx.y); b * kBurgersTy * kBurgersRows < ny; b += static_cast<int>(gridDim.y)) {
+        const BurgersLane ln(nx, b);
+        if (ln.i >= nx || ln.j0 >= ny) return;
+        double c[kBurgersRows + 2], e[kBurgersRows], w[kBurgersRows];
+#pragma unroll
+        for (int r = 0; r < kBurgersRows + 2; ++r) {
+            const double* __restrict__ p = u + ln.row(r, nx, ny);
+            c[r] = p[ln.i];
+            if (r > 0 && r <= kBurgersRows) {
+                e[r - 1] = p[ln.ie];
+                w[r - 1] = p[ln.iw];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kBurgersRows; ++r)
+            if (ln.j0 + r < ny)
+                out[static_cast<long>(ln.j0 + r) * nx + ln.i] =
+                    h * burgers_F<kRecip>(g, c[r + 1], e[r], w[r], c[r + 2], c[r]);
     }
 }
 
 // R = h [N(u + a) - N(u)] with N(w) = F(w) - J(u) w, i.e.
 // h [F(w) - F(u) - J(u) a] for the stage w = u + a (formed here, as the
 // stage vector of the integrator)
-__global__ void burgers_remainder_kernel(const double* __restrict__ u, const double* __restrict__ a,
-                                         double* __restrict__ out, int nx, int ny, double nu, double dx,
-                                         double dy, double h) {
-    const long n = static_cast<long>(nx) * ny;
-    for (long t = blockIdx.x * static_cast<long>(blockDim.x) + threadIdx.x; t < n;
-         t += static_cast<long>(gridDim.x) * blockDim.x) {
-        const int i = static_cast<int>(t % nx), j = static_cast<int>(t / nx);
-        const int ie = (i + 1 == nx) ? 0 : i + 1, iw = (i == 0) ? nx - 1 : i - 1;
-        const int jn = (j + 1 == ny) ? 0 : j + 1, js = (j == 0) ? ny - 1 : j - 1;
-        const long ce = static_cast<long>(j) * nx + ie, cw = static_cast<long>(j) * nx + iw;
-        const long cn = static_cast<long>(jn) * nx + i, cs = static_cast<long>(js) * nx + i;
-        const double ac = a[t], ae = a[ce], aw = a[cw], an = a[cn], as = a[cs];
-        const double wc = u[t] + ac, we = u[ce] + ae, ww = u[cw] + aw, wn = u[cn] + an, ws = u[cs] + as;
-        const double lapw = (we - 2.0 * wc + ww) / (dx * dx) + (wn - 2.0 * wc + ws) / (dy * dy);
-        const double Fw = nu * lapw - 0.5 * ((we * we - ww * ww) / (2.0 * dx) + (wn * wn - ws * ws) / (2.0 * dy));
-        const double lapa = (ae - 2.0 * ac + aw) / (dx * dx) + (an - 2.0 * ac + as) / (dy * dy);
-        const double Ja = nu * lapa - ((u[ce] * ae - u[cw] * aw) / (2.0 * dx) + (u[cn] * an - u[cs] * as) / (2.0 * dy));
-        const double Fu = burgers_F_at(u, i, j, nx, ny, nu, dx, dy);
-        out[t] = h * (Fw - Fu - Ja);
+template <bool kRecip>
+__global__ __launch_bounds__(kBlockThreads) void burgers_remainder_kernel(
+    const double* __restrict__ u, const double* __restrict__ a, double* __restrict__ out, const int nx, const int ny,
+    const BurgersSpacing g, const double h) {
+    for (int b = static_cast<int>(blockIdx.y); b * kBurgersTy * kBurgersRows < ny; b += static_cast<int>(gridDim.y)) {
+        const BurgersLane ln(nx, b);
+        if (ln.i >= nx || ln.j0 >= ny) return;
+        double uc[kBurgersRows + 2], ue[kBurgersRows], uw[kBurgersRows];
+        double ac[kBurgersRows + 2], ae[kBurgersRows], aw[kBurgersRows];
+#pragma unroll
+        for (int r = 0; r < kBurgersRows + 2; ++r) {
+            const long row = ln.row(r, nx, ny);
+            uc[r] = u[row + ln.i];
+            ac[r] = a[row + ln.i];
+            if (r > 0 && r <= kBurgersRows) {
+                ue[r - 1] = u[row + ln.ie];
+                uw[r - 1] = u[row + ln.iw];
+                ae[r - 1] = a[row + ln.ie];
+                aw[r - 1] = a[row + ln.iw];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kBurgersRows; ++r) {
+            const double un = uc[r + 2], us = uc[r], an = ac[r + 2], as = ac[r];
+            const double Fw = burgers_F<kRecip>(g, uc[r + 1] + ac[r + 1], ue[r] + ae[r], uw[r] + aw[r], un + an, us + as);
+            const double Fu = burgers_F<kRecip>(g, uc[r + 1], ue[r], uw[r], un, us);
+            const double lapa = second_differences<kRecip>(g, ac[r + 1], ae[r], aw[r], an, as);
+            const double Ja = g.nu * lapa - (quotient<kRecip>(ue[r] * ae[r] - uw[r] * aw[r], g.x2, g.rx2) +
+                                             quotient<kRecip>(un * an - us * as, g.y2, g.ry2));
+            if (ln.j0 + r < ny) out[static_cast<long>(ln.j0 + r) * nx + ln.i] = h * (Fw - Fu - Ja);
+        }
     }
 }
 
@@ -413,17 +488,41 @@ hipError_t launch_to_fp32(const double* x, float* y, long n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// The spacings; false where a reciprocal would lose its accuracy (quotients are
+// then divided).
+static bool burgers_spacing(double nu, double dx, double dy, BurgersSpacing& g) {
+    g = BurgersSpacing{nu, dx * dx, dy * dy, 2.0 * dx, 2.0 * dy, 0.0, 0.0, 0.0, 0.0};
+    g.rxx = 1.0 / g.xx;
+    g.ryy = 1.0 / g.yy;
+    g.rx2 = 1.0 / g.x2;
+    g.ry2 = 1.0 / g.y2;
+    for (double v : {g.xx, g.yy, g.x2, g.y2})
+        if (!(v >= 1e-150 && v <= 1e150)) return false;
+    return true;
+}
+
+static dim3 burgers_blocks(int nx, int ny) {
+    constexpr int kRows = kBurgersTy * kBurgersRows;
+    return dim3((nx + kBurgersTx - 1) / kBurgersTx, std::min((ny + kRows - 1) / kRows, 65535));
+}
+
 hipError_t launch_burgers_hF(const double* u, double* out, int nx, int ny, double nu, double dx, double dy,
                              double h, hipStream_t s) {
-    hipLaunchKernelGGL(burgers_hF_kernel, dim3(flat_blocks(static_cast<long>(nx) * ny)), dim3(kBlockThreads), 0,
-                       s, u, out, nx, ny, nu, dx, dy, h);
+    BurgersSpacing g;
+    const bool recip = burgers_spacing(nu, dx, dy, g);
+    const dim3 grid = burgers_blocks(nx, ny), block(kBurgersTx, kBurgersTy);
+    if (recip) hipLaunchKernelGGL((burgers_hF_kernel<true>), grid, block, 0, s, u, out, nx, ny, g, h);
+    else hipLaunchKernelGGL((burgers_hF_kernel<false>), grid, block, 0, s, u, out, nx, ny, g, h);
     return hipGetLastError();
 }
 
 hipError_t launch_burgers_remainder(const double* u, const double* a, double* out, int nx, int ny, double nu,
                                     double dx, double dy, double h, hipStream_t s) {
-    hipLaunchKernelGGL(burgers_remainder_kernel, dim3(flat_blocks(static_cast<long>(nx) * ny)),
-                       dim3(kBlockThreads), 0, s, u, a, out, nx, ny, nu, dx, dy, h);
+    BurgersSpacing g;
+    const bool recip = burgers_spacing(nu, dx, dy, g);
+    const dim3 grid = burgers_blocks(nx, ny), block(kBurgersTx, kBurgersTy);
+    if (recip) hipLaunchKernelGGL((burgers_remainder_kernel<true>), grid, block, 0, s, u, a, out, nx, ny, g, h);
+    else hipLaunchKernelGGL((burgers_remainder_kernel<false>), grid, block, 0, s, u, a, out, nx, ny, g, h);
     return hipGetLastError();
 }
 
