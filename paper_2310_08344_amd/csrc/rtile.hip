@@ -358,8 +358,14 @@ __global__ __launch_bounds__(kRtThreads, kEu) void leja_rtile(SweepArgs a, const
         // unless the loop has ended.  Eight columns take 4 to 6 us, less than a
         // window; in launches of their own, 6 us for every second window, a
         // solve of 64 x 64 took 149 us, now 127 (333 x 250 197, now 167).
+        // One thread reads the end flag for all: workgroup 0 of this launch may
+        // set it meanwhile, and advance_columns has barriers.
         const int k = wg - a.nb;
-        if (L > 0 && __hip_atomic_load(&a.ctl->slot[2].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+        __shared__ int s_ended;
+        if (tid == 0)
+            s_ended = L > 0 && __hip_atomic_load(&a.ctl->slot[2].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_ended) return;
         advance_columns<false>(job.s[k], a.xi, job.state + static_cast<long>(k) * 2 * a.ld,
                                job.coef + static_cast<long>(k) * a.ld, a.ld, job.rows, job.j0, job.j1);
         return;
