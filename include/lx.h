@@ -99,7 +99,9 @@ typedef struct {
     int max_iters;      /* 1 .. LX_MAX_ITERS                                              */
     /* LX_FP32_SWEEP only: FP32 sweeps start after the first iteration at which
      * every unconverged output has |d_{m+1}| ||y_{m+1}|| <=
-     * fp32_switch * (rtol ||p|| + atol).  0 means FP32 from the first sweep.  */
+     * fp32_switch * (rtol ||p|| + atol).  0 means FP32 from the first sweep.
+     * (Windows by register marching, forced or tuned: after the first window
+     * at whose last iteration that holds and in which no output stopped.)     */
     double fp32_switch;
     /* Substeps s (not in the paper): the Leja loop loses accuracy once
      * alpha*h*gamma is large (it diverges near 800 on the diffusion-
@@ -121,7 +123,8 @@ typedef struct {
 typedef struct {
     int status;             /* lx_status of the call                          */
     int n_apply;            /* operator applications made                     */
-    int n_fp32;             /* of which in FP32 (LX_FP32_SWEEP)               */
+    int n_fp32;             /* of which in FP32 (LX_FP32_SWEEP); windows: those of
+                               the windows that end in FP32, counted whole   */
     int iters[LX_K_MAX];    /* per output: sweeps until it passed the test    */
     double err[LX_K_MAX];   /* per output: last error estimate                */
     double pnorm[LX_K_MAX]; /* per output: rms norm of the result             */
@@ -487,7 +490,8 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of
  * two iterations per launch, of windows of three to eight on LDS tiles and
  * by register marching (tile rows th or bands, workgroups), and, with any
- * nx, windows on register tiles.  It keeps the fastest
+ * nx, windows on register tiles (FP32 sweeps: where they cannot march).  It
+ * keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration
  * shape with its depth, and of the two the one with the lower time per
@@ -529,7 +533,8 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
  * shape forced, windows on register tiles (any nx and alignment, sides
  * beyond the halo of a window, FP32 sweeps too: 8 iterations for LX_OP_DIFFADV2D with K <= 3
  * and LX_OP_BURGERS2D with K <= 2, 6 for LX_OP_DIFFADV2D_UP3 with K = 1 in FP64) on
- * small and odd grids and by register marching on larger ones, else 2.
+ * small and odd grids and for FP32 sweeps, and by register marching on larger
+ * ones, else 2.
  * Automatic windows whose buffers cannot be allocated run as depth 2.
  * Depths 2..8 apply to grids with even nx and 16-byte aligned vectors; on
  * LDS tiles (FP64 sweeps) 3 and 4 to the diffusion-advection operators and

@@ -358,16 +358,17 @@ bool rtile_ok(const lx_operator& op, int depth) {
 // Beyond that marching in windows as deep as there are, except that the
 // Burgers Jacobian's windows of six need vectors beyond the Infinity Cache
 // (one output: 2048^2 11.4 against 10.0 with four, 4096^2 27.5 against 35.9),
-// where two outputs, which have no windows of six, and FP32 sweeps run on
-// register tiles again (4096^2 39.9 / 51.9; FP32, one output 26.6 / 28.5).  FP32
-// sweeps else as FP64 (Burgers 512^2 1.95 / 4.7, 1400^2 5.6 / 8.2; five-point
-// 1400^2 4.8 / 4.9, 2048^2 9.9 / 6.4; three outputs have no marching windows:
-// 4096^2 39, one iteration per launch 152).  Every odd grid runs on register tiles (its only
-// windows; 1201 x 1100 3.2, one iteration per launch 17.8).
+// where two outputs, which have no windows of six, run on register tiles
+// again (4096^2 39.9 / 51.9).  Every odd grid runs on register tiles (its only
+// windows; 1201 x 1100 3.2, one iteration per launch 17.8).  FP32 sweeps run on
+// register tiles at every size: marching windows go over to FP32 at a window's end
+// only, register tiles after the iteration that lx_leja_opts names, with the
+// bits of one iteration per launch (Burgers 512^2 1.95, marching 4.7; five-point
+// 2048^2 9.9, marching 6.4; 4096^2 with three outputs 39, one per launch 152).
 // Fills t and returns true, or returns false where windows do not apply.
 bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
     const long N = static_cast<long>(op.nx) * op.ny;
-    const bool even = vec2_ok && op.nx % 2 == 0;
+    const bool even = vec2_ok && op.nx % 2 == 0 && op.prec == LX_FP64;
     const int rd = lx::rtile_depth(opcode_of(op.kind), K);
     const bool burgers = op.kind == LX_OP_BURGERS2D;
     constexpr long M = 1L << 20, kBeyondCache = 8 * M;
@@ -376,7 +377,7 @@ bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
         if (burgers && d == 6 && N <= kBeyondCache) continue;
         if (sd == 0 && even && stream_ok(op, K, d)) sd = d;
     }
-    const bool small = N <= (burgers ? 3 * M : 2 * M) || (burgers && (K == 2 || op.prec != LX_FP64) && N > kBeyondCache);
+    const bool small = N <= (burgers ? 3 * M : 2 * M) || (burgers && K == 2 && N > kBeyondCache);
     if (rtile_ok(op, rd) && (sd == 0 || small)) {
         t.stream = 2;
         t.depth = rd;
@@ -2025,9 +2026,13 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
             }
         }
     }
-    // windows on register tiles (any nx)
+    // windows on register tiles (any nx); not beside the marching windows of
+    // FP32 sweeps, which go over to FP32 at another iteration (auto_windows), so
+    // that which of the two is timed faster does not show in a tuned call's results
     const int rd = lx::rtile_depth(opcode, K);
-    if (rtile_ok(*op, rd)) {
+    bool fp32_marching = false;
+    for (int depth : {4, 6, 8}) fp32_marching = fp32_marching || (fp32 && stream_ok(*op, K, depth));
+    if (rtile_ok(*op, rd) && !fp32_marching) {
         s = ensure_blk_ws(ctx, K);
         if (s != LX_OK) return cleanup(s);
         const lx::RtileGrid g = lx::rtile_grid(opcode, rd, nx, ny, nx % 2 == 0);

@@ -176,6 +176,30 @@ __device__ __forceinline__ void rt_level(const RtSten<T>& st, const T cc, P2<T> 
     }
 }
 
+// The same in FP32, of FP64 values that are FP32 ones.
+template <int OP, int RW>
+__device__ __forceinline__ void rt_level_fp32(const RtSten<float>& st, const float cc, double2 (&y)[RW],
+                                              const double2 (&up)[OP == kOpDiffAdv3 ? 2 : 1],
+                                              const double2 (&dn)[OP == kOpDiffAdv3 ? 2 : 1],
+                                              const double2 (&u)[OP == kOpBurgersJ ? RW + 2 : 1]) {
+    constexpr int R = OP == kOpDiffAdv3 ? 2 : 1, U = OP == kOpBurgersJ ? RW + 2 : 1;
+    P2<float> yf[RW], uf[U], upf[R], dnf[R];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) yf[r] = as_t2<float>(y[r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        upf[r] = as_t2<float>(up[r]);
+        dnf[r] = as_t2<float>(dn[r]);
+    }
+    if constexpr (OP == kOpBurgersJ) {
+#pragma unroll
+        for (int r = 0; r < U; ++r) uf[r] = as_t2<float>(u[r]);
+    }
+    rt_level<OP, RW, float>(st, cc, yf, upf, dnf, uf);
+#pragma unroll
+    for (int r = 0; r < RW; ++r) y[r] = as_d2<float>(yf[r]);
+}
+
 // A wavefront's first and last R rows of a level, for its neighbours in the
 // tile; two buffers, so one barrier per level is enough.
 template <int R, typename T = double>
@@ -214,8 +238,10 @@ __device__ __forceinline__ Sten sweep_sten(const SweepArgs& a) {
 // The tiles of this workgroup in a window launch, the levels in T (FP32 levels
 // of FP32 sweeps: the basis and the stencil arithmetic; outputs, terms and sums
 // stay FP64).  s_d[k][j] = d_{m+j} of output k (0 past its last term), s_cc[j-1]
-// the centre of level j.
-template <int OP, int K, int D, int RW, bool kVec, typename T>
+// the centre of level j.  kMixed (T FP64): the window that switches to FP32,
+// with the precisions of one iteration at a time: w.lev64 levels in FP64, the
+// next one formed in FP64 and rounded, the others in FP32.
+template <int OP, int K, int D, int RW, bool kVec, typename T, bool kMixed = false>
 __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K>& w, const Sten& sten, const int wg,
                                           const double (&s_d)[K][D + 1], const double (&s_cc)[D],
                                           RtExchange<radius<OP>(), T>& ex, double (&sy)[D], double (&sp)[K][D]) {
@@ -231,38 +257,11 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
         const bool outs = ln.any_out();
         P2<T> y[RW], u[OP == kOpBurgersJ ? RW + 2 : 1];
         double2 p[K][RW];
-        // where the levels are FP32, the p_0 = d_0 y_0 of a first window are formed
-        // here, from y_0 as stored; else once the first barrier has passed
-        constexpr bool kF = sizeof(T) == sizeof(float);
-        if constexpr (kF) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int r = 0; r < RW; ++r) p[k][r] = double2{0.0, 0.0};
-        }
+        constexpr bool kF = sizeof(T) == sizeof(float);   // never a first window: its y_0 is FP64
         if (w.jmax > 0) {
 #pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const long row = ln.row(r, nx, ny);
-                if constexpr (kF) {
-                    if (w.in32) {
-                        y[r] = rt_ld<kVec>(reinterpret_cast<const float*>(w.yin), row, ln.c0, ln.c1);
-                    } else {
-                        const double2 v = rt_ld<kVec>(w.yin, row, ln.c0, ln.c1);
-                        y[r] = as_t2<float>(v);
-                        if (first) {
-#pragma unroll
-                            for (int k = 0; k < K; ++k) {
-                                const double d0 = a.coef[k * a.ld + w.m];
-                                p[k][r].x = d0 * v.x;
-                                p[k][r].y = d0 * v.y;
-                            }
-                        }
-                    }
-                } else {
-                    y[r] = rt_ld<kVec>(w.yin, row, ln.c0, ln.c1);
-                }
-            }
+            for (int r = 0; r < RW; ++r)
+                y[r] = rt_ld<kVec>(reinterpret_cast<const T*>(w.yin), ln.row(r, nx, ny), ln.c0, ln.c1);
             if constexpr (OP == kOpBurgersJ) {
                 const T* __restrict__ us;
                 if constexpr (kF) us = a.u32;
@@ -278,7 +277,7 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
             const bool rd = outs && (w.nt[k] > 0 || w.copy[k]) && !(first && !w.copy[k]);
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
-                if (!kF || w.copy[k]) p[k][r] = double2{0.0, 0.0};
+                p[k][r] = double2{0.0, 0.0};
                 if (rd && ln.out_row(r) && (ln.o0 || ln.o1)) p[k][r] = rt_ld<kVec>(w.pin[k], ln.row(r, nx, ny), ln.c0, ln.c1);
             }
         }
@@ -305,7 +304,19 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
                     }
             }
             if (!ln.at_work(j * R)) continue;
-            rt_level<OP, RW, T>(st, static_cast<T>(s_cc[j - 1]), y, up, dn, u);
+            if (kMixed && j > w.lev64 + 1) {
+                if constexpr (kMixed)
+                    rt_level_fp32<OP, RW>(RtSten<float>(sten), static_cast<float>(s_cc[j - 1]), y, up, dn, u);
+            } else {
+                rt_level<OP, RW, T>(st, static_cast<T>(s_cc[j - 1]), y, up, dn, u);
+                if (kMixed && j == w.lev64 + 1) {
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) {
+                        y[r].x = static_cast<float>(y[r].x);
+                        y[r].y = static_cast<float>(y[r].y);
+                    }
+                }
+            }
             if (!outs) continue;
             double s = 0.0;
 #pragma unroll
@@ -335,7 +346,12 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
             for (int r = 0; r < RW; ++r) {
                 if (!ln.out_row(r)) continue;
                 const long row = ln.row(r, nx, ny);
-                if (store_y) rt_st<kVec>(reinterpret_cast<T*>(w.yout), row, ln.c0, ln.c1, ln.o0, ln.o1, y[r]);
+                if (store_y) {
+                    if constexpr (kMixed)
+                        rt_st<kVec>(reinterpret_cast<float*>(w.yout), row, ln.c0, ln.c1, ln.o0, ln.o1,
+                                    as_t2<float>(as_d2<T>(y[r])));
+                    else rt_st<kVec>(reinterpret_cast<T*>(w.yout), row, ln.c0, ln.c1, ln.o0, ln.o1, y[r]);
+                }
 #pragma unroll
                 for (int k = 0; k < K; ++k)
                     if (w.nt[k] > 0 || w.copy[k]) rt_st<kVec>(w.pout[k], row, ln.c0, ln.c1, ln.o0, ln.o1, p[k][r]);
@@ -345,7 +361,8 @@ __device__ __forceinline__ void rt_window(const SweepArgs& a, const WindowPlan<K
 }
 
 // Launch L of the window loop: a.tiles_x by a.tiles_y tiles, a.nb workgroups.
-// F32: FP32 sweeps (windows switch to FP32 levels on the device, window_enter).
+// F32: FP32 sweeps (the switch to FP32 levels is decided on the device, and
+// falls on the same iteration as one at a time; window_enter).
 template <int OP, int K, int D, int RW, bool kVec, bool F32, int kEu>
 __global__ __launch_bounds__(kRtThreads, kEu) void leja_rtile(SweepArgs a, const int L, const CoefJob job) {
     constexpr int R = radius<OP>(), H = D * R;
@@ -371,7 +388,7 @@ __global__ __launch_bounds__(kRtThreads, kEu) void leja_rtile(SweepArgs a, const
         return;
     }
     WindowPlan<K> w;
-    if (!window_enter<OP, K, D, true, F32, kRtWaves>(a, L, wg, nullptr, w)) return;
+    if (!window_enter<OP, K, D, true, F32, kRtWaves, F32>(a, L, wg, nullptr, w)) return;
     const Sten st = sweep_sten<OP>(a);
     if (tid < 64 * K && (tid & 63) <= D) {
         const int k = tid >> 6, j = tid & 63;
@@ -395,8 +412,10 @@ __global__ __launch_bounds__(kRtThreads, kEu) void leja_rtile(SweepArgs a, const
     }
     if constexpr (F32) {
         if (w.win32) {
-            rt_window<OP, K, D, RW, kVec, float>(a, w, st, wg, s_d, s_cc,
-                                                 reinterpret_cast<RtExchange<R, float>&>(ex), sy, sp);
+            if (w.in32)
+                rt_window<OP, K, D, RW, kVec, float>(a, w, st, wg, s_d, s_cc,
+                                                     reinterpret_cast<RtExchange<R, float>&>(ex), sy, sp);
+            else rt_window<OP, K, D, RW, kVec, double, true>(a, w, st, wg, s_d, s_cc, ex, sy, sp);
             window_exit<K, D, kRtWaves>(a, L, wg, sy, sp);
             return;
         }

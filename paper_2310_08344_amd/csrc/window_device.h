@@ -41,6 +41,7 @@ struct WindowVerdict {
     bool stop[K];
     int j[K];
     double err[K], pnorm[K], ynorm;
+    int fp32_after;   // kSwitch: the first term after which FP32 sweeps start (D: with the next window), 0: none
 };
 
 // Applies the stop rule at the terms m+1 .. m+D of a window, one lane per
@@ -49,7 +50,11 @@ struct WindowVerdict {
 // j = 1, 2, .. until it stops (its estimate passes, or m + j reaches
 // max_iters); a non-finite norm or estimate at a tested term ends the loop.
 // Every lane of the wavefront must be active; all receive the verdict.
-template <int K, int D>
+//
+// kSwitch: also the term after which FP32 sweeps start, as the one-iteration
+// loop finds it: the first at which some output goes on and every one that
+// does has |d| ||y|| <= fp32_switch * (rtol ||p|| + atol).
+template <int K, int D, bool kSwitch = false>
 __device__ __forceinline__ WindowVerdict<K> window_verdict(const LoopCtl& ctl, const int m, const int (&active)[K],
                                                            const double norm, const double coef) {
     constexpr int R = 1 + K;
@@ -84,6 +89,26 @@ __device__ __forceinline__ WindowVerdict<K> window_verdict(const LoopCtl& ctl, c
         }
     }
     v.ynorm = __shfl(norm, last > 0 ? (last - 1) * R : 0, 64);
+    v.fp32_after = 0;
+    if constexpr (kSwitch) {
+        const unsigned long long b_small =
+            __ballot(live && fin && ctl.fp32_switch >= 0.0 && e <= ctl.fp32_switch * thr);
+        bool ended = false;   // a non-finite value at a tested term
+#pragma unroll
+        for (int i = 1; i <= D; ++i) {
+            bool goes_on = false, small = true;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (!active[k]) continue;
+                const int q = (i - 1) * R + 1 + k;
+                if (v.j[k] >= i && ((b_bad >> q) & 1) != 0) ended = true;
+                if (v.stop[k] && v.j[k] <= i) continue;
+                goes_on = true;
+                if (((b_small >> q) & 1) == 0) small = false;
+            }
+            if (v.fp32_after == 0 && !ended && goes_on && small) v.fp32_after = i;
+        }
+    }
     return v;
 }
 
@@ -95,7 +120,12 @@ __device__ __forceinline__ WindowVerdict<K> window_verdict(const LoopCtl& ctl, c
 // still iterating has |d| ||y|| <= fp32_switch * (rtol ||p|| + atol); from
 // then on every window does.  in32: the window's y_m is stored in FP32.  A
 // re-execution keeps the precision of the window it repeats.
-template <int K, int D, bool kFp32 = false>
+//
+// kSwitch: FP32 sweeps start after the very term (fp32_after) at which they
+// do one iteration at a time.  Where that is not the window's last, the
+// window is formed again with lev64 levels in FP64 and the others in FP32,
+// and its stops are taken from that.
+template <int K, int D, bool kFp32 = false, bool kSwitch = false>
 __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const SweepState& prev,
                                                    const WindowVerdict<K>& v) {
     SweepState nx = prev;
@@ -105,6 +135,10 @@ __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const Swe
         nx.blk_mode = 0;
         nx.iter = prev.iter + D;
         nx.in32 = prev.out32;
+        if (kSwitch && prev.switch_next) {
+            nx.out32 = 1;
+            nx.lev64 = nx.switch_next = 0;
+        }
         bool any = false;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -116,6 +150,12 @@ __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const Swe
         return nx;
     }
     const int m = prev.iter;
+    const int after = kSwitch && !prev.out32 ? v.fp32_after : 0;
+    if (after > 0 && after < D) {
+        nx.out32 = 1;
+        nx.lev64 = after;
+        return nx;
+    }
     bool any_active = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -138,10 +178,15 @@ __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const Swe
 #pragma unroll
         for (int k = 0; k < K; ++k) nx.nt[k] = !prev.active[k] ? 0 : (v.stop[k] ? -v.j[k] : D);
         if (v.capped) nx.status = 3;   // LX_ENOTCONV
+        nx.switch_next = after == D ? 1 : 0;
     } else {
         nx.iter = m + D;
         nx.in32 = prev.out32;
-        if (kFp32 && !prev.out32 && ctl.fp32_switch >= 0.0) {
+        if (after == D) {
+            nx.out32 = 1;
+            nx.lev64 = 0;
+        }
+        if (kFp32 && !kSwitch && !prev.out32 && ctl.fp32_switch >= 0.0) {
             bool small = true;
 #pragma unroll
             for (int k = 0; k < K; ++k)
@@ -163,6 +208,7 @@ struct WindowPlan {
     int nt[K];              // terms each output takes in this launch
     int jmax;               // levels this launch forms
     bool win32;             // levels formed, and y_{m+D} written, in FP32
+    int lev64;              // kSwitch, win32 and not in32: but for the first lev64 (the next is formed in FP64 and rounded)
     bool in32;              // y_m is stored in FP32
     bool copy[K];           // a re-execution copies this output unchanged (pin to pout)
     const double* pin[K];   // outputs as the window finds them
@@ -194,7 +240,8 @@ struct WindowPlan {
 // y_{m+D} to ybuf[w & 1]; it reads the outputs from p (w even) or p2 (w odd)
 // and writes them to the other; a re-execution writes stopped outputs to p,
 // the caller's buffer, so every final result lands there.
-template <int OP, int K, int D, bool kEndCopy = false, bool kFp32 = false, int NW = kBlockThreads / 64>
+template <int OP, int K, int D, bool kEndCopy = false, bool kFp32 = false, int NW = kBlockThreads / 64,
+          bool kSwitch = false>
 __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, const int wg, unsigned* done,
                                              WindowPlan<K>& w) {
     LoopCtl* __restrict__ ctl = gptr(a.ctl);
@@ -214,7 +261,7 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
             if (!kFp32) st.out32 = 0;
             st.n_fp32 = st.out32 ? D : 0;
             // v in, y_D out, the Burgers state, each output written
-            double b = 8.0 + (st.out32 ? 4.0 : 8.0) + (OP == kOpBurgersJ ? (st.out32 ? 4.0 : 8.0) : 0.0);
+            double b = 8.0 + (st.out32 ? 4.0 : 8.0) + (OP == kOpBurgersJ ? (st.out32 && !kSwitch ? 4.0 : 8.0) : 0.0);
             for (int k = 0; k < K; ++k) b += st.nt[k] ? 8.0 : 0.0;
             st.bytes_pp = b;
             s_cur = st;
@@ -238,9 +285,9 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
         const double tot = record_totals<NV, NW>(gptr(a.partials) + static_cast<long>((L - 1) & 1) * a.nb * NV, a.nb);
         if (tid < 64) {
             const double norm = lane < NV ? sqrt(tot) * a.inv_sqrtN : 0.0;
-            const WindowVerdict<K> v = window_verdict<K, D>(*ctl, m, active, norm, cf);
+            const WindowVerdict<K> v = window_verdict<K, D, kSwitch>(*ctl, m, active, norm, cf);
             if (tid == 0) {
-                SweepState st = block_decide<K, D, kFp32>(*ctl, *ps, v);
+                SweepState st = block_decide<K, D, kFp32, kSwitch>(*ctl, *ps, v);
                 if (ended) st.done = 1;
                 if (!st.done) {
                     // algorithmic bytes per point: y in (and out, unless a
@@ -258,7 +305,8 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
                     }
                     // y in (and out), and u, when levels are formed
                     const double yb = st.in32 ? 4.0 : 8.0, ob = st.out32 ? 4.0 : 8.0;
-                    if (!rd || lev > 0) b += yb + (rd ? 0.0 : ob) + (OP == kOpBurgersJ ? ob : 0.0);
+                    const double ub = kSwitch && !st.in32 ? 8.0 : ob;
+                    if (!rd || lev > 0) b += yb + (rd ? 0.0 : ob) + (OP == kOpBurgersJ ? ub : 0.0);
                     st.bytes_pp += b;
                     st.n_levels += lev;
                     if (!rd && st.out32) st.n_fp32 += D;
@@ -282,6 +330,7 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
     w.redo = __builtin_amdgcn_readfirstlane(s_cur.blk_mode) == 1;
     w.win32 = kFp32 && __builtin_amdgcn_readfirstlane(s_cur.out32) != 0;
     w.in32 = kFp32 && __builtin_amdgcn_readfirstlane(s_cur.in32) != 0;
+    w.lev64 = kSwitch ? __builtin_amdgcn_readfirstlane(s_cur.lev64) : 0;
     // terms each output takes in this launch.  A re-execution recomputes
     // only the outputs that stopped (their final buffer is p); the others,
     // and y_{m+D}, the window already wrote exactly.
