@@ -88,10 +88,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // Power launch b of the diffusion-advection instances (power_stream's
-// arithmetic): nlev levels of A, scaled by the norm of the prev levels of
-// launch b - 1.  Launch 0 scales a given start vector by its norm
+// arithmetic): nlev levels of 2^e A (power_exponent: levels of an operator of
+// any size stay in range), scaled by the norm of the prev levels of launch
+// b - 1.  Launch 0 scales a given start vector by its norm
 // (batch_power_norm_kernel) and takes the library's own as it is: its values
-// lie in [-1, 1), so its squared norm keeps the margin the host leaves.
+// lie in [-1, 1).
 // Partial sums in the instance's record: the start vector's norm at [nb + j],
 // launch b's at [2 nb + (b & 1) nb DP + j DP].
 template <int DP>
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(kBlockThreads) void batch_power_stream_final_kernel
             if (j == nlev - 1) last = tot[j];
             if (j == nlev - 2) prev = tot[j];
         }
-        const double rho = sqrt(last / prev);
+        const double rho = sqrt(last / prev) * I.pscale;
         const double lam = -safety * rho;
         I.rho = rho;
         I.c = lam / 2.0;

@@ -289,7 +289,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     std::vector<BatchInst> hi(static_cast<size_t>(n));
     std::vector<int> budget(static_cast<size_t>(n));
     int total_blocks = 0, max_budget = 1;
-    int power_per = lx::kPowerStreamDepth;   // sweeps per marching power launch
+    constexpr int kPowerPer = lx::kPowerStreamDepth;   // sweeps per marching power launch
     long part_total = 0;
     size_t basis_total = 0;
     for (int i = 0; i < n; ++i) {
@@ -367,11 +367,11 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
         const int sk = b.kind == lx::kOpDiffAdv ? 0 : 1;
         lx::stencil_coeffs(sk, b.dx, b.dy, b.D, b.vx, b.vy, b.nu, 0.0, 1.0, b.pw);
         if (march && sk == 0) {
-            // the levels of an unnormalised power launch grow at most like the
-            // Gershgorin bound: their squares stay below 1e300 (x0 as in lx_spectrum)
             const double g = std::fabs(b.pw[0]) + std::fabs(b.pw[1]) + std::fabs(b.pw[2]) + std::fabs(b.pw[3]) +
                              std::fabs(b.pw[4]);
-            if (g > 10.0) power_per = std::max(1, std::min(power_per, static_cast<int>(140.0 / std::log10(g))));
+            const int e = lx::power_exponent(g);
+            for (double& w : b.pw) w = std::ldexp(w, e);
+            b.pscale = std::ldexp(1.0, -e);
         }
         if (power_iters == 0) lx::stencil_coeffs(sk, b.dx, b.dy, b.D, b.vx, b.vy, b.nu, b.c, b.gamma, b.st);
         b.u = q.op.kind == LX_OP_BURGERS2D ? q.d_u : nullptr;
@@ -468,10 +468,10 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
                 e = lx::launch_batch_power_norm(d_inst, W.d_block_inst, total_blocks, W.d_partials,
                                                 march && !scale_own, q);
             if (march && any_diffadv) {
-                const int nblk = (power_iters + power_per - 1) / power_per;
-                int prev = power_per;
+                const int nblk = (power_iters + kPowerPer - 1) / kPowerPer;
+                int prev = kPowerPer;
                 for (int b = 0; b < nblk && e == hipSuccess; ++b) {
-                    const int nlev = b == nblk - 1 ? power_iters - power_per * (nblk - 1) : power_per;
+                    const int nlev = b == nblk - 1 ? power_iters - kPowerPer * (nblk - 1) : kPowerPer;
                     e = lx::launch_batch_power_stream(d_inst, W.d_block_inst, total_blocks, W.d_partials, b, nlev, prev,
                                                       scale_own, q);
                     prev = nlev;
@@ -523,7 +523,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
     };
     // what a captured pipeline bakes in: sizes, launch shape and addresses
     std::vector<long long> key{n, total_blocks, blk ? 1 : 0, pair ? 1 : 0, th, any_burgers ? 1 : 0, power_iters,
-                               ld, static_cast<long long>(ppw), da, db, any_diffadv ? 1 : 0, power_per};
+                               ld, static_cast<long long>(ppw), da, db, any_diffadv ? 1 : 0};
     {
         long long sb;
         std::memcpy(&sb, &safety, sizeof(sb));
@@ -629,7 +629,7 @@ extern "C" lx_status lx_phi_leja_batched(lx_ctx* ctx, int n, const lx_instance* 
             bytes += N * ((24.0 + ub) + (32.0 + ub) * std::max(f.iter - 1, 0));
             max_iter = std::max(max_iter, f.iter);
         }
-        const int sweeps = march && b.kind == lx::kOpDiffAdv ? (power_iters + power_per - 1) / power_per : power_iters;
+        const int sweeps = march && b.kind == lx::kOpDiffAdv ? (power_iters + kPowerPer - 1) / kPowerPer : power_iters;
         bytes += N * (16.0 + ub) * sweeps;   // a marching launch reads and writes once for its sweeps
     }
     S.n_apply = max_iter;

@@ -149,7 +149,8 @@ struct BatchInst {
     long part_off;           // offset of its partial sums: [2][nb][2]
     double dx, dy, D, vx, vy, nu;
     double h, c, gamma, rho;
-    double pw[5];            // stencil of A (power iteration), from the host
+    double pw[5];            // stencil of A (power iteration), from the host; by register marching, of 2^e A
+    double pscale;           // register marching: 2^-e, which takes the estimate back to A's
     double st[5];            // stencil of (A - c)/gamma (Leja sweeps), host or batched power iteration
     const double* u;
     const double* v;

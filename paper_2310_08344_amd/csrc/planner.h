@@ -1,9 +1,22 @@
 // Host planner of the Leja phi-action library (plain C++, no HIP).
 #pragma once
 
+#include <cmath>
+
 namespace lx {
 
 constexpr int kMaxPoints = 1024;   // LX_MAX_ITERS + 24: windows of D iterations read up to d_{max_iters+D}
+
+// The power of two 2^e that brings the Gershgorin bound g of an operator into
+// [1/2, 1).  Several sweeps of power iteration without a normalisation between
+// them grow or shrink the vector like powers of the operator; scaled by 2^e
+// they stay in range for operators of any size, and as the scaling is exact,
+// the estimate, scaled back by 2^-e, has the same bits.
+inline int power_exponent(double g) {
+    if (!(g > 0.0) || !std::isfinite(g)) return 0;
+    const int e = -std::ilogb(g) - 1;
+    return e < -1022 ? -1022 : e;
+}
 
 // phi_l(z) for real z (Sec. 1 recursion; Taylor series near 0).
 double phi_scalar(int l, double z);
