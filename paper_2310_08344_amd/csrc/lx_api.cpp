@@ -969,27 +969,29 @@ lx_status run_leja_sub(lx_ctx* ctx, const LejaCall& q) {
 
 // Power iteration by register marching (power_stream: up to
 // kPowerStreamDepth sweeps per launch) or on register tiles (power_rtile:
-// rtile_power_depth), normalised at launch boundaries.  The unnormalised
-// levels grow at most like the Gershgorin bound g of A (the start of a launch
-// has norm 1), so a launch makes at most 140 / log10(g) levels: their squares
-// stay below 1e280 (below 1e300 for a first launch that takes x0 unscaled
-// with ||x0||^2 <= 1e20).  The bound of a Burgers Jacobian is not known to the
-// host: for register tiles the caller looks at the result (kRtileRho).
+// rtile_power_depth), normalised at launch boundaries.  Diffusion-advection
+// operators are scaled to a Gershgorin bound in [1/2, 1) (power_exponent), so
+// that a launch's unnormalised levels (the start of a launch has norm 1, a first
+// launch may take x0 unscaled with ||x0||^2 in [1e-200, 1e20]) stay in range.
+// The bound of a Burgers Jacobian is not known to the host: the caller looks at
+// the result (kRtileRho).
 lx_status spectrum_deep(lx_ctx* ctx, const lx_operator& op, const double* u, const double* x0, int iters,
                         double safety, bool tiles, bool vec, double* rho_hat, double* c, double* gamma) {
     const int opcode = opcode_of(op.kind);
-    const int DP = tiles ? lx::rtile_power_depth(opcode) : lx::kPowerStreamDepth;
+    const int per = tiles ? lx::rtile_power_depth(opcode) : lx::kPowerStreamDepth;
     const int nx = op.nx, ny = op.ny;
     const long N = static_cast<long>(nx) * ny;
     PowerArgs a{};
     a.nx = nx;
     a.ny = ny;
     a.u = u;
-    double g = 0.0;
+    int e = 0;   // 2^e A
     if (is_diffadv(op.kind)) {
-        double pk[9];
+        double pk[9], g = 0.0;
         diffadv_stencil9(op, 0.0, 1.0, pk);
         for (double v : pk) g += std::fabs(v);
+        e = lx::power_exponent(g);
+        for (double& v : pk) v = std::ldexp(v, e);
         a.cE = pk[0];
         a.cW = pk[1];
         a.cN = pk[2];
@@ -1007,22 +1009,20 @@ lx_status spectrum_deep(lx_ctx* ctx, const lx_operator& op, const double* u, con
         a.gx = pk[2];
         a.gy = pk[3];
     }
-    const int cap = g > 10.0 ? static_cast<int>(140.0 / std::log10(g)) : DP;
-    const int per = std::max(1, std::min(DP, cap));
     int rw = 0;
     if (tiles) {
-        const lx::RtileGrid rg = lx::rtile_grid(opcode, DP, nx, ny, vec);
+        const lx::RtileGrid rg = lx::rtile_grid(opcode, per, nx, ny, vec);
         a.tiles_x = rg.tiles_x;
         a.tiles_y = rg.tiles_y;
         a.nb = rg.nb;
         rw = rg.rw;
     } else {
-        const StreamGrid sg = stream_grid(lx::kOpDiffAdv, false, nx, ny, 1, DP, 0, 0, true);
+        const StreamGrid sg = stream_grid(lx::kOpDiffAdv, false, nx, ny, 1, per, 0, 0, true);
         a.tiles_x = sg.strips;
         a.tiles_y = sg.bands;
         a.nb = sg.nb;
     }
-    lx_status s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb) * (1 + DP));
+    lx_status s = ensure_partials(ctx, 2 * static_cast<size_t>(a.nb) * (1 + per));
     if (s != LX_OK) return s;
     a.partials = ctx->partials;
     a.rho = ctx->h_rho;
@@ -1032,7 +1032,7 @@ lx_status spectrum_deep(lx_ctx* ctx, const lx_operator& op, const double* u, con
         if (s != LX_OK) return s;
     }
     // raw: the first launch takes x0 unscaled and measures its norm itself
-    // (when it makes a full DP levels); a NaN estimate from it means that
+    // (marching: when it makes a full per levels); a NaN estimate from it means that
     // ||x0|| lay outside the range where that is safe, and the iteration
     // runs again with x0 scaled first
     double rho = 0.0;
@@ -1054,13 +1054,14 @@ lx_status spectrum_deep(lx_ctx* ctx, const lx_operator& op, const double* u, con
                           : lx::launch_power_stream_final(a, nblk - 1, nlev, raw, ctx->stream));
         return wait_rho(ctx, &rho);
     };
-    const bool raw = tiles || (per == DP && iters >= DP);
+    const bool raw = tiles || iters >= per;
     s = run(raw);
     if (s != LX_OK) return s;
-    if (raw && !std::isfinite(rho)) {
+    if (raw && !std::isfinite(rho) && x0 != ctx->ybuf[1]) {   // the library's own start vector lies in that range
         s = run(false);
         if (s != LX_OK) return s;
     }
+    rho = std::ldexp(rho, -e);
     lx_stats& S = ctx->stats;
     S.n_apply = iters;
     S.n_launch = nblk;
@@ -1244,8 +1245,8 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         x0 = ctx->ybuf[1];
     }
     const bool vec2 = aligned16(x0) && (d_u == nullptr || aligned16(d_u));
-    // register tiles (odd grids: of the diffusion-advection operators); an estimate outside kRtileRho, where a
-    // launch's unnormalised levels could lose range, is formed again below
+    // register tiles (odd grids: of the diffusion-advection operators); a Burgers estimate outside kRtileRho, where
+    // a launch's unnormalised levels could lose range, is formed again below
     const bool vec_rt = vec2 && nx % 2 == 0;
     lx_operator op64 = *op;
     op64.prec = LX_FP64;
@@ -1253,7 +1254,7 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u, con
         (vec_rt ? op->kind != LX_OP_DIFFADV2D || N <= kRtilePowerPoints : is_diffadv(op->kind))) {
         double rho = 0.0;
         s = spectrum_deep(ctx, *op, d_u, x0, iters, safety, true, vec_rt, &rho, c, gamma);
-        if (s == LX_OK && rho >= kRtileRhoMin && rho <= kRtileRhoMax) {
+        if (s == LX_OK && (is_diffadv(op->kind) || (rho >= kRtileRhoMin && rho <= kRtileRhoMax))) {
             if (rho_hat) *rho_hat = rho;
             return LX_OK;
         }

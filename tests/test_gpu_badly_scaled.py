@@ -3,9 +3,10 @@ normalisation between them must not leave the range of a double."""
 import numpy as np
 import pytest
 
+from oracle.operators import diffadv_apply
 from oracle.phi_action import leja_phi, power_iteration, shift_scale
 from paper_2310_08344_amd import binding as B
-from tests.gpu_helpers import oracle_parity, say
+from tests.gpu_helpers import dev, diffadv_setup, oracle_parity, say
 from tests.test_gpu_batch import _mixed_batch, _run, splitmix_vector
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +44,24 @@ def test_marching_batch_of_badly_scaled_operators(ctx, scale):
         oracle_parity([o], [r["iters"]],
                       lambda f, q=q: leja_phi(q["A"], q["v"], [(q["l"], 1.0, 1.0)], q["h"], c, g, 1e-9, 0.0, 400, f),
                       PARITY)
+
+
+@pytest.mark.parametrize("scale", [1e-150, 1e-56, 1e-20, 1e30, 1e100])
+@pytest.mark.parametrize("nx,ny,march", [(64, 48, False), (65, 48, False), (64, 48, True), (2048, 700, False)])
+@pytest.mark.parametrize("given", [True, False])
+def test_spectrum_of_badly_scaled_operators(lx, nx, ny, march, scale, given):
+    """Even and odd grids, on register tiles and by marching (forced, and the
+    automatic choice of a grid this large)."""
+    rng = np.random.default_rng(11)
+    prm, _ = diffadv_setup(nx, ny, vx=0.7 * nx, vy=-0.4 * ny)
+    op = B.make_operator(kind=B.LX_OP_DIFFADV2D, nx=nx, ny=ny, dx=prm["dx"], dy=prm["dy"], D=prm["D"] * scale,
+                         vx=prm["vx"] * scale, vy=prm["vy"] * scale)
+    x0 = rng.standard_normal((ny, nx)) if given else splitmix_vector(0, nx * ny).reshape(ny, nx)
+    rho_o, _ = power_iteration(lambda y: diffadv_apply(y, prm["D"], prm["vx"], prm["vy"], prm["dx"], prm["dy"]), x0, 20)
+    say("badly scaled spectrum", nx, ny, march, scale, given)
+    with lx.context(n_max=nx * ny, k_max=1) as c:
+        if march:
+            c.set_window_kernel(2)
+        rho, _, _ = c.spectrum(op, x0=dev(x0) if given else None, iters=20)
+        assert c.stats()["marching"] == int(march or nx == 2048)
+    assert abs(rho - rho_o * scale) <= 1e-12 * rho_o * scale
