@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kBlockThreads) void leja_sweep(SweepArgs a, const i
     constexpr int NV = 1 + K;
     __shared__ SweepState s_cur;
     const int tid = flat_tid();
-    if (blockIdx.x == 0 && tid == 0) report_progress(a.progress, m);
+    if (blockIdx.x == 0 && tid == 0) report_progress(a, m);
     if (m == 0) {
         if (tid == 0) s_cur = ctl->slot[0];
     } else {

@@ -537,7 +537,6 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     // the launch that ends the loop writes its final state here (pinned)
     volatile SweepState* pub = ctx->h_poll;
     pub->done = 0;
-    *ctx->h_progress = 0;
     // the coefficients' first launch also writes the loop's initial state
     lx::CoefArgs ca{};
     ca.K = K;
@@ -613,6 +612,7 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     a.ctl = ctx->ctl;
     a.pub = ctx->h_poll;
     a.progress = ctx->h_progress;
+    a.progress_base = ctx->progress_next;
     const int opcode = opcode_of(op.kind);
     const size_t need_partials = 2 * static_cast<size_t>(a.nb) * (1 + K) * (blk ? D : (pair ? 2 : 1));
     if (q.scratch != nullptr) {
@@ -649,12 +649,14 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     // says so in pinned memory), so that the queue never runs dry and at
     // most `ahead` launches run past the end of the loop.
     const int ahead = blk ? 3 : 4;
-    volatile int* progress = ctx->h_progress;
+    ctx->progress_next += static_cast<unsigned>(last) + 2u;
+    volatile unsigned* progress = ctx->h_progress;
+    auto room = [&](int launched) { return launched < lx::launches_started(*progress, a.progress_base) + ahead; };
     int launched = 0;
     bool idle = false;
     while (!pub->done && !idle) {
         const bool more = launched <= last;
-        if (more && launched < *progress + ahead) {
+        if (more && room(launched)) {
             const int L = launched;
             s = ensure_coeffs(coeffs_for(L + 1));
             if (s != LX_OK) return s;
@@ -680,7 +682,7 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
             ++launched;
             continue;
         }
-        s = wait_for(ctx, [&] { return pub->done != 0 || (more && launched < *progress + ahead); }, &idle);
+        s = wait_for(ctx, [&] { return pub->done != 0 || (more && room(launched)); }, &idle);
         if (s != LX_OK) return s;
     }
     // Once the final state is published, every launch that writes an output
@@ -1183,7 +1185,7 @@ lx_status lx_create(lx_ctx** out, size_t n_max, int k_max, void* stream) {
     const size_t d_ctl = place(dev_bytes, sizeof(LoopCtl)), d_coef = place(dev_bytes, kTable * k_max),
                  d_state = place(dev_bytes, kTable * k_max * 2), d_xi = place(dev_bytes, kTable);
     const size_t p_ctl = place(pin_bytes, sizeof(LoopCtl)), p_poll = place(pin_bytes, sizeof(SweepState)),
-                 p_progress = place(pin_bytes, sizeof(int)), p_rho = place(pin_bytes, sizeof(lx::RhoRecord)),
+                 p_progress = place(pin_bytes, sizeof(unsigned)), p_rho = place(pin_bytes, sizeof(lx::RhoRecord)),
                  p_coef = place(pin_bytes, kTable * k_max), p_xi = place(pin_bytes, kTable);
     if (hipMalloc(&ctx->small_mem, dev_bytes) != hipSuccess) return bail(LX_ENOMEM);
     if (hipHostMalloc(reinterpret_cast<void**>(&ctx->pinned_mem), pin_bytes, hipHostMallocDefault) != hipSuccess)
@@ -1194,7 +1196,7 @@ lx_status lx_create(lx_ctx** out, size_t n_max, int k_max, void* stream) {
     ctx->xi = reinterpret_cast<double*>(ctx->small_mem + d_xi);
     ctx->h_ctl = reinterpret_cast<LoopCtl*>(ctx->pinned_mem + p_ctl);
     ctx->h_poll = reinterpret_cast<SweepState*>(ctx->pinned_mem + p_poll);
-    ctx->h_progress = reinterpret_cast<int*>(ctx->pinned_mem + p_progress);
+    ctx->h_progress = reinterpret_cast<unsigned*>(ctx->pinned_mem + p_progress);
     ctx->h_rho = reinterpret_cast<lx::RhoRecord*>(ctx->pinned_mem + p_rho);
     ctx->h_coef = reinterpret_cast<double*>(ctx->pinned_mem + p_coef);
     ctx->h_xi = reinterpret_cast<double*>(ctx->pinned_mem + p_xi);

@@ -76,7 +76,8 @@ struct lx_ctx {
     lx::LoopCtl* h_ctl = nullptr;           // initial loop control (pinned)
     // what running kernels write to the host (pinned)
     lx::SweepState* h_poll = nullptr;       // a Leja loop's final state
-    int* h_progress = nullptr;              // the launches of a Leja loop that have started
+    unsigned* h_progress = nullptr;         // the launches of Leja loops that have started (launches_started)
+    unsigned progress_next = 0;             // the next loop's base
     lx::RhoRecord* h_rho = nullptr;         // a power iteration's result
     double* h_coef = nullptr;
     double* h_xi = nullptr;

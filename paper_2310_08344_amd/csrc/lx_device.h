@@ -111,7 +111,8 @@ struct SweepArgs {
     double* partials;        // [2][nb][1+K]
     LoopCtl* ctl;
     SweepState* pub;         // host-visible copy of the final state (pinned host memory), or NULL
-    int* progress;           // pinned: launch L stores L + 1 as it starts working; or NULL
+    unsigned* progress;      // pinned: launch L stores progress_base + L + 1 as it starts; or NULL
+    unsigned progress_base;
 };
 
 struct PowerArgs {

@@ -281,7 +281,7 @@ __device__ __forceinline__ void pair_launch(const SweepArgs& a, const int L, con
     __shared__ int s_add0[K], s_add1[K];
     const int tid = flat_tid();
     const int m = 2 * L;
-    if (wg == 0 && tid == 0) report_progress(a.progress, L);
+    if (wg == 0 && tid == 0) report_progress(a, L);
     if (L == 0) {
         if (tid == 0) {
             s_mode = 0;

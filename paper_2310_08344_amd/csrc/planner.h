@@ -18,6 +18,15 @@ inline int power_exponent(double g) {
     return e < -1022 ? -1022 : e;
 }
 
+// The launches of a loop that have started, by its progress word: launch L of
+// the loop that was given `base` stores base + L + 1, and every later loop gets
+// a base beyond those.  A launch that an earlier loop left on the stream may
+// still store its own number: that counts as none.
+inline int launches_started(unsigned word, unsigned base) {
+    const int n = static_cast<int>(word - base);
+    return n > 0 ? n : 0;
+}
+
 // phi_l(z) for real z (Sec. 1 recursion; Taylor series near 0).
 double phi_scalar(int l, double z);
 

@@ -242,10 +242,12 @@ __device__ __forceinline__ void publish_final(LoopCtl* ctl, SweepState* pub, con
 }
 
 // Launch L of a loop has started: every launch before it is complete.  The
-// host reads this to keep a few launches queued without an event between
-// them (an event's marker costs the stream 6 us).
-__device__ __forceinline__ void report_progress(int* progress, const int L) {
-    if (progress != nullptr) __hip_atomic_store(progress, L + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+// host reads this (launches_started) to keep a few launches queued without an
+// event between them (an event's marker costs the stream 6 us).
+__device__ __forceinline__ void report_progress(const SweepArgs& a, const int L) {
+    if (a.progress != nullptr)
+        __hip_atomic_store(a.progress, a.progress_base + static_cast<unsigned>(L) + 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The end of a power iteration: its result, then the flag the host waits for.

@@ -248,7 +248,7 @@ __device__ __forceinline__ bool window_enter(const SweepArgs& a, const int L, co
     constexpr int NV = D * (1 + K);
     __shared__ SweepState s_cur;
     const int tid = flat_tid();
-    if (wg == 0 && tid == 0) report_progress(a.progress, L);
+    if (wg == 0 && tid == 0) report_progress(a, L);
     if (L == 0) {
         if (tid == 0) {
             SweepState st = ctl->slot[0];

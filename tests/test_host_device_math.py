@@ -1,0 +1,56 @@
+"""CPU tests of the plain arithmetic that host and device share (headers under
+csrc that a C++ compiler takes as they are): built into a small library here."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = r"""
+#include "planner.h"
+extern "C" int started(unsigned word, unsigned base) { return lx::launches_started(word, base); }
+extern "C" int exponent(double g) { return lx::power_exponent(g); }
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    d = tmp_path_factory.mktemp("shim")
+    (d / "shim.cpp").write_text(SOURCE)
+    subprocess.run([cxx, "-O2", "-std=c++17", "-ffp-contract=off", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2310_08344_amd", "csrc"), str(d / "shim.cpp"), "-o", str(d / "shim.so")],
+                   check=True)
+    lib = ctypes.CDLL(str(d / "shim.so"))
+    lib.exponent.argtypes = [ctypes.c_double]
+    lib.started.argtypes = [ctypes.c_uint, ctypes.c_uint]
+    return lib
+
+
+def test_progress_of_an_earlier_loop_counts_as_none(shim):
+    """A loop of 40 launches (base 0), then one with base 42: a late store of
+    the first loop must not let the second enqueue 40 launches at once.  The
+    counter may wrap."""
+    for base in (0, 42, 2**32 - 42, 2**32 - 1):
+        nxt = (base + 42) % 2**32
+        for launch in range(40):
+            assert shim.started((base + launch + 1) % 2**32, base) == launch + 1
+            assert shim.started((base + launch + 1) % 2**32, nxt) == 0
+        assert shim.started(base, base) == 0
+        assert shim.started((nxt + 1) % 2**32, nxt) == 1
+
+
+@pytest.mark.parametrize("g", [5e-324, 1e-310, 2.3e-308, 1e-120, 1e-17, 0.49, 0.5, 0.75, 1.0, 3.0, 4.0, 1e17, 1e300])
+def test_power_exponent_brings_the_bound_below_one(shim, g):
+    e = shim.exponent(g)
+    assert 0.5 <= g * 2.0 ** (e // 2) * 2.0 ** (e - e // 2) < 1.0
+
+
+def test_power_exponent_of_degenerate_bounds(shim):
+    for g in (0.0, float("inf"), float("nan")):
+        assert shim.exponent(g) == 0
