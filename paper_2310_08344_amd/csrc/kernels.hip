@@ -26,6 +26,7 @@
 #include <algorithm>
 
 #include "lx_device.h"
+#include "quotient.h"
 #include "sweep_device.h"
 
 namespace lx {
@@ -172,8 +173,8 @@ __global__ void to_fp32_kernel(const double* __restrict__ x, float* __restrict__
 // Bound by memory: two passes over a grid take 13 us at 2048^2, three 20 us, at
 // the rate of a large copy.  A point has 4 quotients (12 for the remainder) by
 // the same four spacings, 11 instructions each as divisions; as products with
-// the rounded reciprocal, corrected once by the exact residual, 3, with the
-// quotient's rounding.  Together with 64-bit indices by division this took 22
+// the rounded reciprocal, corrected once by the exact residual, 3 and a
+// selection, with the quotient's rounding (quotient_rcp).  Together with 64-bit indices by division this took 22
 // and 46 us, now 20 and 26 (512^2: 4.2 and 8.0, now 4.1 and 4.7).
 constexpr int kBurgersRows = 4, kBurgersTx = 64, kBurgersTy = kBlockThreads / kBurgersTx;
 
@@ -182,12 +183,10 @@ struct BurgersSpacing {
     double rxx, ryy, rx2, ry2;          // their reciprocals
 };
 
-// x / d, r = 1 / d rounded
 template <bool kRecip>
 __device__ __forceinline__ double quotient(const double x, const double d, const double r) {
     if constexpr (!kRecip) return x / d;
-    const double q = x * r;
-    return fma(fma(-q, d, x), r, q);
+    return quotient_rcp(x, d, r);
 }
 
 template <bool kRecip>

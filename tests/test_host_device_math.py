@@ -1,18 +1,22 @@
 """CPU tests of the plain arithmetic that host and device share (headers under
 csrc that a C++ compiler takes as they are): built into a small library here."""
 import ctypes
+import math
 import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
 #include "planner.h"
+#include "quotient.h"
 extern "C" int started(unsigned word, unsigned base) { return lx::launches_started(word, base); }
 extern "C" int exponent(double g) { return lx::power_exponent(g); }
+extern "C" double quotient(double x, double d) { return lx::quotient_rcp(x, d, 1.0 / d); }
 """
 
 
@@ -28,6 +32,8 @@ def shim(tmp_path_factory):
                    check=True)
     lib = ctypes.CDLL(str(d / "shim.so"))
     lib.exponent.argtypes = [ctypes.c_double]
+    lib.quotient.argtypes = [ctypes.c_double, ctypes.c_double]
+    lib.quotient.restype = ctypes.c_double
     lib.started.argtypes = [ctypes.c_uint, ctypes.c_uint]
     return lib
 
@@ -54,3 +60,18 @@ def test_power_exponent_brings_the_bound_below_one(shim, g):
 def test_power_exponent_of_degenerate_bounds(shim):
     for g in (0.0, float("inf"), float("nan")):
         assert shim.exponent(g) == 0
+
+
+def test_quotient_is_the_division(shim):
+    rng = np.random.default_rng(3)
+    xs = np.concatenate([rng.standard_normal(2000) * 10.0 ** rng.uniform(-130, 130, 2000), [0.0, -0.0, 1.0, -7.0]])
+    for d in np.concatenate([10.0 ** rng.uniform(-140, 140, 8), [1.0 / 2048, (1.0 / 333) ** 2, 2.0 / 96]]):
+        for x in xs:
+            assert shim.quotient(x, d) == x / d
+
+
+@pytest.mark.parametrize("x", [1e308, -1.7e308, float("inf"), float("-inf")])
+def test_quotient_that_overflows_is_an_infinity(shim, x):
+    for d in (1e-3, 1.0 / 4096, 1e-140):
+        assert shim.quotient(x, d) == math.copysign(math.inf, x)
+    assert math.isnan(shim.quotient(float("nan"), 0.25))
