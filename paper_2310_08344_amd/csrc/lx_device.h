@@ -24,10 +24,10 @@ struct SweepState {
     // leja_block (several iterations per launch, speculative windows):
     int blk_mode;            // 0: a window whose terms are added speculatively; 1: its re-execution
     int nt[kKMax];           // terms each output takes in this launch (0..depth; -j: stops after j)
-    int lev64;               // a window that switches to FP32 (out32 and not in32): y_{m+1} .. y_{m+lev64} are FP64
-    int switch_next;         // the window after the one re-executed starts in FP32
     int n_work;              // launches that did work so far
     int n_levels;            // operator applications they made
+    int lev64;               // a window that switches to FP32 (out32 and not in32): y_{m+1} .. y_{m+lev64} are FP64;
+                             // a re-execution in FP64: -1 if the next window starts in FP32
     double bytes_pp;         // their algorithmic bytes per grid point
 };
 

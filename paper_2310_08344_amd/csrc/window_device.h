@@ -135,9 +135,9 @@ __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const Swe
         nx.blk_mode = 0;
         nx.iter = prev.iter + D;
         nx.in32 = prev.out32;
-        if (kSwitch && prev.switch_next) {
+        if (kSwitch && prev.lev64 < 0) {
             nx.out32 = 1;
-            nx.lev64 = nx.switch_next = 0;
+            nx.lev64 = 0;
         }
         bool any = false;
 #pragma unroll
@@ -178,7 +178,7 @@ __device__ __forceinline__ SweepState block_decide(const LoopCtl& ctl, const Swe
 #pragma unroll
         for (int k = 0; k < K; ++k) nx.nt[k] = !prev.active[k] ? 0 : (v.stop[k] ? -v.j[k] : D);
         if (v.capped) nx.status = 3;   // LX_ENOTCONV
-        nx.switch_next = after == D ? 1 : 0;
+        if (after == D) nx.lev64 = -1;
     } else {
         nx.iter = m + D;
         nx.in32 = prev.out32;
