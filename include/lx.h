@@ -490,8 +490,8 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of
  * two iterations per launch, of windows of three to eight on LDS tiles and
  * by register marching (tile rows th or bands, workgroups), and, with any
- * nx, windows on register tiles (FP32 sweeps: where they cannot march).  It
- * keeps the fastest
+ * nx, windows on register tiles (FP32 sweeps: where they cannot march; left out
+ * where there is no memory for their buffers).  It keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration
  * shape with its depth, and of the two the one with the lower time per
@@ -535,7 +535,8 @@ lx_status lx_set_tile(lx_ctx* ctx, int tx, int ty, int ry, int vec, int nb);
  * and LX_OP_BURGERS2D with K <= 2, 6 for LX_OP_DIFFADV2D_UP3 with K = 1 in FP64) on
  * small and odd grids and for FP32 sweeps, and by register marching on larger
  * ones, else 2.
- * Automatic windows whose buffers cannot be allocated run as depth 2.
+ * Automatic windows, and tuned ones on register tiles, whose buffers cannot be
+ * allocated run as depth 2.
  * Depths 2..8 apply to grids with even nx and 16-byte aligned vectors; on
  * LDS tiles (FP64 sweeps) 3 and 4 to the diffusion-advection operators and
  * the Burgers Jacobian, 6 to LX_OP_DIFFADV2D (others fall back to 4, then

@@ -396,8 +396,8 @@ bool auto_windows(const lx_operator& op, int K, bool vec2_ok, Tile& t) {
 // tuned entry's, else auto_windows', else two.  Two or more need FP64 sweeps and 16-byte pairs;
 // windows of three or more need sides of depth x radius cells (else two),
 // and six the five-point diffusion-advection operator (else four).
-// windows_ok = false leaves the automatic choice at two (no memory for windows).
-// Returns true if windows were the automatic choice.
+// windows_ok = false (no memory for windows) leaves the automatic choice and an
+// entry on register tiles at two.  Returns true if one of them gave windows.
 bool choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok, Tile& t, bool windows_ok) {
     const bool pair_ok = op.prec == LX_FP64 && vec2_ok && op.nx % 2 == 0;
     // register-marching windows also take FP32 sweeps
@@ -408,15 +408,15 @@ bool choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok,
         if (it == ctx->tuned.end()) {
             if (windows_ok && auto_windows(op, K, vec2_ok, t)) return true;
         } else if (const int rd = lx::rtile_depth(opcode_of(op.kind), K);
-                   it->second.stream == 2 && it->second.depth == rd && rtile_ok(op, rd)) {
+                   windows_ok && it->second.stream == 2 && it->second.depth == rd && rtile_ok(op, rd)) {
             t.stream = 2;
             t.depth = it->second.depth;
-            return false;
+            return true;
         }
     }
     int depth = 2;
     if (ctx->depth_forced != 0) depth = ctx->depth_forced;
-    else if (it != ctx->tuned.end()) depth = it->second.depth;
+    else if (it != ctx->tuned.end() && windows_ok) depth = it->second.depth;
     // windows stage a halo of depth * radius cells, which the periodic index
     // wrap allows only on sides of at least that many cells
     // windows by register marching: forced by lx_set_window_kernel, else the
@@ -453,8 +453,10 @@ bool choose_depth(const lx_ctx* ctx, const lx_operator& op, int K, bool vec2_ok,
 lx_status ensure_blk_ws(lx_ctx* ctx, int K) {
     while (static_cast<int>(ctx->blk_ws.size()) < K) {
         double* p = nullptr;
-        if (hipMalloc(&p, sizeof(double) * ctx->n_max) != hipSuccess)
+        if (hipMalloc(&p, sizeof(double) * ctx->n_max) != hipSuccess) {
+            (void)hipGetLastError();   // not an error of the launches that follow
             return fail(ctx, LX_ENOMEM, "second output buffers of the multi-iteration loop");
+        }
         ctx->blk_ws.push_back(p);
     }
     return LX_OK;
@@ -517,7 +519,6 @@ lx_status run_leja(lx_ctx* ctx, const LejaCall& q) {
     const bool rule = choose_depth(ctx, op, K, vec2, t, true);
     if (rule && q.scratch == nullptr && ensure_blk_ws(ctx, K) != LX_OK) {
         // no memory for a second buffer per output: two iterations per launch
-        (void)hipGetLastError();
         (void)choose_depth(ctx, op, K, vec2, t, false);
     }
     const bool vec_rt = vec2 && nx % 2 == 0;   // register tiles load whole pairs
@@ -2035,9 +2036,8 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
     const int rd = lx::rtile_depth(opcode, K);
     bool fp32_marching = false;
     for (int depth : {4, 6, 8}) fp32_marching = fp32_marching || (fp32 && stream_ok(*op, K, depth));
-    if (rtile_ok(*op, rd) && !fp32_marching) {
-        s = ensure_blk_ws(ctx, K);
-        if (s != LX_OK) return cleanup(s);
+    // left out where there is no memory for a second buffer per output
+    if (rtile_ok(*op, rd) && !fp32_marching && ensure_blk_ws(ctx, K) == LX_OK) {
         const lx::RtileGrid g = lx::rtile_grid(opcode, rd, nx, ny, nx % 2 == 0);
         SweepArgs a{};
         a.nx = nx;
