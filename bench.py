@@ -357,7 +357,7 @@ def bench_paper_problems(lib, n: int = 8192, axpby_gbs=None, tune: bool = True, 
                 dt = time.perf_counter() - t0
                 gbs = nbytes / dt / 1e9
                 run = {"problem": "II" if source else "I", "h_cfl": cfl, "t_final": t_final, "steps": steps,
-                       "iters_first_last": [iters[0], iters[-1]], "seconds": round(dt, 4),
+                       "iters_first_last": [iters[0], iters[-1]], "depth": r.stats["depth"], "seconds": round(dt, 4),
                        "ms_per_step": round(dt * 1e3 / steps, 3), "gbs": round(gbs, 1),
                        "frac_of_8tbs": round(gbs / HBM_PEAK_GBS, 4),
                        "gbs_one_iteration_bytes": round(nbytes1 / dt / 1e9, 1)}

@@ -494,8 +494,9 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * where there is no memory for their buffers).  It keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration
- * shape with its depth, and of the two the one with the lower time per
- * iteration: later calls with the same (kind, nx, ny, K, prec) use them
+ * shape with its depth (register tiles: if a loop of 50 iterations ends sooner
+ * on them, with what their deeper windows form past its end), and of the two
+ * the one with the lower time per iteration: later calls with the same (kind, nx, ny, K, prec) use them
  * (the window kernel needs a second buffer per output, which this call
  * allocates and keeps in the context).  When the
  * environment variable LX_TUNE_CACHE names a file, the winners are

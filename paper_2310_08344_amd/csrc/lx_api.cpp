@@ -2079,7 +2079,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
         char line[112];
         std::snprintf(line, sizeof(line), "%d 64 8 %d 2 %d %.3f\n", 100 + rd, 8 * g.rw, a.nb, us);
         rep += line;
-        if (us < best_pair_us) {
+        if (lx::windows_faster(us, rd, best_pair_us, best.depth)) {
             best_pair_us = us;
             best.depth = rd;
             best.stream = 2;

@@ -16,6 +16,7 @@ SOURCE = r"""
 #include "quotient.h"
 extern "C" int started(unsigned word, unsigned base) { return lx::launches_started(word, base); }
 extern "C" int exponent(double g) { return lx::power_exponent(g); }
+extern "C" int windows_faster(double a, int da, double b, int db) { return lx::windows_faster(a, da, b, db); }
 extern "C" double quotient(double x, double d) { return lx::quotient_rcp(x, d, 1.0 / d); }
 """
 
@@ -34,6 +35,7 @@ def shim(tmp_path_factory):
     lib.exponent.argtypes = [ctypes.c_double]
     lib.quotient.argtypes = [ctypes.c_double, ctypes.c_double]
     lib.quotient.restype = ctypes.c_double
+    lib.windows_faster.argtypes = [ctypes.c_double, ctypes.c_int, ctypes.c_double, ctypes.c_int]
     lib.started.argtypes = [ctypes.c_uint, ctypes.c_uint]
     return lib
 
@@ -75,3 +77,10 @@ def test_quotient_that_overflows_is_an_infinity(shim, x):
     for d in (1e-3, 1.0 / 4096, 1e-140):
         assert shim.quotient(x, d) == math.copysign(math.inf, x)
     assert math.isnan(shim.quotient(float("nan"), 0.25))
+
+
+@pytest.mark.parametrize("a,da,b,db,faster", [(640.0, 6, 653.0, 4, 0), (600.0, 6, 653.0, 4, 1), (2.7, 8, 3.7, 8, 1),
+                                              (39.0, 8, 38.9, 8, 0), (11.4, 8, 1e300, 1, 1), (7.1, 8, 6.9, 2, 0)])
+def test_deeper_windows_must_win_back_what_they_form_past_the_end(shim, a, da, b, db, faster):
+    """Measured times per iteration (register tiles first)."""
+    assert shim.windows_faster(a, da, b, db) == faster
