@@ -19,6 +19,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -155,7 +156,8 @@ lx_status ensure_xi(lx_ctx* ctx, int M) {
 }
 
 // Waits until ready() (a read of pinned memory that a kernel on the stream
-// writes).  Every kQueryMs it asks whether the stream still runs (the query
+// writes), with a pause between two reads and a yield to other threads every
+// 256, a few microseconds.  Every kQueryMs it asks whether the stream still runs (the query
 // puts a marker on it, which costs 6 us between two launches): *idle is set
 // if everything on it has finished without ready().
 constexpr double kQueryMs = 20.0;
@@ -165,7 +167,9 @@ lx_status wait_for(lx_ctx* ctx, Ready ready, bool* idle) {
     auto t0 = std::chrono::steady_clock::now();
     for (unsigned n = 1;; ++n) {
         if (ready()) return LX_OK;
+        __builtin_ia32_pause();
         if ((n & 255u) != 0) continue;
+        std::this_thread::yield();
         const auto t1 = std::chrono::steady_clock::now();
         if (std::chrono::duration<double, std::milli>(t1 - t0).count() < kQueryMs) continue;
         t0 = t1;
