@@ -540,7 +540,8 @@ def main() -> int:
                        {2: "leja_pair (diffusion-advection, K=3, FP64, two iterations per launch)",
                         3: "leja_block (diffusion-advection, K=3, FP64, windows of three iterations)",
                         4: "leja_block (diffusion-advection, K=3, FP64, windows of four iterations)",
-                        6: "leja_block (diffusion-advection, K=3, FP64, windows of six iterations)"}.get(
+                        6: "leja_block (diffusion-advection, K=3, FP64, windows of six iterations)",
+                        8: "leja_rtile (diffusion-advection, K=3, FP64, windows of eight on register tiles)"}.get(
                            depth, "leja_sweep (diffusion-advection, K=3, FP64)")),
             "launches": launches, "avg_launch_us": round(sweep_ms * 1e3 / launches, 2),
             "iterations_per_launch": depth,

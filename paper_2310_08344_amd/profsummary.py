@@ -28,8 +28,9 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2310_08344_amd", "csrc")
 # the sources the FP64 Leja kernels (one, two and more iterations per launch) are compiled from
-SWEEP_SOURCES = ("kernels.hip", "pair.hip", "block.hip", "stream.hip", "tile_device.h", "sweep_device.h",
-                 "window_device.h", "lx_device.h")
+SWEEP_SOURCES = ("kernels.hip", "pair.hip", "block.hip", "stream.hip", "rtile.hip", "stream_device.h",
+                 "tile_device.h", "sweep_device.h", "window_device.h", "coef_device.h", "dd_math.h", "quotient.h",
+                 "lx_device.h")
 COPY_ELEMS = 1 << 26
 
 
