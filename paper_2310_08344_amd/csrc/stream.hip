@@ -23,7 +23,7 @@
 // tiles); along x the strip's side columns are formed by two wavefronts
 // (128 columns per at most 128 - 2D outputs).
 //
-// The outputs: for the diffusion-advection operators (ring windows, below)
+// The outputs: for the diffusion-advection operators (ring windows, stream_device.h)
 // every level also goes into a small ring in LDS and the outputs of row
 // t - D take all their terms at step t; otherwise (the Burgers Jacobian) an
 // output row enters the registers when level 0 reaches it, takes term j

@@ -1,5 +1,6 @@
-// The window loop's control, shared by its two kernels: leja_block (LDS
-// tiles, block.hip) and leja_stream (register streaming, stream.hip).
+// The window loop's control, shared by its kernels: leja_block (LDS tiles,
+// block.hip), leja_stream (register marching, stream.hip) and leja_rtile
+// (register tiles, rtile.hip).
 //
 // Launch w of the plain loop advances the Newton recurrence (Sec. 2.1,
 // Eq. (2)) from y_m (m = wD) through y_{m+1} .. y_{m+D}.  The stop rule
