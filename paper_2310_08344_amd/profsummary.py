@@ -107,7 +107,13 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, points: int, exit_bytes
     kf = [v * 1024 * scale_f for v in _values(f, kernel)]
     kw = [v * 1024 * scale_w for v in _values(w, kernel)]
     if len(kf) != len(kw):
-        raise SystemExit(f"{kernel}: {len(kf)} FETCH dispatches but {len(kw)} WRITE dispatches")
+        # launches that a loop enqueued past its end, whose number is the pace of
+        # the host: they move next to nothing
+        least = 0.5 * exit_bytes_per_point * points
+        kf = [v for v in kf if v >= least]
+        kw = [v for v in kw if v >= least]
+    if len(kf) != len(kw):
+        raise SystemExit(f"{kernel}: {len(kf)} working FETCH dispatches but {len(kw)} working WRITE dispatches")
     # working launches: those that moved at least exit_bytes_per_point bytes per point
     pairs = [(a, b) for a, b in zip(kf, kw) if exit_bytes_per_point * points <= a + b < max_bytes_per_point * points]
     return {
