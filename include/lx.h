@@ -217,7 +217,9 @@ lx_status lx_spectrum(lx_ctx* ctx, const lx_operator* op, const double* d_u,
  * or with LX_ENOTCONV after max_iters sweeps (outputs then hold the last
  * polynomial; with substeps, of the call that did not converge), or with
  * LX_ENONFINITE.  With more than one substep the call allocates, on first
- * use, up to 10 workspace vectors of the context's n_max. */
+ * use, up to 10 workspace vectors of the context's n_max; windows (see
+ * lx_set_depth, also as the automatic choice) one per output, kept by the
+ * context. */
 lx_status lx_phi_leja(lx_ctx* ctx, const lx_operator* op, const double* d_u,
                       const double* d_v, int K, const int* l, const double* alpha,
                       const double* sigma, double* const* d_out, double h,

@@ -266,9 +266,9 @@ __device__ __forceinline__ bool loop_ended(const LoopCtl* ctl) {
 
 // Adds the nb partial records of NV values written by the previous launch:
 // consecutive lanes hold consecutive values, 64 / NV records at a time per
-// wavefront, each lane in record order, then the lanes of a value and the
-// wavefronts in index order, so every workgroup of the grid obtains bitwise
-// the same totals.  Thread q < NV receives total q.
+// wavefront, each lane in record order, then the lanes of a value in a fixed
+// tree and the wavefronts in index order, so every workgroup of the grid obtains
+// bitwise the same totals.  Thread q < NV receives total q.
 template <int NV, int NW = kBlockThreads / 64>
 __device__ __forceinline__ double record_totals(const double* __restrict__ P, const int nb) {
     static_assert(NV <= 64, "a record per wavefront at least");
@@ -290,10 +290,15 @@ __device__ __forceinline__ double record_totals(const double* __restrict__ P, co
         }
         for (; o < end; o += step) acc += P[o];
     }
-    double s = 0.0;
+    // the lanes of a value folded in halves: log2 G steps (one by one they are
+    // 64 for one value, which cost a launch of one sweep 4 us)
+    const int g = lane / NV;
 #pragma unroll
-    for (int g = 0; g < G; ++g) s += __shfl(acc, (lane + g * NV) & 63, 64);
-    if (lane < NV) red[wid][lane] = s;
+    for (int w = (1 << log2_up(G)) / 2; w >= 1; w /= 2) {
+        const double o = __shfl(acc, (lane + w * NV) & 63, 64);
+        if (g < w && g + w < G) acc += o;
+    }
+    if (lane < NV) red[wid][lane] = acc;
     __syncthreads();
     double r = 0.0;
     if (tid < NV)
