@@ -492,7 +492,8 @@ lx_status lx_phi_leja_learned(lx_ctx* ctx, lx_predictor* p, int n, const lx_inst
  * (tx, ty, ry, vec, workgroups) and, for FP64 with even nx, the shapes of
  * two iterations per launch, of windows of three to eight on LDS tiles and
  * by register marching (tile rows th or bands, workgroups), and, with any
- * nx, windows on register tiles (FP32 sweeps: where they cannot march; left out
+ * nx, windows on register tiles (FP32 sweeps: where they cannot march, and
+ * deeper marching windows up to 1 % slower are taken; left out
  * where there is no memory for their buffers).  It keeps the fastest
  * one-sweep shape (used by the one-sweep power iteration, the right-hand
  * side of lx_linear_step and depth-1 loops) and the fastest multi-iteration

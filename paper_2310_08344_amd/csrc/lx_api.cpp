@@ -2024,7 +2024,7 @@ lx_status lx_tune(lx_ctx* ctx, const lx_operator* op, int K, int sweeps, char* r
                 char line[112];
                 std::snprintf(line, sizeof(line), "%d 64 1 %d 2 %d %.3f\n", 100 + depth, g.bands, a.nb, us);
                 rep += line;
-                if (us < best_pair_us) {
+                if (fp32 ? lx::fp32_marching_taken(us, depth, best_pair_us, best.depth) : us < best_pair_us) {
                     best_pair_us = us;
                     best.depth = depth;
                     best.stream = 1;

@@ -38,6 +38,15 @@ inline bool windows_faster(double a, int da, double b, int db) {
     return a * (m + da) < b * (m + db);
 }
 
+// Whether the tuner takes marching windows of FP32 sweeps of depth da at a us per
+// iteration instead of depth db at b.  The two go over to FP32 at different
+// iterations, so the choice shows in the results (by about 1e-9 at rtol 1e-6):
+// deeper windows are taken up to 1 % slower, the spread of these timings, so that
+// it turns on their noise for fewer grids (five-point operator, depth six over
+// depth four, five timings each: 980^2 1.00 to 1.01, 1024^2 0.98 to 1.01, 1200^2 0.98
+// to 1.00; elsewhere the two differ by more, 512^2 1.27, 2048^2 0.89).
+inline bool fp32_marching_taken(double a, int da, double b, int db) { return a < (da > db ? 1.01 * b : b); }
+
 // phi_l(z) for real z (Sec. 1 recursion; Taylor series near 0).
 double phi_scalar(int l, double z);
 

@@ -31,6 +31,7 @@ extern "C" void div_rcp(double xh, double xl, double yh, double yl, double ulps,
     o[0] = r.hi;
     o[1] = r.lo;
 }
+extern "C" int fp32_taken(double a, int da, double b, int db) { return lx::fp32_marching_taken(a, da, b, db); }
 extern "C" int windows_faster(double a, int da, double b, int db) { return lx::windows_faster(a, da, b, db); }
 extern "C" double quotient(double x, double d) { return lx::quotient_rcp(x, d, 1.0 / d); }
 """
@@ -54,6 +55,7 @@ def shim(tmp_path_factory):
     lib.inv_fact.argtypes = [ctypes.c_int, p]
     lib.phi.argtypes = [ctypes.c_int, ctypes.c_int, d, d, p]
     lib.div_rcp.argtypes = [d, d, d, d, d, p]
+    lib.fp32_taken.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
     lib.windows_faster.argtypes = [ctypes.c_double, ctypes.c_int, ctypes.c_double, ctypes.c_int]
     lib.started.argtypes = [ctypes.c_uint, ctypes.c_uint]
     return lib
@@ -155,3 +157,12 @@ def test_device_phi_has_the_accuracy_of_the_host_phi(shim, l):
             err, err_old = abs(_exact(o) / ref - 1), abs(_exact(old) / ref - 1)
             # (phi_0 below exp(-600) has no low part, below exp(-708) it is subnormal, in both forms)
             assert err <= max(mp.mpf("1e-29"), 4 * err_old), (z, err, err_old)
+
+
+@pytest.mark.parametrize("t4,t6,depth", [(3.0, 3.8, 4), (4.0, 3.99, 6), (4.0, 4.03, 6), (4.0, 4.05, 4), (7.2, 6.4, 6),
+                                         (10.9, 12.0, 4)])
+def test_tuned_fp32_marching_depth_turns_on_more_than_noise(shim, t4, t6, depth):
+    """Windows of six up to 1 % slower than windows of four are taken; of one
+    depth the faster."""
+    assert (6 if shim.fp32_taken(t6, 6, t4, 4) else 4) == depth
+    assert shim.fp32_taken(t4, 4, t4 * 1.001, 4) and not shim.fp32_taken(t4, 4, t4 * 0.999, 4)
